@@ -36,6 +36,7 @@ BatchLaunch batch_launch_params(bool f32, bool lds, int max_tbl, int64_t max_ele
 hipError_t batch_prepare(const BatchLaunch& L);
 hipError_t batch_launch(const BatchLaunch& L, void** args, unsigned* counter, hipStream_t s);
 int sur_nparams();
+int sur_halves();
 constexpr int kSurMaxEnvKnots = 512;   // the inference kernel stages the envelope in LDS
 constexpr int kAlphasMaxHints = 2048;  // alpha_s search hints staged in LDS
 int sur_out_width();
@@ -45,7 +46,7 @@ size_t sur_workspace_floats(int B);
 hipError_t sur_train_prepare();
 hipError_t sur_forward_backward(const SurBufs& b, const float* in, const float* T, int B, float* loss_out,
                                 hipStream_t s);
-hipError_t sur_train_begin(const SurBufs& b, int64_t step, int64_t nbatches, int total, float lr0, float lrf,
+hipError_t sur_train_begin(const SurBufs& b, int64_t step, int64_t nbatches, int B, int total, float lr0, float lrf,
                            float* loss_out, hipStream_t s);
 hipError_t sur_train_step(const SurBufs& b, const float* in, const float* T, int B, hipStream_t s);
 hipError_t sur_adam(const SurBufs& b, float lr, int step, hipStream_t s);
@@ -1304,7 +1305,7 @@ extern "C" int pdf_surrogate_create(int32_t member, uint64_t seed, int32_t* sid_
       o += nx + nq;
     }
   }
-  const size_t bp = align_up((size_t)NP * 4, 256), bpb = align_up((size_t)NP * 4, 256);  // Pb: hi and lo halves
+  const size_t bp = align_up((size_t)NP * 4, 256), bpb = align_up((size_t)sur_halves() * 2, 256);
   const size_t be = align_up(env.size() * 4, 256), bl = align_up(lxk.size() * 8, 256);
   hipError_t e = hipMalloc(&S.pmem, 4 * bp + bpb + 2 * be + bl + 2048 + align_up(sizeof(SurStep), 256));
   if (e != hipSuccess) return fail_hip(e, "hipMalloc(surrogate)");
@@ -1434,7 +1435,7 @@ extern "C" int pdf_surrogate_train(int32_t sid, const pdf_train_opts* opts, pdf_
   if (steps == 0) return PDF_OK;
   hipError_t e = sur_train_prepare();
   if (e != hipSuccess) return fail_hip(e, "surrogate training set-up");
-  e = sur_train_begin(S->b, S->step, nb, opts->total_steps, opts->lr, opts->lr_final, opts->loss_out, s);
+  e = sur_train_begin(S->b, S->step, nb, batch, opts->total_steps, opts->lr, opts->lr_final, opts->loss_out, s);
   if (e != hipSuccess) return fail_hip(e, "surrogate training start");
   if (opts->use_graph) {
     if (!S->exec || S->g_batch != batch || S->g_in != S->d_in || S->g_bmem != S->bmem) {

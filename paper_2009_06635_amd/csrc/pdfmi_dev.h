@@ -174,17 +174,18 @@ struct SurStep {
   int64_t step;      // global step: batch (step % nb), learning rate, Adam update number step + 1
   int64_t call;      // step index within the current train call (index into loss_out)
   int64_t nb;        // batches in the training set
+  int64_t row;       // first row of this step's batch: (step % nb) * batch
   int total;         // cosine schedule length
   float lr0, lrf;    // schedule end points
   float* loss_out;   // the call's per-step losses, or null
-  unsigned done;     // workgroups of the step's update kernel that have finished (the last one advances the step)
+  float lr, c1, c2;  // this step's learning rate and bias corrections (written by k_train_fb, read by k_train_update)
 };
 
 // Surrogate device buffers (parameters, Adam moments, gradient, training workspace).
 // Matrix operands are BF16 pairs (hi, lo) with value = hi + lo.
 struct SurBufs {
   float* P;                 // FP32 master parameters
-  unsigned short* Pb;       // BF16 halves of the parameters: [0, n) hi, [n, 2n) lo
+  unsigned short* Pb;       // BF16 halves of the parameters: [0, n) hi, [n, 2n) lo, then the transposed hi halves
   float *M, *V, *G;         // Adam moments, gradient
   float* loss;              // [1]
   float* wpart;             // per-slice partial gradients and losses of a training step
