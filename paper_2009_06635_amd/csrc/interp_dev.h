@@ -10,8 +10,64 @@
 
 namespace pdfmi {
 
+// Point-location tables as a kernel reads them: from LDS (staged copy of the
+// member's table block) or from global memory.
+struct Tables {
+  const double* knots;
+  const CellCoef* cells;
+  const QCell* qcells;
+  const short* hints;
+  const SubDesc* subs;
+  const LogEntry* logt;
+};
+
+__device__ __forceinline__ Tables tables_at(const unsigned char* base, const MemberDev& m) {
+  return Tables{reinterpret_cast<const double*>(base), reinterpret_cast<const CellCoef*>(base + m.cells_off),
+                reinterpret_cast<const QCell*>(base + m.qcells_off),
+                reinterpret_cast<const short*>(base + m.hints_off),
+                reinterpret_cast<const SubDesc*>(base + m.subs_off),
+                reinterpret_cast<const LogEntry*>(base + m.logt_off)};
+}
+
+__device__ __forceinline__ int high_word(double v) { return __double2hiint(v); }
+
+// ln v by table (Tang's method): v = 2^k z with z in [0.6875, 1.375), z in
+// interval i of 128 with c_i near its middle, r = z / c_i - 1, |r| <= 2^-7:
+// ln v = k ln 2 + ln c_i + log1p(r).  The two intervals next to 1 have c = 1,
+// so small logarithms keep their relative precision; ln 2 is split so that
+// k ln 2's high part is exact, the error of its sum with ln c_i is carried,
+// and the c_i are chosen so that ln c_i is a double to about 1/64 ulp.  Error
+// against long double: rms 0.28-0.31 ulp, as the correctly rounded result's,
+// at most 1 ulp.  About 25 instructions and one 16-byte table read; with the
+// library function (about 100) alpha_s of 1e7 points took 86 us, now 37.
+__device__ __forceinline__ double normal_log(double v, int kadd, const LogEntry* __restrict__ t) {
+  const int hi = high_word(v);
+  const int off = hi - kLogOrigin;
+  const LogEntry e = t[(off >> 13) & (kLogEntries - 1)];
+  const double z = __hiloint2double(hi - (off & (int)0xfff00000), __double2loint(v));
+  const double r = fma(z, e.inv, -1.0);
+  double q = fma(r, -1.0 / 8.0, 1.0 / 7.0);
+  q = fma(r, q, -1.0 / 6.0);
+  q = fma(r, q, 1.0 / 5.0);
+  q = fma(r, q, -1.0 / 4.0);
+  q = fma(r, q, 1.0 / 3.0);
+  q = fma(r, q, -0.5);
+  const double k = (double)((off >> 20) + kadd);
+  const double a = k * 0x1.62e42fefa3800p-1;  // high part of ln 2, 11 trailing zero bits
+  const double s = a + e.log;
+  const double err = e.log - (s - a);
+  return s + (r + fma(r * r, q, fma(k, 0x1.ef35793c76730p-45, err)));
+}
+// Arguments that are not positive normal numbers: subnormals scaled, the rest as the library function.
+__device__ __forceinline__ double fast_log(double v, const LogEntry* __restrict__ t) {
+  double l = normal_log(v, 0, t);
+  if ((unsigned)(high_word(v) - 0x00100000) >= 0x7fe00000u)  // not a positive normal number
+    l = v == 0.0 ? -INFINITY : (v > 0.0 && v < INFINITY ? normal_log(v * 0x1p54, -54, t) : (v > 0.0 ? v : NAN));
+  return l;
+}
+
 // Largest i in [0, n-2] with t[i] <= v, 0 if t[0] > v (t strictly increasing).
-__device__ __forceinline__ int find_cell(const double* __restrict__ t, int n, double v) {
+__device__ __forceinline__ int find_cell_binary(const double* __restrict__ t, int n, double v) {
   const int last = n - 2;
   int i = 0;
   int step = last > 0 ? (1 << (31 - __builtin_clz((unsigned)last))) : 0;
@@ -22,275 +78,175 @@ __device__ __forceinline__ int find_cell(const double* __restrict__ t, int n, do
   return i;
 }
 
-// Same index as find_cell, from the table's bucket hints (see HintAxis):
-// one hint read, then two independent knot comparisons.  v > 0.
-__device__ __forceinline__ int find_cell_hint(const double* __restrict__ t, int n, double v, const HintAxis& h,
-                                              const short* __restrict__ hints) {
-  if (h.off < 0) return find_cell(t, n, v);
-  const int last = n - 2;
-  const unsigned key = (unsigned)((unsigned long long)__double_as_longlong(v) >> h.shift);
-  const int b = min(max((int)(key - h.key0), 0), h.n - 1);
+// The same index from the table's bucket hints (see HintAxis): one hint read,
+// then two independent knot comparisons.  Knot i + 2 may lie one past the
+// table (whatever follows it in the block is read): the index is then at
+// least n-2 already and the comparison changes nothing.  Any v (NaN, <= 0)
+// gives an index in range.
+__device__ __forceinline__ int find_cell(const double* __restrict__ t, int n, double v, const HintAxis& h,
+                                         const short* __restrict__ hints) {
+  if (h.off < 0) return find_cell_binary(t, n, v);
+  const int b = min(max((int)((unsigned)high_word(v) >> h.shift) - h.key0, 0), h.n - 1);
   const int i = hints[h.off + b];
-  const int i1 = min(i + 1, last), i2 = min(i + 2, last);
-  return i + ((i + 1 <= last && t[i1] <= v) ? 1 : 0) + ((i + 2 <= last && t[i2] <= v) ? 1 : 0);
+  return min(i + (t[i + 1] <= v ? 1 : 0) + (t[i + 2] <= v ? 1 : 0), n - 2);
 }
 
-// Point-location tables as a kernel reads them: from LDS (staged copy of the
-// member's table block) or from global memory.
-struct Tables {
-  const double* knots;
-  const CellCoef* cells;
-  const short* hints;
-  const SubDesc* subs;
-};
-
-__device__ __forceinline__ Tables tables_at(const unsigned char* base, const MemberDev& m) {
-  return Tables{reinterpret_cast<const double*>(base), reinterpret_cast<const CellCoef*>(base + m.cells_off),
-                reinterpret_cast<const short*>(base + m.hints_off), reinterpret_cast<const SubDesc*>(base + m.subs_off)};
-}
-
-// Hermite weights of knots i-1..i+2 re-based onto the stencil that starts at
-// knot i - d (d = 0 left edge, 1 interior, 2 right edge).
+// Hermite weights of knots i-1..i+2 at cell parameter u (see CellCoef).  The
+// basis in factored form: 1 - u is exact, so every basis value keeps its
+// relative precision near u = 0 and u = 1 (the expanded forms cancel there,
+// leaving absolute errors of one ulp that the large weights of a cell next to
+// a much narrower one magnify).
 template <typename T>
-__device__ __forceinline__ void stencil_weights(double u64, const CellCoef& c, int d, T out[4]) {
-  // the Hermite basis in factored form: 1 - u is exact, so every basis value
-  // keeps its relative precision near u = 0 and u = 1 (the expanded forms
-  // cancel there, leaving absolute errors of one ulp that the large weights
-  // of a cell next to a much narrower one magnify)
+__device__ __forceinline__ void hermite_weights(double u64, const CellCoef& c, T r[4]) {
   const T u = (T)u64;
   const T w = (T)1 - u;
   const T u2 = u * u, w2 = w * w;
-  const T h00 = w2 * ((T)1 + (T)2 * u);
-  const T h10 = u * w2;
-  const T h01 = ((T)3 - (T)2 * u) * u2;
-  const T h11 = -(w * u2);
-  const bool L = c.hl >= 0.0, R = c.hr >= 0.0;
-  const double am1 = L ? -c.hl : 0.0, a0 = L ? c.hl - 0.5 : -1.0, a1 = L ? 0.5 : 1.0;
-  const double b0 = R ? -0.5 : -1.0, b1 = R ? 0.5 - c.hr : 1.0, b2 = R ? c.hr : 0.0;
-  T r[4];
-  r[0] = h10 * (T)am1;
-  r[1] = h00 + h10 * (T)a0 + h11 * (T)b0;
-  r[2] = h01 + h10 * (T)a1 + h11 * (T)b1;
-  r[3] = h11 * (T)b2;
-  out[0] = d == 0 ? r[1] : (d == 1 ? r[0] : (T)0);
-  out[1] = d == 0 ? r[2] : (d == 1 ? r[1] : r[0]);
-  out[2] = d == 0 ? r[3] : (d == 1 ? r[2] : r[1]);
-  out[3] = d == 1 ? r[3] : (d == 2 ? r[2] : (T)0);
+  const T h10 = u * w2, h11 = -(w * u2);
+  const T hl = (T)c.hl, hr = (T)c.hr, el = (T)c.el, er = (T)c.er;
+  r[0] = -(hl * h10);
+  r[1] = fma(w2, fma((T)2, u, (T)1), fma(hl - el, h10, -(er * h11)));   // h00 + ...
+  r[2] = fma(u2, fma((T)-2, u, (T)3), fma(er - hr, h11, el * h10));     // h01 + ...
+  r[3] = hr * h11;
 }
 
-// Cell parameter with exact 0 / 1 at the cell's knots.
-__device__ __forceinline__ double cell_u(double v, const CellCoef& c) {
-  return v == c.t0 ? 0.0 : (v == c.t1 ? 1.0 : log(v * c.inv_t0) * c.invD);
+// Cell parameter of v, exactly 0 at the cell's first knot.
+__device__ __forceinline__ double cell_u(double v, double t0, double l, double invD) {
+  return v == t0 ? 0.0 : l * invD;
 }
 
-// alpha_s at one Q^2 from the table (knots sk, values sv, cells sc); NaN for
-// Q^2 <= 0 or non-finite.
-__device__ __forceinline__ double alphas_point(const AlphasDev& A, const double* sk, const double* sv,
-                                               const CellCoef* sc, const short* sh, double q2) {
-  const bool valid = q2 > 0.0 && q2 < INFINITY;
-  if (!valid) return NAN;
-  if (q2 < sk[0]) return sv[0];
-  if (q2 > sk[A.n - 1]) return sv[A.n - 1];
-  int s = 0;
-  for (int j = 1; j < A.nseg; ++j)
-    if (A.seg_first[j] <= q2) s = j;
-  const int lo = A.seg_lo[s], hi = A.seg_hi[s];
-  const int m = hi - lo + 1;
-  const int c = lo + find_cell_hint(sk + lo, m, q2, A.seg_hint[s], sh);
-  const CellCoef cc = sc[c];
-  const int m4 = m < 4 ? m : 4;
-  const int st = min(max(c - 1, lo), hi - m4 + 1);
-  double w[4];
-  stencil_weights<double>(cell_u(q2, cc), cc, c - st, w);
-  double acc = w[0] * sv[st];
-  for (int a = 1; a < m4; ++a) acc = fma(w[a], sv[st + a], acc);
-  return acc;
+// Entry i of a table of E (multiplication in 24 bits: full rate).
+template <typename E>
+__device__ __forceinline__ const E& entry(const void* base, int i) {
+  return *reinterpret_cast<const E*>(static_cast<const unsigned char*>(base) +
+                                     __umul24((unsigned)i, (unsigned)sizeof(E)));
 }
 
-
-// The alpha_s table as a kernel reads it (staged in LDS) and where a fused
-// evaluation writes alpha_s: out == nullptr means no alpha_s output.
+// The alpha_s table as a kernel reads it (the block staged in LDS; logt is
+// the block's own or an equal copy) and where a fused evaluation writes
+// alpha_s: out == nullptr means no alpha_s output.
 struct AsView {
-  const double* k;
-  const double* v;
-  const CellCoef* c;
-  const short* h;
+  const unsigned char* base;
+  const LogEntry* logt;
   double* out;
 };
 
-struct PointLoc {
-  int mode;      // region bits | kXHigh | (anchor row << 8) for high Q^2
-  int k, ix, iq;
-  int sx, sq;    // stencil origin (first x and Q^2 knot of the 4x4 stencil)
-  int base;      // element offset of f[sx][sq][0]
-  int sa;        // element stride between x knots
-  double p0, p1; // extrapolation parameters
-};
-
-// Phase 1: everything that depends on the point only.
-template <typename T>
-__device__ __forceinline__ PointLoc locate_point(const MemberDev& m, const Tables& tb, double x, double q2, T w[4],
-                                                 T v[4]) {
-  PointLoc L;
-  L.p0 = 0.0;
-  L.p1 = 0.0;
-  const bool valid = (x > 0.0) && (x <= m.xmax) && (q2 > 0.0) && (q2 < INFINITY);
-  if (!valid) {
-    L.mode = kInvalid;
-    L.k = L.ix = L.iq = -1;
-    L.sx = L.sq = 0;
-    L.base = 0;
-    L.sa = 0;
-    for (int a = 0; a < 4; ++a) w[a] = v[a] = (T)0;
-    return L;
+// alpha_s at one Q^2: cubic Hermite in ln Q^2 inside a segment, constant
+// outside the knots; NaN for Q^2 <= 0 or non-finite.
+__device__ __forceinline__ double alphas_point(const AlphasDev& A, const AsView& av, double q2) {
+  const double* sk = reinterpret_cast<const double*>(av.base);
+  const int i = find_cell(sk, A.ncell + 1, q2, A.h, reinterpret_cast<const short*>(av.base + A.hints_off));
+  const AsCell& c = entry<AsCell>(av.base + A.cells_off, i);
+  const double u = cell_u(q2, c.t0, fast_log(q2 * c.inv_t0, av.logt), c.invD), w = 1.0 - u, u2 = u * u;
+  // f0 + h01 df + h10 d0 + h11 d1 (h00 = 1 - h01)
+  double acc = c.f0 + fma(u2 * fma(-2.0, u, 3.0), c.df, (u * w) * fma(w, c.d0, -(u * c.d1)));
+  if (!(q2 >= A.q_lo && q2 < A.q_hi)) {
+    acc = q2 < A.q_lo ? A.a_lo : A.a_hi;
+    if (!(q2 > 0.0 && q2 < INFINITY)) acc = NAN;
   }
-  int mode = 0;
-  if (x < m.xmin) mode |= kLowX;
-  if (q2 < m.qmin) mode |= kLowQ;
-  if (q2 > m.qmax) mode |= kHighQ;
-  int k = 0;
-  for (int j = 1; j < m.K; ++j)
-    if (m.sub[j].qfirst <= q2) k = j;
-  const SubDesc S = tb.subs[k];
-  const int ix = find_cell_hint(tb.knots + S.xk_off, S.nx, x, S.xh, tb.hints);
-  const int iq = find_cell_hint(tb.knots + S.qk_off, S.nq, q2, S.qh, tb.hints);
-  const CellCoef cx = tb.cells[S.xc_off + ix];
-  const CellCoef cq = tb.cells[S.qc_off + iq];
-  const int sx = min(max(ix - 1, 0), S.nxp - 4);
-  const int sq = min(max(iq - 1, 0), S.nqp - 4);
-  // one logarithm per axis whatever the region: below x_0 the cell is the
-  // first one and ux = ln(x/x_0) / ln(x_1/x_0) is the continuation parameter
-  // itself; above the last Q^2 knot uq - 1 = ln(Q^2/q_n-1) / ln(q_n-1/q_n-2)
-  const double ux = cell_u(x, cx);
-  const double uq = cell_u(q2, cq);
-  if (!(mode & kLowX)) {
-    stencil_weights<T>(ux, cx, ix - sx, w);
-  } else {
-    for (int a = 0; a < 4; ++a) w[a] = (T)0;
-    if (mode & (kLowQ | kHighQ)) L.p1 = ux; else L.p0 = ux;
-  }
-  if (!(mode & (kLowQ | kHighQ))) {
-    stencil_weights<T>(uq, cq, iq - sq, v);
-  } else {
-    for (int b = 0; b < 4; ++b) v[b] = (T)0;
-    if (mode & kLowQ) {
-      L.p0 = q2 * cq.inv_t0;                       // r = Q^2 / Q^2_0
-    } else {
-      L.p0 = uq - 1.0;                             // s = ln(Q^2/q_n-1) / ln(q_n-1/q_n-2)
-      mode |= (S.nq - 2 - sq) << 8;                // stencil row of q_n-2
-    }
-  }
-  if (x > 0.9) mode |= kXHigh;
-  L.mode = mode;
-  L.k = k;
-  L.ix = ix;
-  L.iq = iq;
-  L.sx = sx;
-  L.sq = sq;
-  const int Pp = sizeof(T) == 8 ? m.P64 : m.P32;
-  L.sa = S.nqp * Pp;
-  L.base = (int)((sizeof(T) == 8 ? S.val_off64 : S.val_off32) + (int64_t)(sx * S.nqp + sq) * Pp);
-  return L;
+  return acc;
 }
 
-// The same location in two halves, for points that share Q^2 (the two
-// lookups of a Monte-Carlo point): the Q^2 half (validity of Q^2, region bits,
-// sub-grid, Q^2 cell and weights) is computed once, the x half completes each
-// location.  locate_x(locate_q(q2), x) equals locate_point(x, q2) field by
-// field (the fused Monte-Carlo sum, which uses the halves, is compared bit
-// for bit with the unfused one, which uses locate_point); locate_point stays
-// one function because the split form compiles to a slower schedule in the
-// fused x*f + alpha_s kernel.
+// Location of a point in a member's grid, in two halves so that points that
+// share Q^2 (the two lookups of a Monte-Carlo point) locate it once.  Every
+// kernel uses these functions, so the fused and the separate evaluations agree
+// bit for bit.
+//
+// The stencil of a point: Q^2 knots sq .. sq+3 (kept inside the sub-grid) with
+// weights v; x knots ix-1 .. ix+2 with weights w, where a knot outside the
+// table is replaced by its neighbour ix or ix+1 (its weight is 0).  In rows of
+// P values the four x knots start at row, row + s1, + nqp, + s3 (each added to
+// the one before; s1 and s3 are nqp or 0).
 template <typename T>
 struct QLoc {
-  int mode;      // kInvalid (Q^2 <= 0 or not finite), else kLowQ | kHighQ | (anchor row << 8)
-  int k, iq, sq;
-  double p0;     // Q^2 continuation parameter (below Q^2_min: r; above Q^2_max: s)
   T v[4];
+  int row, nqp, kiq, d;
+  double u;  // cell parameter
+  double r;  // Q^2 / t0
 };
 
 template <typename T>
 __device__ __forceinline__ QLoc<T> locate_q(const MemberDev& m, const Tables& tb, double q2) {
+  const QCell& c = entry<QCell>(tb.qcells, find_cell(tb.knots + m.qk_off, m.nqk, q2, m.qh, tb.hints));
   QLoc<T> Q;
-  Q.p0 = 0.0;
-  for (int b = 0; b < 4; ++b) Q.v[b] = (T)0;
-  if (!((q2 > 0.0) && (q2 < INFINITY))) {
-    Q.mode = kInvalid;
-    Q.k = Q.iq = -1;
-    Q.sq = 0;
-    return Q;
-  }
-  int mode = 0;
-  if (q2 < m.qmin) mode |= kLowQ;
-  if (q2 > m.qmax) mode |= kHighQ;
-  int k = 0;
-  for (int j = 1; j < m.K; ++j)
-    if (m.sub[j].qfirst <= q2) k = j;
-  const SubDesc S = tb.subs[k];
-  const int iq = find_cell_hint(tb.knots + S.qk_off, S.nq, q2, S.qh, tb.hints);
-  const CellCoef cq = tb.cells[S.qc_off + iq];
-  const int sq = min(max(iq - 1, 0), S.nqp - 4);
-  // one logarithm whatever the region: above the last knot
-  // uq - 1 = ln(Q^2/q_n-1) / ln(q_n-1/q_n-2)
-  const double uq = cell_u(q2, cq);
-  if (!(mode & (kLowQ | kHighQ))) {
-    stencil_weights<T>(uq, cq, iq - sq, Q.v);
-  } else if (mode & kLowQ) {
-    Q.p0 = q2 * cq.inv_t0;                         // r = Q^2 / Q^2_0
-  } else {
-    Q.p0 = uq - 1.0;                               // s = ln(Q^2/q_n-1) / ln(q_n-1/q_n-2)
-    mode |= (S.nq - 2 - sq) << 8;                  // stencil row of q_n-2
-  }
-  Q.mode = mode;
-  Q.k = k;
-  Q.iq = iq;
-  Q.sq = sq;
+  Q.row = c.row;
+  Q.nqp = c.nqp;
+  Q.kiq = c.kiq;
+  Q.d = c.d;
+  Q.r = q2 * c.c.inv_t0;
+  Q.u = cell_u(q2, c.c.t0, fast_log(Q.r, tb.logt), c.c.invD);
+  if (q2 == m.qmax) Q.u = 1.0;
+  T r[4];
+  hermite_weights<T>(Q.u, c.c, r);
+  // r[0] (left end) and r[3] (right end) are 0 where the shift would lose them
+  const bool lo = c.d == 0, hi = c.d == 2;
+  Q.v[0] = lo ? r[1] : (hi ? (T)0 : r[0]);
+  Q.v[1] = lo ? r[2] : (hi ? r[0] : r[1]);
+  Q.v[2] = lo ? r[3] : (hi ? r[1] : r[2]);
+  Q.v[3] = lo ? (T)0 : (hi ? r[2] : r[3]);
   return Q;
 }
 
+struct PointLoc {
+  int mode;      // 0 inside the grid; else region bits | kXHigh | (anchor row << 8) for high Q^2
+  int ix;
+  int row, s1, s3;  // stencil rows (see above; nqp from the QLoc)
+  double p0, p1; // extrapolation parameters
+};
+
+// Completes the location of (x, q2) given Q = locate_q(q2): x weights w, and
+// for points outside the grid the region and its parameters.  v: the Q^2
+// weights the point uses (Q.v inside).
 template <typename T>
-__device__ __forceinline__ PointLoc locate_x(const MemberDev& m, const Tables& tb, const QLoc<T>& Q, double x, T w[4],
-                                             T v[4]) {
+__device__ __forceinline__ PointLoc locate_x(const MemberDev& m, const Tables& tb, const QLoc<T>& Q, double x,
+                                             double q2, T w[4], T v[4]) {
   PointLoc L;
+  int nx = m.nx, xk = m.xk_off, xc = m.xc_off;
+  HintAxis xh = m.xh;
+  if (!m.shared_x) {
+    const SubDesc S = tb.subs[Q.kiq >> 16];
+    nx = S.nx;
+    xk = S.xk_off;
+    xc = S.xc_off;
+    xh = S.xh;
+  }
+  const int ix = find_cell(tb.knots + xk, nx, x, xh, tb.hints);
+  const CellCoef& c = entry<CellCoef>(tb.cells, xc + ix);
+  const double u = cell_u(x, c.t0, fast_log(x * c.inv_t0, tb.logt), c.invD);
+  hermite_weights<T>(u, c, w);
+#pragma unroll
+  for (int b = 0; b < 4; ++b) v[b] = Q.v[b];
+  L.mode = 0;
   L.p0 = 0.0;
   L.p1 = 0.0;
-  if ((Q.mode & kInvalid) || !((x > 0.0) && (x <= m.xmax))) {
-    L.mode = kInvalid;
-    L.k = L.ix = L.iq = -1;
-    L.sx = L.sq = 0;
-    L.base = 0;
-    L.sa = 0;
-    for (int a = 0; a < 4; ++a) w[a] = v[a] = (T)0;
-    return L;
-  }
-  int mode = Q.mode;
-  const bool qout = mode & (kLowQ | kHighQ);
-  const SubDesc S = tb.subs[Q.k];
-  const int ix = find_cell_hint(tb.knots + S.xk_off, S.nx, x, S.xh, tb.hints);
-  const CellCoef cx = tb.cells[S.xc_off + ix];
-  const int sx = min(max(ix - 1, 0), S.nxp - 4);
-  // below x_0 the cell is the first one and ux = ln(x/x_0) / ln(x_1/x_0) is
-  // the continuation parameter itself
-  const double ux = cell_u(x, cx);
-  if (!(x < m.xmin)) {
-    stencil_weights<T>(ux, cx, ix - sx, w);
-  } else {
-    mode |= kLowX;
-    for (int a = 0; a < 4; ++a) w[a] = (T)0;
-    if (qout) L.p1 = ux; else L.p0 = ux;
-  }
-  if (qout) L.p0 = Q.p0;
-  for (int b = 0; b < 4; ++b) v[b] = Q.v[b];
-  if (x > 0.9) mode |= kXHigh;
-  L.mode = mode;
-  L.k = Q.k;
   L.ix = ix;
-  L.iq = Q.iq;
-  L.sx = sx;
-  L.sq = Q.sq;
-  const int Pp = sizeof(T) == 8 ? m.P64 : m.P32;
-  L.sa = S.nqp * Pp;
-  L.base = (int)((sizeof(T) == 8 ? S.val_off64 : S.val_off32) + (int64_t)(sx * S.nqp + Q.sq) * Pp);
+  L.s1 = ix > 0 ? Q.nqp : 0;
+  L.s3 = ix < nx - 2 ? Q.nqp : 0;
+  L.row = Q.row + (int)__umul24((unsigned)ix, (unsigned)Q.nqp) - L.s1;
+  if (!(x >= m.xmin && x < m.xmax && q2 >= m.qmin && q2 <= m.qmax)) {
+    if (x == m.xmax) {  // the last knot: exact weights
+      w[0] = w[1] = w[3] = (T)0;
+      w[2] = (T)1;
+    }
+    const bool valid = (x > 0.0) && (x <= m.xmax) && (q2 > 0.0) && (q2 < INFINITY);
+    const bool lowx = x < m.xmin, lowq = q2 < m.qmin, highq = q2 > m.qmax;
+    if (!valid) {
+      L.mode = kInvalid;
+    } else if (lowx || lowq || highq) {
+      // one logarithm per axis whatever the region: below x_0 the cell is the
+      // first one and u = ln(x/x_0) / ln(x_1/x_0) is the continuation
+      // parameter itself; above the last Q^2 knot
+      // Q.u - 1 = ln(Q^2/q_n-1) / ln(q_n-1/q_n-2), and the stencil row of q_n-2 is Q.d
+      L.mode = (lowx ? kLowX : 0) | (lowq ? kLowQ : 0) | (highq ? kHighQ | (Q.d << 8) : 0) | (x > 0.9 ? kXHigh : 0);
+      if (lowq) L.p0 = Q.r; else if (highq) L.p0 = Q.u - 1.0; else L.p0 = u;
+      if (lowx && (lowq || highq)) L.p1 = u;
+    }
+    if (!valid || lowx)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) w[a] = (T)0;
+    if (!valid || lowq || highq)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) v[b] = (T)0;
+  }
   return L;
 }
 
@@ -363,68 +319,89 @@ __device__ __forceinline__ T interp_stencil(const T F[4][4], const T w[4], const
 }
 
 // Extrapolated value of one column (rare path).  f points at the column's
-// entry of the stencil origin; only the anchor knots the formula needs are
-// read:
+// entry of the stencil's first row; s1, sa, s3 are the steps between its x
+// knots and Pp the stride between Q^2 knots (elements).  Only the anchor knots
+// the formula needs are read:
 //   x below x_min only:     rows x_0, x_1 interpolated in Q^2
 //   Q^2 outside, x inside:  the two anchor Q^2 rows interpolated in x
 //   corners:                the four anchor knot values
+// (below x_min the cell is the first one: x_0 and x_1 are the stencil's
+// second and third x knot)
 struct Wts {
   double w0, w1, w2, w3, v0, v1, v2, v3;
 };
 
 template <typename T>
-__device__ __noinline__ double extrap_entry(const T* f, int sa, int Pp, int mode, Wts wt, double p0, double p1,
-                                            double invL01) {
+static __device__ __noinline__ double extrap_entry(const T* f, int s1, int sa, int s3, int Pp, int mode, Wts wt, double p0,
+                                            double p1, double invL01) {
   const double w[4] = {wt.w0, wt.w1, wt.w2, wt.w3};
   const double v[4] = {wt.v0, wt.v1, wt.v2, wt.v3};
+  const T* fx[4] = {f, f + s1, f + s1 + sa, f + s1 + sa + s3};
   const bool lowx = mode & kLowX, lowq = mode & kLowQ, highq = mode & kHighQ;
   double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
   if (lowx && !(lowq || highq)) {
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-      a0 += v[b] * (double)f[b * Pp];
-      a1 += v[b] * (double)f[sa + b * Pp];
+      a0 += v[b] * (double)fx[1][b * Pp];
+      a1 += v[b] * (double)fx[2][b * Pp];
     }
   } else {
     const int ra = lowq ? 0 : (mode >> 8) & 3;
     if (!lowx) {
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
-        a0 += w[a] * (double)f[a * sa + ra * Pp];
-        a1 += w[a] * (double)f[a * sa + (ra + 1) * Pp];
+        a0 += w[a] * (double)fx[a][ra * Pp];
+        a1 += w[a] * (double)fx[a][(ra + 1) * Pp];
       }
     } else {
-      a0 = (double)f[ra * Pp];
-      a1 = (double)f[sa + ra * Pp];
-      a2 = (double)f[(ra + 1) * Pp];
-      a3 = (double)f[sa + (ra + 1) * Pp];
+      a0 = (double)fx[1][ra * Pp];
+      a1 = (double)fx[2][ra * Pp];
+      a2 = (double)fx[1][(ra + 1) * Pp];
+      a3 = (double)fx[2][(ra + 1) * Pp];
     }
   }
   return extrapolate(mode, a0, a1, a2, a3, p0, p1, invL01);
 }
 
-
-// Value of one stored column at one point (location, weights, stencil and,
-// outside the grid, the extrapolation formula); NaN for an invalid point.
+// Per-point record of a located point, written by one lane and read by
+// others: weights and location side by side (80 bytes in FP64, 48 in FP32), so
+// that the 9-16 different records one load instruction reads fall in
+// different LDS banks.  Locations are bytes: the stencil's first row and the
+// steps between its x knots.  All are multiples of 16; the low bits carry the
+// point's state: bits 0 and 1 of o say outside the grid and invalid, and the
+// low four bits of s1 and s3 hold the mode of a point that is either.
 template <typename T>
-__device__ __forceinline__ T interp_point(const MemberDev& m, const Tables& tb, double x, double q2, int col,
-                                          double invL01) {
-  T w[4], v[4];
-  const PointLoc L = locate_point<T>(m, tb, x, q2, w, v);
-  if (L.mode & kInvalid) return (T)NAN;
-  const int Pp = sizeof(T) == 8 ? m.P64 : m.P32;
-  const T* f = member_values<T>(m) + L.base + col;
-  if (!(L.mode & (kLowX | kLowQ | kHighQ))) {
-    T F[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int b = 0; b < 4; ++b) F[a][b] = f[a * L.sa + b * Pp];
-    return interp_stencil<T>(F, w, v);
+struct PointRec {
+  T w[4];
+  T v[4];
+  int o, s1, sa, s3;
+};
+constexpr int kRecSlow = 1, kRecInvalid = 2;
+
+template <typename T>
+__device__ __forceinline__ void set_stencil(PointRec<T>& r, const QLoc<T>& Q, const PointLoc& L, int rowb) {
+  r.o = (int)__umul24((unsigned)L.row, (unsigned)rowb);
+  r.sa = (int)__umul24((unsigned)Q.nqp, (unsigned)rowb);
+  r.s1 = L.s1 ? r.sa : 0;
+  r.s3 = L.s3 ? r.sa : 0;
+  if (L.mode) {
+    r.o |= L.mode & kInvalid ? kRecInvalid : kRecSlow;
+    r.s1 |= L.mode & 15;  // region
+    r.s3 |= (L.mode & kXHigh ? 1 : 0) | ((L.mode >> 8) & 3) << 1;
   }
-  const Wts wt{(double)w[0], (double)w[1], (double)w[2], (double)w[3],
-               (double)v[0], (double)v[1], (double)v[2], (double)v[3]};
-  return (T)extrap_entry<T>(f, L.sa, Pp, L.mode, wt, L.p0, L.p1, invL01);
+}
+
+// One column of a point outside the grid (kRecSlow); col0 points at the
+// column's entry of grid row 0.
+template <typename T>
+__device__ __forceinline__ T rec_extrapolate(const PointRec<T>& r, const T* col0, int Pp, double p0, double p1,
+                                             double invL01) {
+  const int mode = (r.s1 & 15) | (r.s3 & 1 ? kXHigh : 0) | ((r.s3 >> 1) & 3) << 8;
+  const int es = (int)sizeof(T);
+  const Wts wt{(double)r.w[0], (double)r.w[1], (double)r.w[2], (double)r.w[3],
+               (double)r.v[0], (double)r.v[1], (double)r.v[2], (double)r.v[3]};
+  const T* f = reinterpret_cast<const T*>(reinterpret_cast<const unsigned char*>(col0) + (r.o & ~15));
+  return (T)extrap_entry<T>(f, (r.s1 & ~15) / es, r.sa / es, (r.s3 & ~15) / es, Pp, mode, wt, p0, p1, invL01);
 }
 
 }  // namespace pdfmi

@@ -146,25 +146,7 @@ __device__ __forceinline__ void stage_rows(T* dst, const T* src, int rows, int P
 // afterwards, one point at a time across the wave.
 constexpr int kWave = 64;
 
-// Per-point record of phase 1, read back by the wave's own lanes in phase 2.
-struct PointInfo {
-  int boff;  // byte offset of the stencil origin f[sx][sq][0] in the member's values
-  int sab;   // byte stride between consecutive x knots
-  int mode;  // region bits (see locate_point)
-  int pad;
-};
-
 __device__ constexpr AlphasDev kNoAlphas{};
-
-// A point's record: weights and location side by side (80 bytes in FP64,
-// 48 in FP32), so that the 9-16 different records one phase-2 load
-// instruction reads fall in different LDS banks.
-template <typename T>
-struct PointRec {
-  T w[4];
-  T v[4];
-  PointInfo info;
-};
 
 template <typename T>
 __host__ __device__ constexpr size_t wave_record_bytes() {
@@ -203,26 +185,23 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
   const int e_dp = kWave / NE, e_dj = kWave - (kWave / NE) * NE;
   if constexpr (kAlphas) {  // alpha_s at the same points (fused evaluation), counted like pdf_alphas_q2
     const bool qbad = lane < tp && !(qv > 0.0 && qv < INFINITY);
-    if (lane < tp) av.out[lane] = alphas_point(A, av.k, av.v, av.c, av.h, qv);
+    if (lane < tp) av.out[lane] = alphas_point(A, av, qv);
     const unsigned long long qb = __ballot(qbad);
     if (qb && lane == 0) atomicAdd(nerr, (unsigned long long)__popcll(qb));
   }
   bool bad = false, slow = false;
   if (lane < tp) {
-    T w[4], v[4];
-    const PointLoc L = locate_point<T>(m, tb, xv, qv, w, v);
+    PointRec<T> r;
+    const QLoc<T> Q = locate_q<T>(m, tb, qv);
+    const PointLoc L = locate_x<T>(m, tb, Q, xv, qv, r.w, r.v);
     bad = L.mode & kInvalid;
     slow = L.mode & kSlow;
-    PointRec<T> r;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      r.w[a] = w[a];
-      r.v[a] = v[a];
+    set_stencil(r, Q, L, rowb);
+    if (L.mode) {
+      sp[2 * lane] = L.p0;
+      sp[2 * lane + 1] = L.p1;
     }
-    r.info = PointInfo{L.base * (int)sizeof(T), L.sa * (int)sizeof(T), L.mode, 0};
     srec[lane] = r;
-    sp[2 * lane] = L.p0;
-    sp[2 * lane + 1] = L.p1;
   }
   const unsigned long long bal = __ballot(bad);
   if (bal && lane == 0) atomicAdd(nerr, (unsigned long long)__popcll(bal));
@@ -237,15 +216,17 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
   const int nev = tp * NE;
   int p = e_p0, j = e_j0;
   for (int e = lane; e < nev; e += kWave) {
-    const PointInfo pi = srec[p].info;
-    if (!(pi.mode & kSlow)) {
+    const PointRec<T>& pr = srec[p];
+    const int po = pr.o;
+    if (!(po & kRecSlow)) {
       T w[4], v[4];
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
-        w[a] = srec[p].w[a];
-        v[a] = srec[p].v[a];
+        w[a] = pr.w[a];
+        v[a] = pr.v[a];
       }
-      const bool inv = pi.mode & kInvalid;
+      const int s1 = pr.s1, sa = pr.sa, s3 = pr.s3;
+      const bool inv = po & kRecInvalid;
       int c0;       // first output column of this entry
       int ccol;     // its stored column (-1: flavour absent from the grid)
       if constexpr (G == 1) {
@@ -263,11 +244,12 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
 #pragma unroll
         for (int i = 0; i < G; ++i) res[i] = (T)0;
       } else {
-        const int o0 = pi.boff + ccol * (int)sizeof(T);
+        const int o0 = po + ccol * (int)sizeof(T);
+        const int ox[4] = {o0, o0 + s1, o0 + s1 + sa, o0 + s1 + sa + s3};
         T F[G][4][4];
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-          const int oa = o0 + a * pi.sab;
+          const int oa = ox[a];
 #pragma unroll
           for (int b = 0; b < 4; ++b) {
             T q[G];
@@ -310,17 +292,12 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
   while (slow_mask) {
     const int q = __builtin_ctzll(slow_mask);
     slow_mask &= slow_mask - 1;
-    const PointInfo pi = srec[q].info;
     const PointRec<T>& rq = srec[q];
-    const Wts wt{(double)rq.w[0], (double)rq.w[1], (double)rq.w[2], (double)rq.w[3],
-                 (double)rq.v[0], (double)rq.v[1], (double)rq.v[2], (double)rq.v[3]};
     for (int jj = lane; jj < R; jj += kWave) {
       const int col = G == 1 ? scol[jj] : jj;
       T val = (T)0;
       if (col >= 0) {
-        const T* f = reinterpret_cast<const T*>(reinterpret_cast<const unsigned char*>(kLdsGrid ? sgrid : gvals) +
-                                                pi.boff) + col;
-        val = (T)extrap_entry<T>(f, pi.sab / (int)sizeof(T), Pp, pi.mode, wt, sp[2 * q], sp[2 * q + 1], invL01);
+        val = rec_extrapolate(rq, (kLdsGrid ? sgrid : gvals) + col, Pp, sp[2 * q], sp[2 * q + 1], invL01);
       }
       obase[q * R + jj] = val;
     }
@@ -333,6 +310,12 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
 #ifndef PDFMI_WAVES_PER_EU
 #define PDFMI_WAVES_PER_EU 1
 #endif
+
+// Bytes of the alpha_s block a kernel stages: all of it, or without its
+// logarithm table when the member's (equal) one is in LDS already.
+__host__ __device__ static inline int alphas_staged_bytes(const AlphasDev& A, bool member_tables) {
+  return member_tables ? A.logt_off : A.bytes;
+}
 
 // LDS layout of k_xfxq2 and k_batched: [location tables][column map][per-wave
 // records][grid values], the tables only when they are staged (kLdsTables)
@@ -351,32 +334,16 @@ void k_xfxq2(MemberDev m, ReqCols rc, const double* __restrict__ X, const double
   T* sgrid = reinterpret_cast<T*>(srec + kWaves * wave_record_bytes<T>());
   // alpha_s table (fused alpha_s output only), after the staged grid
   unsigned char* sas = reinterpret_cast<unsigned char*>(sgrid) + (kLdsGrid ? (size_t)lds_grid_elems * sizeof(T) : 0);
-  const int an2 = (A.n + 1) & ~1;
-  AsView av{reinterpret_cast<const double*>(sas), reinterpret_cast<const double*>(sas) + an2,
-            reinterpret_cast<const CellCoef*>(reinterpret_cast<const double*>(sas) + 2 * an2),
-            reinterpret_cast<const short*>(reinterpret_cast<const CellCoef*>(reinterpret_cast<const double*>(sas) +
-                                                                               2 * an2) + an2),
-            nullptr};
-  if constexpr (kAlphas) {
-    double* k = const_cast<double*>(av.k);
-    double* v = const_cast<double*>(av.v);
-    CellCoef* c = const_cast<CellCoef*>(av.c);
-    short* h = const_cast<short*>(av.h);
-    for (int i = threadIdx.x; i < A.n; i += BS) {
-      k[i] = A.knots[i];
-      v[i] = A.vals[i];
-      c[i] = A.cells[i];
-    }
-    for (int i = threadIdx.x; i < A.nhints; i += BS) h[i] = A.hints[i];
-  }
-
+  AsView av{sas, nullptr, nullptr};
+  if constexpr (kAlphas) stage_copy<BS>(sas, A.tables, alphas_staged_bytes(A, kLdsTables));
   if constexpr (kLdsTables) stage_copy<BS>(stbl, m.tables, m.tbl_bytes);
   for (int i = threadIdx.x; i < rc.n; i += BS) scol[i] = rc.col[i];
   const T* __restrict__ gvals = member_values<T>(m);
   const uint32_t gbytes = (uint32_t)((sizeof(T) == 8 ? m.elems64 : m.elems32) * (int64_t)sizeof(T));
   if constexpr (kLdsGrid) stage_copy<BS>(sgrid, gvals, (int64_t)lds_grid_elems * (int64_t)sizeof(T));
   __syncthreads();
-  const Tables tb = kLdsTables ? tables_at(stbl, m) : Tables{m.knots, m.cells, m.hints, m.subs};
+  const Tables tb = tables_at(kLdsTables ? stbl : m.tables, m);
+  av.logt = kLdsTables ? tb.logt : reinterpret_cast<const LogEntry*>(sas + A.logt_off);
 
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -415,36 +382,27 @@ __global__ __launch_bounds__(256) void k_locate(MemberDev m, const double* __res
                                                 int32_t* __restrict__ iqo, int8_t* __restrict__ rego) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     double w[4], v[4];
-    const PointLoc L = locate_point<double>(m, Tables{m.knots, m.cells, m.hints, m.subs}, X[i], Q2[i], w, v);
-    ko[i] = L.k;
-    ixo[i] = L.ix;
-    iqo[i] = L.iq;
+    const Tables tb = tables_at(m.tables, m);
+    const QLoc<double> Q = locate_q<double>(m, tb, Q2[i]);
+    const PointLoc L = locate_x<double>(m, tb, Q, X[i], Q2[i], w, v);
+    const bool bad = L.mode & kInvalid;
+    ko[i] = bad ? -1 : Q.kiq >> 16;
+    ixo[i] = bad ? -1 : L.ix;
+    iqo[i] = bad ? -1 : Q.kiq & 0xffff;
     rego[i] = (int8_t)(L.mode & (kLowX | kLowQ | kHighQ | kInvalid));
   }
 }
 
-// alpha_s(Q^2) (paper section 2.3): segment (repeated knot = threshold, the
-// upper segment owns it), FP64 knot search, cubic Hermite in ln Q^2 with
-// one-sided slopes at segment ends, constant outside the knots.  The table
-// (knots, values, cell coefficients) is staged in LDS once per workgroup.
-constexpr int kAlphasMaxKnots = 256;
-
-// alpha_s(Q^2) at n points, the table and its search hints staged in LDS;
-// four independent evaluations in flight per lane.
-constexpr int kAlphasMaxHints = 2048;
-
+// alpha_s(Q^2) at n points (paper section 2.3): segment (repeated knot =
+// threshold, the upper segment owns it), FP64 knot search, cubic Hermite in
+// ln Q^2 with one-sided slopes at segment ends, constant outside the knots.
+// The table block (at most 28 KB) is staged in LDS once per workgroup; four
+// independent evaluations in flight per lane.
 __global__ __launch_bounds__(256) void k_alphas(AlphasDev A, const double* __restrict__ Q2, int64_t n,
                                                 double* __restrict__ out, unsigned long long* __restrict__ nerr) {
-  __shared__ double sk[kAlphasMaxKnots];
-  __shared__ double sv[kAlphasMaxKnots];
-  __shared__ CellCoef sc[kAlphasMaxKnots];
-  __shared__ short sh[kAlphasMaxHints];
-  for (int i = threadIdx.x; i < A.n; i += 256) {
-    sk[i] = A.knots[i];
-    sv[i] = A.vals[i];
-    sc[i] = A.cells[i];
-  }
-  for (int i = threadIdx.x; i < A.nhints; i += 256) sh[i] = A.hints[i];
+  extern __shared__ __align__(16) unsigned char sas[];
+  stage_copy<256>(sas, A.tables, A.bytes);
+  const AsView av{sas, reinterpret_cast<const LogEntry*>(sas + A.logt_off), nullptr};
   __syncthreads();
   // each wave takes 256 consecutive points per step, lane l the points l + 64 j
   // (j = 0..3): every load and store instruction covers 512 contiguous bytes.
@@ -470,7 +428,7 @@ __global__ __launch_bounds__(256) void k_alphas(AlphasDev A, const double* __res
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int64_t i = c * 256 + j * 64 + lane;
-      const double r = alphas_point(A, sk, sv, sc, sh, q[j]);
+      const double r = alphas_point(A, av, q[j]);
       if (i < n) out[i] = r;
       cnt += __popcll(__ballot(i < n && !(q[j] > 0.0 && q[j] < INFINITY)));
     }
@@ -486,14 +444,12 @@ __global__ __launch_bounds__(256) void k_alphas(AlphasDev A, const double* __res
 // Location tables up to this size are staged in LDS (typical sets need
 // 10-40 KB: a few hundred knots of 8 bytes plus 48 bytes of coefficients per
 // cell); larger ones are read from global memory.
-constexpr size_t kMaxLdsTables = 56 * 1024;
+constexpr size_t kMaxLdsTables = 64 * 1024;
 static bool tables_fit(const MemberDev& m) { return (size_t)m.tbl_bytes <= kMaxLdsTables; }
 
-// LDS bytes of the alpha_s table staged for a fused alpha_s output.
-size_t alphas_lds_bytes(const AlphasDev* A) {
-  if (!A) return 0;
-  const size_t an2 = (size_t)((A->n + 1) & ~1);
-  return an2 * (8 + 8 + sizeof(CellCoef)) + (size_t)A->nhints * 2;
+// LDS bytes of the alpha_s table staged for a fused alpha_s output (member_tables: beside the member's tables).
+size_t alphas_lds_bytes(const AlphasDev* A, bool member_tables) {
+  return A ? (size_t)alphas_staged_bytes(*A, member_tables) : 0;
 }
 
 // LDS bytes of k_xfxq2 other than the staged grid, for a block of bs threads.
@@ -510,7 +466,7 @@ constexpr int64_t kStageTablesMinPoints = 32768;
 constexpr int kBlockTables = 512;   // tables staged in LDS, grid read from global memory
 constexpr int kBlockLds = 1024;     // tables and grid staged once per workgroup in LDS
 size_t xfxq2_shared_bytes(const MemberDev& m, bool f32) {
-  return shared_bytes(m, f32, kBlockLds, true) + alphas_lds_bytes(nullptr);
+  return shared_bytes(m, f32, kBlockLds, true);
 }
 
 // Launch context: the alpha_s table and output of a fused evaluation (A and
@@ -539,7 +495,7 @@ static hipError_t launch_xfxq2_g(const MemberDev& m, const ReqCols& rc, const do
                                  double invL01, const LaunchCfg& cfg, const AsOut& ao, hipStream_t s) {
   const int n_cu = cfg.n_cu;
   const bool f32 = sizeof(T) == 4;
-  const size_t as_bytes = alphas_lds_bytes(ao.A);
+  const size_t as_bytes = alphas_lds_bytes(ao.A, true);
   if (lds_grid_elems > 0) {
     const size_t shm = shared_bytes(m, f32, kBlockLds, true) + (size_t)lds_grid_elems * sizeof(T) + as_bytes;
     const int per_cu = (int)(160 * 1024 / shm) > 0 ? (int)(160 * 1024 / shm) : 1;
@@ -554,7 +510,7 @@ static hipError_t launch_xfxq2_g(const MemberDev& m, const ReqCols& rc, const do
     const int64_t nb = min(ntiles, (int64_t)n_cu * cfg.blocks_per_cu);
     return launch_one<T, G, kBlockTables, false, true, kAlphas>(m, rc, x, q2, n, out, nerr, 0, invL01, nb, shm, ao, s);
   }
-  const size_t shm = shared_bytes(m, f32, kBlockGlobal, false) + as_bytes;
+  const size_t shm = shared_bytes(m, f32, kBlockGlobal, false) + alphas_lds_bytes(ao.A, false);
   const int64_t ntiles = (n + kBlockGlobal - 1) / kBlockGlobal;
   const int64_t nb = min(ntiles, (int64_t)n_cu * cfg.blocks_per_cu);
   return launch_one<T, G, kBlockGlobal, false, false, kAlphas>(m, rc, x, q2, n, out, nerr, 0, invL01, nb, shm, ao, s);
@@ -604,7 +560,7 @@ hipError_t launch_locate(const MemberDev& m, const double* x, const double* q2, 
 hipError_t launch_alphas(const AlphasDev& A, const double* q2, int64_t n, double* out, unsigned long long* nerr,
                          int n_cu, hipStream_t s) {
   const int64_t nb = min((n + 1023) / 1024, (int64_t)n_cu * 8);
-  hipLaunchKernelGGL(k_alphas, dim3((unsigned)nb), dim3(256), 0, s, A, q2, n, out, nerr);
+  hipLaunchKernelGGL(k_alphas, dim3((unsigned)nb), dim3(256), (size_t)A.bytes, s, A, q2, n, out, nerr);
   return hipGetLastError();
 }
 
@@ -787,14 +743,28 @@ __device__ __forceinline__ T mc_pick(const T (&f)[kGW], int e) {
   }
 }
 
+// A located point's stencil in the values read by k_mc_fused (row stride P):
+// element offset of each x knot's first row.
+struct McOrigin {
+  int x[4];
+};
+__device__ __forceinline__ McOrigin mc_origin(const PointLoc& L, int nqp, int P) {
+  McOrigin o;
+  o.x[0] = (int)__umul24((unsigned)L.row, (unsigned)P);
+  const int sa = (int)__umul24((unsigned)nqp, (unsigned)P);
+  o.x[1] = o.x[0] + (L.s1 ? sa : 0);
+  o.x[2] = o.x[1] + sa;
+  o.x[3] = o.x[2] + (L.s3 ? sa : 0);
+  return o;
+}
+
 // One flavour of one located point, the value k_xfxq2 writes for it: NaN for
 // an invalid point, 0 for a flavour absent from the grid, the stencil sum
 // inside the grid, the extrapolation formula outside.  g points at the
-// stencil origin's entry of the flavour's column; sa, P are the x and Q^2
-// strides of the values read.
+// flavour's column of grid row 0; P is the row stride of the values read.
 template <typename T, bool kMaySlow>
-__device__ __forceinline__ T mc_value(const T* g, const PointLoc& L, const T w[4], const T v[4], int sa, int P,
-                                      int col, double invL01) {
+__device__ __forceinline__ T mc_value(const T* g, const PointLoc& L, const McOrigin& o, const T w[4], const T v[4],
+                                      int P, int col, double invL01) {
   if (L.mode & kInvalid) return (T)NAN;
   if (col < 0) return (T)0;
   if (!kMaySlow || !(L.mode & (kLowX | kLowQ | kHighQ))) {
@@ -802,25 +772,16 @@ __device__ __forceinline__ T mc_value(const T* g, const PointLoc& L, const T w[4
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
-      for (int b = 0; b < 4; ++b) F[a][b] = g[a * sa + b * P];
+      for (int b = 0; b < 4; ++b) F[a][b] = g[o.x[a] + b * P];
     return interp_stencil<T>(F, w, v);
   }
   const Wts wt{(double)w[0], (double)w[1], (double)w[2], (double)w[3],
                (double)v[0], (double)v[1], (double)v[2], (double)v[3]};
-  return (T)extrap_entry<T>(g, sa, P, L.mode, wt, L.p0, L.p1, invL01);
+  return (T)extrap_entry<T>(g + o.x[0], o.x[1] - o.x[0], o.x[2] - o.x[1], o.x[3] - o.x[2], P, L.mode, wt, L.p0, L.p1,
+                            invL01);
 }
 
-// Location of a point in the values read by k_mc_fused: element offset of
-// the stencil origin and stride between x knots (Q^2 stride P).
-__device__ __forceinline__ void mc_origin(const Tables& tb, const int* soff, const PointLoc& L, int P, int& base,
-                                          int& sa) {
-  const int k = max(L.k, 0);
-  const int nqp = tb.subs[k].nqp;
-  sa = nqp * P;
-  base = soff[k] + (L.sx * nqp + L.sq) * P;
-}
-
-template <typename T, bool kLdsGrid, int kGW>
+template <typename T, bool kLdsGrid, int kGW, bool kLdsTables = true>
 __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc, AlphasDev A,
                                                          const double* __restrict__ X1,
                                                          const double* __restrict__ X2,
@@ -828,50 +789,28 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
                                                          double* __restrict__ partial,
                                                          unsigned long long* __restrict__ nerr, double invL01) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int an2 = (A.n + 1) & ~1;
   unsigned char* stbl = smem;
-  double* ask = reinterpret_cast<double*>(smem + m.tbl_bytes);
-  double* asv = ask + an2;
-  CellCoef* asc = reinterpret_cast<CellCoef*>(asv + an2);
-  short* ash = reinterpret_cast<short*>(asc + an2);          // [A.nhints, padded to 8]
-  double* tree = reinterpret_cast<double*>(ash + ((A.nhints + 7) & ~7));  // [4][256]
+  unsigned char* sas = smem + (kLdsTables ? m.tbl_bytes : 0);
+  const int as_bytes = alphas_staged_bytes(A, kLdsTables);
+  double* tree = reinterpret_cast<double*>(sas + as_bytes);  // [4][256]
   int* scol = reinterpret_cast<int*>(tree + kMcFusedBS);  // [kMaxReq]
-  int* soff = scol + kMaxReq;                             // [kMaxSub] staged sub-grid offsets
-  int* sstep = soff + kMaxSub;                            // [kMaxReq + 4] column-group steps (kGW > 1)
-  T* sgrid = reinterpret_cast<T*>(sstep + kMaxReq + 4);   // 16-byte aligned: 2 kMaxReq + kMaxSub + 4 ints
+  int* sstep = scol + kMaxReq;                            // [kMaxReq + 4] column-group steps (kGW > 1)
+  T* sgrid = reinterpret_cast<T*>(sstep + kMaxReq + 4);   // 16-byte aligned: 2 kMaxReq + 4 ints
 
-  stage_copy<kMcFusedBS>(stbl, m.tables, m.tbl_bytes);
-  for (int i = threadIdx.x; i < A.n; i += kMcFusedBS) {
-    ask[i] = A.knots[i];
-    asv[i] = A.vals[i];
-    asc[i] = A.cells[i];
-  }
-  for (int i = threadIdx.x; i < A.nhints; i += kMcFusedBS) ash[i] = A.hints[i];
+  if constexpr (kLdsTables) stage_copy<kMcFusedBS>(stbl, m.tables, m.tbl_bytes);
+  stage_copy<kMcFusedBS>(sas, A.tables, as_bytes);
   for (int i = threadIdx.x; i < rc.n; i += kMcFusedBS) scol[i] = rc.col[i];
   const int Pp = sizeof(T) == 8 ? m.P64 : m.P32;
   const T* __restrict__ gvals = member_values<T>(m);
   // row stride of the values read below: in LDS P, or P rounded up to whole
   // column groups (<= Pp, whose padding columns are zero in global memory)
   const int P = kLdsGrid ? (m.P + kGW - 1) & ~(kGW - 1) : Pp;
-  if (threadIdx.x == 0) {
-    int off = 0;
-    for (int k = 0; k < m.K; ++k) {
-      soff[k] = kLdsGrid ? off : (int)(sizeof(T) == 8 ? m.sub[k].val_off64 : m.sub[k].val_off32);
-      off += m.sub[k].nxp * m.sub[k].nqp * P;
-    }
-    if constexpr (kGW > 1) mc_build_steps<kGW>(rc, sstep);
-  }
-  if constexpr (kLdsGrid) {
-    int off = 0;
-    for (int k = 0; k < m.K; ++k) {
-      const SubDesc& S = m.sub[k];
-      const int rows = S.nxp * S.nqp;
-      stage_rows<kMcFusedBS>(sgrid + off, gvals + (sizeof(T) == 8 ? S.val_off64 : S.val_off32), rows, P, Pp);
-      off += rows * P;
-    }
-  }
+  if constexpr (kGW > 1)
+    if (threadIdx.x == 0) mc_build_steps<kGW>(rc, sstep);
+  if constexpr (kLdsGrid) stage_rows<kMcFusedBS>(sgrid, gvals, m.rows, P, Pp);
   __syncthreads();
-  const Tables tb = tables_at(stbl, m);
+  const Tables tb = tables_at(kLdsTables ? stbl : m.tables, m);
+  const AsView av{sas, kLdsTables ? tb.logt : reinterpret_cast<const LogEntry*>(sas + A.logt_off), nullptr};
   const T* grid = kLdsGrid ? sgrid : gvals;
 
   const int q = threadIdx.x / kMcThreads, t = threadIdx.x % kMcThreads;
@@ -890,22 +829,20 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
         x2 = X2[i];
         q2 = Q2[i];
       }
-      // Q^2 weights: the shared location's.  locate_x copies them for a valid
-      // point (and zeros them for an invalid one, whose value is NaN before
-      // any weight is read), so both lookups read them from Qs.
+      // Q^2 weights: a valid point inside the grid in Q^2 has Qs.v (an invalid
+      // one's value is NaN, an extrapolated one's Q^2 weights are unused
+      // unless Q^2 is inside), so both lookups read them from Qs
       T w1[4], w2[4], vx[4];
       const QLoc<T> Qs = locate_q<T>(m, tb, q2);  // shared Q^2: located once for both lookups
-      const PointLoc L1 = locate_x<T>(m, tb, Qs, x1, w1, vx);
-      const PointLoc L2 = locate_x<T>(m, tb, Qs, x2, w2, vx);
+      const PointLoc L1 = locate_x<T>(m, tb, Qs, x1, q2, w1, vx);
+      const PointLoc L2 = locate_x<T>(m, tb, Qs, x2, q2, w2, vx);
       const T* v = Qs.v;
-      const double as = alphas_point(A, ask, asv, asc, ash, q2);
+      const double as = alphas_point(A, av, q2);
       const bool bad1 = live && (L1.mode & kInvalid), bad2 = live && (L2.mode & kInvalid);
       const bool bada = live && !(q2 > 0.0 && q2 < INFINITY);
       const unsigned long long nb = __popcll(__ballot(bad1)) + __popcll(__ballot(bad2)) + __popcll(__ballot(bada));
       if (nb && (threadIdx.x & 63) == 0) atomicAdd(nerr, nb);
-      int b1, sa1, b2, sa2;
-      mc_origin(tb, soff, L1, P, b1, sa1);
-      mc_origin(tb, soff, L2, P, b2, sa2);
+      const McOrigin o1 = mc_origin(L1, Qs.nqp, P), o2 = mc_origin(L2, Qs.nqp, P);
       double lum = 0.0;
       if (kLdsGrid && kGW > 1 && !((L1.mode | L2.mode) & (kLowX | kLowQ | kHighQ))) {
         // both lookups inside the LDS-staged grid, read a column group at a
@@ -921,8 +858,7 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
             lum = fma((double)f1, (double)f2, lum);
             continue;
           }
-          const T* g1 = grid + b1 + (st & 0xFFFF);
-          const T* g2 = grid + b2 + (st & 0xFFFF);
+          const T* g = grid + (st & 0xFFFF);
           // the stencils Q^2 row by Q^2 row (interp_stencil's steps): one
           // row's reads of both lookups in flight at a time
           T f1[kGW], f2[kGW];
@@ -931,8 +867,8 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
             T u1[4][kGW], u2[4][kGW];
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
-              const V q1 = *reinterpret_cast<const V*>(g1 + a * sa1 + b * P);
-              const V q2v = *reinterpret_cast<const V*>(g2 + a * sa2 + b * P);
+              const V q1 = *reinterpret_cast<const V*>(g + o1.x[a] + b * P);
+              const V q2v = *reinterpret_cast<const V*>(g + o2.x[a] + b * P);
               __builtin_memcpy(u1[a], &q1, sizeof(V));
               __builtin_memcpy(u2[a], &q2v, sizeof(V));
             }
@@ -972,14 +908,13 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
           T f1 = (T)0, f2 = (T)0;
           if (col >= 0) {
             T F1[4][4], F2[4][4];
-            const T* g1 = grid + b1 + col;
-            const T* g2 = grid + b2 + col;
+            const T* g = grid + col;
 #pragma unroll
             for (int a = 0; a < 4; ++a)
 #pragma unroll
               for (int b = 0; b < 4; ++b) {
-                F1[a][b] = g1[a * sa1 + b * P];
-                F2[a][b] = g2[a * sa2 + b * P];
+                F1[a][b] = g[o1.x[a] + b * P];
+                F2[a][b] = g[o2.x[a] + b * P];
               }
             f1 = interp_stencil<T>(F1, w1, v);
             f2 = interp_stencil<T>(F2, w2, v);
@@ -991,8 +926,8 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
       } else if (!((L1.mode | L2.mode) & (kLowX | kLowQ | kHighQ))) {
         for (int j = 0; j < R; ++j) {
           const int col = scol[j];
-          const T f1 = mc_value<T, false>(grid + b1 + col, L1, w1, v, sa1, P, col, invL01);
-          const T f2 = mc_value<T, false>(grid + b2 + col, L2, w2, v, sa2, P, col, invL01);
+          const T f1 = mc_value<T, false>(grid + col, L1, o1, w1, v, P, col, invL01);
+          const T f2 = mc_value<T, false>(grid + col, L2, o2, w2, v, P, col, invL01);
           lum = fma((double)f1, (double)f2, lum);
         }
       } else {
@@ -1000,8 +935,8 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
         // extrapolation formulas
         for (int j = 0; j < R; ++j) {
           const int col = scol[j];
-          const T f1 = mc_value<T, true>(grid + b1 + col, L1, w1, v, sa1, P, col, invL01);
-          const T f2 = mc_value<T, true>(grid + b2 + col, L2, w2, v, sa2, P, col, invL01);
+          const T f1 = mc_value<T, true>(grid + col, L1, o1, w1, v, P, col, invL01);
+          const T f2 = mc_value<T, true>(grid + col, L2, o2, w2, v, P, col, invL01);
           lum = fma((double)f1, (double)f2, lum);
         }
       }
@@ -1021,11 +956,10 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
 }
 
 // LDS bytes of k_mc_fused (grid_elems > 0: the grid staged with row stride P).
-size_t mc_fused_shared_bytes(const MemberDev& m, const AlphasDev& A, int64_t grid_elems, bool f32) {
-  const size_t an2 = (size_t)((A.n + 1) & ~1);
-  return (size_t)m.tbl_bytes + an2 * (8 + 8 + sizeof(CellCoef)) + (size_t)((A.nhints + 7) & ~7) * 2 +
-         kMcFusedBS * 8 + (2 * kMaxReq + kMaxSub + 4) * 4 +
-         (size_t)grid_elems * (f32 ? 4 : 8);
+static size_t mc_fused_shared_bytes(const MemberDev& m, const AlphasDev& A, int64_t grid_elems, bool f32,
+                                    bool tables) {
+  return (tables ? (size_t)m.tbl_bytes : 0) + (size_t)alphas_staged_bytes(A, tables) + kMcFusedBS * 8 +
+         (2 * kMaxReq + 4) * 4 + (size_t)grid_elems * (f32 ? 4 : 8);
 }
 
 template <typename T>
@@ -1036,30 +970,30 @@ hipError_t launch_mc_fused(const MemberDev& m, const ReqCols& rc, const AlphasDe
   if (np > 0) {
     constexpr int kGW = sizeof(T) == 4 ? 4 : 1;  // column groups in FP32 only
     const int Pg = (m.P + kGW - 1) & ~(kGW - 1);
-    int64_t rows = 0;
-    for (int k = 0; k < m.K; ++k) rows += (int64_t)m.sub[k].nxp * m.sub[k].nqp;
+    const int64_t rows = m.rows;
     const bool f32 = sizeof(T) == 4;
-    // grid in LDS in column groups, else in LDS with stride P, else in global memory
-    const size_t lds_g = mc_fused_shared_bytes(m, A, rows * Pg, f32);
-    const size_t lds_1 = mc_fused_shared_bytes(m, A, rows * m.P, f32);
-    const int mode = kGW > 1 && lds_g <= 160 * 1024 ? 2 : (lds_1 <= 160 * 1024 ? 1 : 0);
-    const size_t shm = mode == 2 ? lds_g : (mode == 1 ? lds_1 : mc_fused_shared_bytes(m, A, 0, f32));
-    const void* fn = mode == 2   ? reinterpret_cast<const void*>(&k_mc_fused<T, true, kGW>)
-                     : mode == 1 ? reinterpret_cast<const void*>(&k_mc_fused<T, true, 1>)
-                                 : reinterpret_cast<const void*>(&k_mc_fused<T, false, 1>);
+    // grid in LDS in column groups, else in LDS with stride P, else in global
+    // memory; location tables in LDS unless even they alone do not fit
+    const size_t lds_g = mc_fused_shared_bytes(m, A, rows * Pg, f32, true);
+    const size_t lds_1 = mc_fused_shared_bytes(m, A, rows * m.P, f32, true);
+    const size_t lds_0 = mc_fused_shared_bytes(m, A, 0, f32, true);
+    const int mode = kGW > 1 && lds_g <= 160 * 1024 ? 3
+                     : lds_1 <= 160 * 1024          ? 2
+                     : lds_0 <= 160 * 1024          ? 1
+                                                    : 0;
+    const size_t shm = mode == 3 ? lds_g : mode == 2 ? lds_1 : mode == 1 ? lds_0
+                                                                          : mc_fused_shared_bytes(m, A, 0, f32, false);
+    auto kernel = mode == 3   ? &k_mc_fused<T, true, kGW>
+                  : mode == 2 ? &k_mc_fused<T, true, 1>
+                  : mode == 1 ? &k_mc_fused<T, false, 1>
+                              : &k_mc_fused<T, false, 1, false>;
+    const void* fn = reinterpret_cast<const void*>(kernel);
     hipError_t e = allow_dynamic_lds(fn, shm);
     if (e != hipSuccess) return e;
     const int per_cu = max(1, (int)(160 * 1024 / shm));
     const int64_t nb = min((np + 3) / 4, (int64_t)n_cu * per_cu);
-    if (mode == 2)
-      hipLaunchKernelGGL((k_mc_fused<T, true, kGW>), dim3((unsigned)nb), dim3(kMcFusedBS), shm, s, m, rc, A, x1, x2,
-                         q2, n, partial, nerr, invL01);
-    else if (mode == 1)
-      hipLaunchKernelGGL((k_mc_fused<T, true, 1>), dim3((unsigned)nb), dim3(kMcFusedBS), shm, s, m, rc, A, x1, x2,
-                         q2, n, partial, nerr, invL01);
-    else
-      hipLaunchKernelGGL((k_mc_fused<T, false, 1>), dim3((unsigned)nb), dim3(kMcFusedBS), shm, s, m, rc, A, x1, x2,
-                         q2, n, partial, nerr, invL01);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(kMcFusedBS), shm, s, m, rc, A, x1, x2, q2, n, partial, nerr,
+                       invL01);
   }
   hipLaunchKernelGGL(k_mc_final, dim3(1), dim3(kMcThreads), 0, s, partial, np, sum_out);
   return hipGetLastError();
@@ -1130,7 +1064,7 @@ __global__ __launch_bounds__(kBatchBS) void k_batched(const BatchReq* __restrict
     for (int i = threadIdx.x; i < rq.R; i += kBatchBS) scol[i] = cols[rq.col_off + i];
     __syncthreads();
     if (threadIdx.x == 0) s_member = rq.member;
-    const Tables tb = kLdsTables ? tables_at(stbl, m) : Tables{m.knots, m.cells, m.hints, m.subs};
+    const Tables tb = tables_at(kLdsTables ? stbl : m.tables, m);
     const double invL01 = invL01s[rq.member];
     T* out = reinterpret_cast<T*>(rq.out);
     for (int w0 = wv * kWave; w0 < tl.count; w0 += kWaves * kWave) {

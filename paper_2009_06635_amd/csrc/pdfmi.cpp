@@ -21,7 +21,7 @@
 
 namespace pdfmi {
 size_t xfxq2_shared_bytes(const MemberDev& m, bool f32);
-size_t alphas_lds_bytes(const AlphasDev* A);
+size_t alphas_lds_bytes(const AlphasDev* A, bool member_tables);
 hipError_t launch_xfxq2_f64(const MemberDev&, const ReqCols&, const double*, const double*, int64_t, double*,
                             unsigned long long*, int, double, const LaunchCfg&, const AlphasDev*, double*, hipStream_t);
 hipError_t launch_xfxq2_f32(const MemberDev&, const ReqCols&, const double*, const double*, int64_t, float*,
@@ -63,7 +63,6 @@ hipError_t launch_mc_sum(const T*, const T*, int, const double*, int64_t, double
 template <typename T>
 hipError_t launch_mc_fused(const MemberDev&, const ReqCols&, const AlphasDev&, const double*, const double*,
                            const double*, int64_t, double*, double*, unsigned long long*, double, int, hipStream_t);
-size_t mc_fused_shared_bytes(const MemberDev& m, const AlphasDev& A, int64_t grid_elems, bool f32);
 hipError_t launch_fk_contract(const double* F, const double* FK, int nrep, int ndat, int64_t K, double* T, int S,
                               double* ws, hipStream_t s);
 int fk_slices(int nrep, int ndat, int64_t K, int n_cu);
@@ -109,6 +108,7 @@ struct Member {
   std::vector<double> h_knots, h_values;
   double invL01 = 0.0;
   uint64_t gen = 0;        // load generation: a slot reused by a later load gets a new one
+  size_t mc_bytes = 0;     // the member's share of the table size that pdf_mc_fused accepts
 };
 
 std::mutex g_mu;
@@ -120,6 +120,7 @@ std::string g_arch;  // device architecture name (autotune cache keys)
 unsigned long long* g_nerr = nullptr;
 bool g_has_alphas = false;
 AlphasDev g_alphas{};
+size_t g_alphas_mc_bytes = 0;  // the alpha_s table's share of the table size that pdf_mc_fused accepts
 void* g_alphas_mem = nullptr;
 int g_lds_policy = 0;  // 0 auto, 1 never stage the grid in LDS, 2 whenever it fits
 int g_vector_cols = 1; // serve all-column requests with G-wide vector gathers
@@ -167,19 +168,20 @@ bool valid_pid(int p) { return (p >= -6 && p <= 6) || p == 21; }
 int norm_pid(int p) { return p == 0 ? 21 : p; }
 
 // Hermite coefficients of every cell of a strictly increasing 1D table
-// (see CellCoef); edge flags within [lo, hi].
+// (see CellCoef).
 void cell_coefs(const double* t, int n, CellCoef* out) {
   std::vector<double> D(n - 1);
   for (int i = 0; i + 1 < n; ++i) D[i] = std::log(t[i + 1] / t[i]);
   for (int i = 0; i + 1 < n; ++i) {
     CellCoef c{};
     c.t0 = t[i];
-    c.t1 = t[i + 1];
     c.inv_t0 = 1.0 / t[i];
     c.invD = 1.0 / D[i];
     const bool L = i > 0, R = i + 1 < n - 1;
-    c.hl = L ? 0.5 * (D[i] / D[i - 1]) : -1.0;
-    c.hr = R ? 0.5 * (D[i] / D[i + 1]) : -1.0;
+    c.hl = L ? 0.5 * (D[i] / D[i - 1]) : 0.0;
+    c.hr = R ? 0.5 * (D[i] / D[i + 1]) : 0.0;
+    c.el = L ? 0.5f : 1.0f;
+    c.er = R ? 0.5f : 1.0f;
     out[i] = c;
   }
 }
@@ -207,7 +209,7 @@ uint64_t double_bits(double v) {
 }
 
 HintAxis build_hints(const double* t, int n, std::vector<short>& hints) {
-  HintAxis h{-1, 0, 0, 0u};
+  HintAxis h{-1, 0, 0, 0};
   if (n < 4) return h;
   const int last = n - 2;
   for (int shift = 52; shift >= 32; --shift) {
@@ -223,8 +225,8 @@ HintAxis build_hints(const double* t, int n, std::vector<short>& hints) {
     if (*std::max_element(inside.begin(), inside.end()) > 2) continue;
     h.off = (int)hints.size();
     h.n = (int)nb;
-    h.shift = shift;
-    h.key0 = (unsigned)k0;
+    h.shift = shift - 32;
+    h.key0 = (int)k0;
     for (uint64_t b = 0; b < nb; ++b) {
       const uint64_t lo_bits = (k0 + b) << shift;
       double lo;
@@ -235,6 +237,40 @@ HintAxis build_hints(const double* t, int n, std::vector<short>& hints) {
     return h;
   }
   return h;
+}
+
+// Table of fast_log: interval i of [0.6875, 1.375) (width 2^-8 below 1, 2^-7
+// above); inv the one of 64 candidates near 1 / its middle whose -ln is
+// nearest to a double, 1 next to 1.
+std::vector<LogEntry> make_log_table() {
+  std::vector<LogEntry> t(kLogEntries);
+  for (int i = 0; i < kLogEntries; ++i) {
+    // interval i starts at the double with high word kLogOrigin + (i << 13)
+    auto start = [](int j) {
+      const uint64_t u = (uint64_t)(uint32_t)(kLogOrigin + (j << 13)) << 32;
+      double v;
+      std::memcpy(&v, &u, 8);
+      return v;
+    };
+    const double a = start(i), b = start(i + 1);
+    t[i] = LogEntry{1.0, 0.0};
+    if (a == 1.0 || b == 1.0) continue;
+    long double best = 1.0L;
+    for (int j = -32; j < 32; ++j) {
+      const double inv = 2.0 / (a + b) * (1.0 + j * 0x1p-20);
+      const long double l = -std::log((long double)inv);
+      const long double err = std::fabs((l - (long double)(double)l) / l);
+      if (err < best) {
+        best = err;
+        t[i] = LogEntry{inv, (double)l};
+      }
+    }
+  }
+  return t;
+}
+const std::vector<LogEntry>& log_table() {
+  static const std::vector<LogEntry> t = make_log_table();
+  return t;
 }
 
 int check_stream_args(const void* a, const void* b, int64_t n) {
@@ -361,84 +397,114 @@ extern "C" int pdf_load_grid(int32_t K, const int32_t* shape, int32_t P, const i
   const int P64 = P <= 4 ? 4 : (P <= 8 ? 8 : (P + 15) & ~15), P32 = (P + 3) & ~3;
   d.P64 = P64;
   d.P32 = P32;
-  int64_t n64 = 0, n32 = 0;
+  // rows of the values: sub-grids with fewer than 4 knots on an axis are padded to 4
+  std::vector<int> row_off(K), nqp(K);
+  int64_t rows = 0;
   for (int k = 0; k < K; ++k) {
-    const int nx = shape[2 * k], nq = shape[2 * k + 1];
-    SubDesc& S = d.sub[k];
-    S.nx = nx;
-    S.nq = nq;
-    S.nxp = nx < 4 ? 4 : nx;
-    S.nqp = nq < 4 ? 4 : nq;
-    S.val_off64 = n64;
-    S.val_off32 = n32;
-    n64 += (int64_t)S.nxp * S.nqp * P64;
-    n32 += (int64_t)S.nxp * S.nqp * P32;
+    nqp[k] = std::max(shape[2 * k + 1], 4);
+    row_off[k] = (int)rows;
+    rows += (int64_t)std::max(shape[2 * k], 4) * nqp[k];
   }
+  const int64_t n64 = rows * P64, n32 = rows * P32;
+  d.rows = (int)rows;
   d.elems64 = n64;
   d.elems32 = n32;
-  // location tables: knots, cells and hints per axis; sub-grids whose x knots
-  // equal sub-grid 0's share its x tables
-  std::vector<double> hk;
+  // location tables: x knots, cells and hints per sub-grid (those whose x
+  // knots equal sub-grid 0's share its tables), and one Q^2 table for all
+  // sub-grids (the threshold between two is one knot)
+  std::vector<double> hk, hq;
   std::vector<CellCoef> hc;
-  std::vector<short> hh;
+  std::vector<QCell> hqc;
+  std::vector<short> hh, one;
+  std::vector<SubDesc> subs(K);
   std::vector<double> hv((size_t)n64, 0.0);
   std::vector<float> hf((size_t)n32, 0.0f);
   int64_t ko = 0, vo = 0;
+  size_t ref_knots = 0, ref_cells = 0, ref_hints = 0;
+  d.shared_x = 1;
   for (int k = 0; k < K; ++k) {
-    SubDesc& S = d.sub[k];
+    SubDesc& S = subs[k];
+    const int nx = shape[2 * k], nq = shape[2 * k + 1];
     const double* xk = knots + ko;
-    const double* qk = knots + ko + S.nx;
-    const SubDesc& S0 = d.sub[0];
-    if (k > 0 && S.nx == S0.nx && std::memcmp(xk, knots, sizeof(double) * S.nx) == 0) {
-      S.xk_off = S0.xk_off;
-      S.xc_off = S0.xc_off;
-      S.xh = S0.xh;
+    const double* qk = knots + ko + nx;
+    if (k > 0 && nx == subs[0].nx && std::memcmp(xk, knots, sizeof(double) * nx) == 0) {
+      S = subs[0];
     } else {
+      if (k > 0) d.shared_x = 0;
+      S.nx = nx;
       S.xk_off = (int)hk.size();
-      hk.insert(hk.end(), xk, xk + S.nx);
+      hk.insert(hk.end(), xk, xk + nx);
       S.xc_off = (int)hc.size();
-      hc.resize(hc.size() + S.nx - 1);
-      cell_coefs(xk, S.nx, &hc[S.xc_off]);
-      S.xh = build_hints(xk, S.nx, hh);
+      hc.resize(hc.size() + nx - 1);
+      cell_coefs(xk, nx, &hc[S.xc_off]);
+      S.xh = build_hints(xk, nx, hh);
+      ref_hints += S.xh.off < 0 ? 0 : S.xh.n;
+      ref_knots += nx;
+      ref_cells += nx - 1;
     }
-    S.qk_off = (int)hk.size();
-    hk.insert(hk.end(), qk, qk + S.nq);
-    S.qc_off = (int)hc.size();
-    hc.resize(hc.size() + S.nq - 1);
-    cell_coefs(qk, S.nq, &hc[S.qc_off]);
-    S.qh = build_hints(qk, S.nq, hh);
-    S.qfirst = qk[0];
-    for (int ix = 0; ix < S.nx; ++ix)
-      for (int iq = 0; iq < S.nq; ++iq)
+    std::vector<CellCoef> qc(nq - 1);
+    cell_coefs(qk, nq, qc.data());
+    ref_knots += nq;
+    ref_cells += nq - 1;
+    for (int i = 0; i + 1 < nq; ++i) {
+      const int sq = std::min(std::max(i - 1, 0), nqp[k] - 4);
+      hq.push_back(qk[i]);
+      hqc.push_back(QCell{qc[i], row_off[k] + sq, nqp[k], k << 16 | i, i - sq, {}});
+    }
+    if (k == K - 1) hq.push_back(qk[nq - 1]);
+    if (K > 1) {
+      one.clear();
+      build_hints(qk, nq, one);
+      ref_hints += one.size();
+    }
+    for (int ix = 0; ix < nx; ++ix)
+      for (int iq = 0; iq < nq; ++iq)
         for (int c = 0; c < P; ++c) {
-          const double v = values[vo + ((int64_t)ix * S.nq + iq) * P + c];
-          hv[S.val_off64 + ((int64_t)ix * S.nqp + iq) * P64 + c] = v;
-          hf[S.val_off32 + ((int64_t)ix * S.nqp + iq) * P32 + c] = (float)v;
+          const double v = values[vo + ((int64_t)ix * nq + iq) * P + c];
+          const int64_t row = row_off[k] + (int64_t)ix * nqp[k] + iq;
+          hv[row * P64 + c] = v;
+          hf[row * P32 + c] = (float)v;
         }
-    ko += S.nx + S.nq;
-    vo += (int64_t)S.nx * S.nq * P;
+    ko += nx + nq;
+    vo += (int64_t)nx * nq * P;
   }
-  d.nknots = (int)hk.size();
-  d.nknots_pad = (d.nknots + 1) & ~1;
+  d.nx = subs[0].nx;
+  d.xk_off = subs[0].xk_off;
+  d.xc_off = subs[0].xc_off;
+  d.xh = subs[0].xh;
+  d.nqk = (int)hq.size();
+  d.qk_off = (int)hk.size();
+  d.qh = build_hints(hq.data(), d.nqk, hh);
+  if (K == 1) ref_hints += d.qh.off < 0 ? 0 : d.qh.n;
+  hk.insert(hk.end(), hq.begin(), hq.end());
   d.xmin = knots[0];
   d.xmax = knots[shape[0] - 1];
-  d.qmin = d.sub[0].qfirst;
-  d.qmax = hk[d.sub[K - 1].qk_off + d.sub[K - 1].nq - 1];
-  M.invL01 = hc[d.sub[0].qc_off].invD;
+  d.qmin = hq.front();
+  d.qmax = hq.back();
+  M.invL01 = hqc[0].c.invD;
+  // pdf_mc_fused accepts members whose tables, at 8 bytes a knot, 48 a cell, 2
+  // a hint and 88 a sub-grid (thresholds and hints counted per sub-grid), fit LDS
+  M.mc_bytes = align_up(ref_knots, 2) * 8 + ref_cells * 48 + align_up(ref_hints * 2, 16) +
+               align_up((size_t)K * 88, 16);
 
-  // table block: [knots][cells][hints][sub-grid descriptors], 16-byte aligned parts
-  d.cells_off = d.nknots_pad * 8;
-  d.hints_off = d.cells_off + (int)(hc.size() * sizeof(CellCoef));
+  // table block, 16-byte aligned parts
+  const std::vector<LogEntry>& lt = log_table();
+  d.cells_off = (int)align_up(hk.size() * 8, 16);
+  d.qcells_off = d.cells_off + (int)(hc.size() * sizeof(CellCoef));
+  d.hints_off = d.qcells_off + (int)(hqc.size() * sizeof(QCell));
   d.subs_off = d.hints_off + (int)align_up(hh.size() * sizeof(short), 16);
-  d.tbl_bytes = d.subs_off + (int)align_up((size_t)K * sizeof(SubDesc), 16);
+  d.logt_off = d.subs_off + (int)align_up((size_t)K * sizeof(SubDesc), 16);
+  d.tbl_bytes = d.logt_off + (int)(lt.size() * sizeof(LogEntry));
   const size_t bt = align_up((size_t)d.tbl_bytes, 256);
   const size_t b64 = align_up((size_t)n64 * sizeof(double), 256);
   const size_t b32 = align_up((size_t)n32 * sizeof(float), 256);
   std::vector<unsigned char> blob(bt + b64 + b32, 0);
   std::memcpy(blob.data(), hk.data(), hk.size() * sizeof(double));
   std::memcpy(blob.data() + d.cells_off, hc.data(), hc.size() * sizeof(CellCoef));
+  std::memcpy(blob.data() + d.qcells_off, hqc.data(), hqc.size() * sizeof(QCell));
   if (!hh.empty()) std::memcpy(blob.data() + d.hints_off, hh.data(), hh.size() * sizeof(short));
-  std::memcpy(blob.data() + d.subs_off, d.sub, (size_t)K * sizeof(SubDesc));
+  std::memcpy(blob.data() + d.subs_off, subs.data(), (size_t)K * sizeof(SubDesc));
+  std::memcpy(blob.data() + d.logt_off, lt.data(), lt.size() * sizeof(LogEntry));
   std::memcpy(blob.data() + bt, hv.data(), (size_t)n64 * sizeof(double));
   std::memcpy(blob.data() + bt + b64, hf.data(), (size_t)n32 * sizeof(float));
 
@@ -451,10 +517,6 @@ extern "C" int pdf_load_grid(int32_t K, const int32_t* shape, int32_t P, const i
   }
   unsigned char* base = static_cast<unsigned char*>(M.dmem);
   d.tables = base;
-  d.knots = reinterpret_cast<const double*>(base);
-  d.cells = reinterpret_cast<const CellCoef*>(base + d.cells_off);
-  d.hints = reinterpret_cast<const short*>(base + d.hints_off);
-  d.subs = reinterpret_cast<const SubDesc*>(base + d.subs_off);
   d.v64 = reinterpret_cast<const double*>(base + bt);
   d.v32 = reinterpret_cast<const float*>(base + bt + b64);
 
@@ -509,36 +571,51 @@ extern "C" int pdf_load_alphas(int32_t n, const double* q2k, const double* a) {
   std::lock_guard<std::mutex> lock(g_mu);
   if ((rc = ensure_init()) != PDF_OK) return rc;
   AlphasDev A{};
-  A.n = n;
-  A.nseg = 0;
-  int lo = 0;
-  for (int i = 1; i <= n; ++i) {
-    if (i == n || q2k[i] == q2k[i - 1]) {
-      A.seg_lo[A.nseg] = lo;
-      A.seg_hi[A.nseg] = i - 1;
-      A.seg_first[A.nseg] = q2k[lo];
-      ++A.nseg;
-      lo = i;
+  // the cells of every segment with their stencil values, the knots once each
+  std::vector<double> hk;
+  std::vector<AsCell> hc;
+  std::vector<short> hh, ref_hints;
+  for (int lo = 0, i = 1; i <= n; ++i) {
+    if (i < n && q2k[i] != q2k[i - 1]) continue;
+    const int m = i - lo;  // knots lo .. i - 1 form a segment
+    std::vector<CellCoef> c(m - 1);
+    cell_coefs(q2k + lo, m, c.data());
+    for (int j = 0; j + 1 < m; ++j) {
+      // slopes times the cell's log-width from the weights of CellCoef
+      const double f0 = a[lo + j], f1 = a[lo + j + 1];
+      const double fm = j > 0 ? a[lo + j - 1] : f0, fp = j + 2 < m ? a[lo + j + 2] : f1;
+      const AsCell ac{c[j].t0, c[j].inv_t0, c[j].invD, f0, f1 - f0, c[j].el * (f1 - f0) + c[j].hl * (f0 - fm),
+                      c[j].er * (f1 - f0) + c[j].hr * (fp - f1), {}};
+      hk.push_back(q2k[lo + j]);
+      hc.push_back(ac);
     }
+    // hints counted as per-segment lists for the size that pdf_mc_fused accepts
+    const size_t before = ref_hints.size();
+    build_hints(q2k + lo, m, ref_hints);
+    if ((int)ref_hints.size() > kAlphasMaxHints) ref_hints.resize(before);
+    lo = i;
   }
-  std::vector<CellCoef> hc((size_t)n);  // cell j valid when j, j+1 share a segment
-  for (int s = 0; s < A.nseg; ++s) cell_coefs(q2k + A.seg_lo[s], A.seg_hi[s] - A.seg_lo[s] + 1, &hc[A.seg_lo[s]]);
-  std::vector<short> hh;
-  for (int s = 0; s < A.nseg; ++s) {
-    A.seg_hint[s] = build_hints(q2k + A.seg_lo[s], A.seg_hi[s] - A.seg_lo[s] + 1, hh);
-    if ((int)hh.size() > kAlphasMaxHints) {  // keep the staged list small: binary search this segment
-      hh.resize(A.seg_hint[s].off);
-      A.seg_hint[s].off = -1;
-    }
+  hk.push_back(q2k[n - 1]);
+  A.ncell = (int)hc.size();
+  A.h = build_hints(hk.data(), (int)hk.size(), hh);
+  if ((int)hh.size() > kAlphasMaxHints) {  // keep the staged list small: binary search
+    hh.clear();
+    A.h.off = -1;
   }
-  A.nhints = (int)hh.size();
-  const size_t bk = align_up((size_t)n * 8, 256), bv = align_up((size_t)n * 8, 256);
-  const size_t bc = align_up(hc.size() * sizeof(CellCoef), 256);
-  std::vector<unsigned char> blob(bk + bv + bc + hh.size() * sizeof(short) + 16, 0);
-  std::memcpy(blob.data(), q2k, (size_t)n * 8);
-  std::memcpy(blob.data() + bk, a, (size_t)n * 8);
-  std::memcpy(blob.data() + bk + bv, hc.data(), hc.size() * sizeof(CellCoef));
-  if (!hh.empty()) std::memcpy(blob.data() + bk + bv + bc, hh.data(), hh.size() * sizeof(short));
+  A.q_lo = q2k[0];
+  A.q_hi = q2k[n - 1];
+  A.a_lo = a[0];
+  A.a_hi = a[n - 1];
+  const std::vector<LogEntry>& lt = log_table();
+  A.cells_off = (int)align_up(hk.size() * 8, 16);
+  A.hints_off = A.cells_off + (int)(hc.size() * sizeof(AsCell));
+  A.logt_off = A.hints_off + (int)align_up(hh.size() * sizeof(short), 16);
+  A.bytes = A.logt_off + (int)(lt.size() * sizeof(LogEntry));
+  std::vector<unsigned char> blob((size_t)A.bytes, 0);
+  std::memcpy(blob.data(), hk.data(), hk.size() * 8);
+  std::memcpy(blob.data() + A.cells_off, hc.data(), hc.size() * sizeof(AsCell));
+  if (!hh.empty()) std::memcpy(blob.data() + A.hints_off, hh.data(), hh.size() * sizeof(short));
+  std::memcpy(blob.data() + A.logt_off, lt.data(), lt.size() * sizeof(LogEntry));
   void* mem = nullptr;
   hipError_t e = hipMalloc(&mem, blob.size());
   if (e != hipSuccess) return fail_hip(e, "hipMalloc(alpha_s)");
@@ -547,11 +624,8 @@ extern "C" int pdf_load_alphas(int32_t n, const double* q2k, const double* a) {
     (void)hipFree(mem);
     return fail_hip(e, "hipMemcpy(alpha_s)");
   }
-  unsigned char* b = static_cast<unsigned char*>(mem);
-  A.knots = reinterpret_cast<const double*>(b);
-  A.vals = reinterpret_cast<const double*>(b + bk);
-  A.cells = reinterpret_cast<const CellCoef*>(b + bk + bv);
-  A.hints = reinterpret_cast<const short*>(b + bk + bv + bc);
+  A.tables = static_cast<const unsigned char*>(mem);
+  g_alphas_mc_bytes = align_up(n, 2) * (8 + 8 + 48) + align_up(ref_hints.size(), 8) * 2;
   if (g_alphas_mem) (void)hipFree(g_alphas_mem);
   g_alphas_mem = mem;
   g_alphas = A;
@@ -576,7 +650,7 @@ static int xfxq2_impl(int32_t member, const int32_t* pids, int32_t n_pids, const
   if (n == 0) return PDF_OK;
   if (n * (int64_t)req.n > ((int64_t)1 << 40)) return fail(PDF_ERR_ARG, "n too large");
   const bool f32 = sizeof(T) == 4;
-  const int lds = lds_grid_elems(*M, f32, n, alphas_lds_bytes(fused ? &g_alphas : nullptr));
+  const int lds = lds_grid_elems(*M, f32, n, alphas_lds_bytes(fused ? &g_alphas : nullptr, true));
   hipError_t e;
   const LaunchCfg cfg{g_ncu, g_blocks_per_cu, g_vector_cols};
   const AlphasDev* A = fused ? &g_alphas : nullptr;
@@ -1316,6 +1390,7 @@ extern "C" int pdf_surrogate_create(int32_t member, uint64_t seed, int32_t* sid_
   S.seed = seed;
   S.sd.P = P;
   S.sd.nx = nx0;
+  S.sd.K = K;
   S.sd.lx0 = std::log(M->dev.xmin);
   S.sd.ilx = 1.0 / (std::log(M->dev.xmax) - std::log(M->dev.xmin));
   S.sd.lq0 = std::log(M->dev.qmin);
@@ -1328,6 +1403,7 @@ extern "C" int pdf_surrogate_create(int32_t member, uint64_t seed, int32_t* sid_
       const int nx = M->h_shape[2 * k], nq = M->h_shape[2 * k + 1];
       const double* xk = M->h_knots.data() + o;
       const double* qk = xk + nx;
+      S.sd.qfirst[k] = qk[0];
       S.sd.trust[k] = nx >= 4 && nq >= 4;
       S.sd.txlo[k] = S.sd.trust[k] ? xk[1] : 0.0;
       S.sd.txhi[k] = S.sd.trust[k] ? xk[nx - 2] : 0.0;
@@ -1642,6 +1718,9 @@ extern "C" int pdf_mc_chunk_sum_f32(const float* xf1, const float* xf2, int32_t 
   return mc_sum_impl<float>(xf1, xf2, n_pids, alphas, n, workspace, sum_out, stream);
 }
 
+// LDS of the one-kernel form besides the tables: the summation tree and the request's column lists.
+constexpr size_t kMcFixedBytes = 1024 * 8 + (2 * kMaxReq + kMaxSub + 4) * 4;
+
 template <typename T>
 static int mc_fused_impl(int32_t member, const int32_t* pids, int32_t n_pids, const double* x1, const double* x2,
                          const double* q2, int64_t n, double* workspace, double* sum_out, pdf_stream_t stream) {
@@ -1656,7 +1735,7 @@ static int mc_fused_impl(int32_t member, const int32_t* pids, int32_t n_pids, co
   if (!g_has_alphas) return fail(PDF_ERR_STATE, "no alpha_s table loaded");
   ReqCols rcols{};
   if ((rc = build_req(*M, pids, n_pids, rcols)) != PDF_OK) return rc;
-  if (mc_fused_shared_bytes(M->dev, g_alphas, 0, sizeof(T) == 4) > kLdsBytes)
+  if (M->mc_bytes + g_alphas_mc_bytes + kMcFixedBytes > kLdsBytes)
     return fail(PDF_ERR_GRID, "location tables too large for the fused kernel; use pdf_xfxq2 + pdf_mc_chunk_sum");
   hipError_t e = launch_mc_fused<T>(M->dev, rcols, g_alphas, x1, x2, q2, n, workspace, sum_out, g_nerr, M->invL01,
                                     g_ncu, (hipStream_t)stream);

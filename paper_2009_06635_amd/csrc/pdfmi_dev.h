@@ -20,80 +20,100 @@ enum : int { kLowX = 1, kLowQ = 2, kHighQ = 4, kInvalid = 8, kXHigh = 16 };
 
 // Per-cell Hermite data of one 1D knot table (cell i = [t_i, t_{i+1}]), FP64,
 // computed on the host.  With Hermite basis h00,h10,h01,h11 of the cell
-// parameter u, the weights of the four knots i-1..i+2 are
-//   w(-1) = h10*am1
-//   w(0)  = h00 + h10*a0 + h11*b0
-//   w(1)  = h01 + h10*a1 + h11*b1
-//   w(2)  = h11*b2
-// where (am1,a0,a1) expand Delta_i * slope_i and (b0,b1,b2) expand
-// Delta_i * slope_{i+1} over the knot values (finite-difference slopes:
-// mean of adjacent secants inside the table, the one secant at its ends).
-// Inside the table they depend only on hl = Delta_i / (2 Delta_{i-1}) and
-// hr = Delta_i / (2 Delta_{i+1}):
-//   am1 = -hl, a0 = hl - 1/2, a1 = 1/2;   b0 = -1/2, b1 = 1/2 - hr, b2 = hr;
-// at the table's first cell (no left neighbour, hl < 0 marks it)
-//   am1 = 0, a0 = -1, a1 = 1, and at its last cell (hr < 0)
-//   b0 = -1, b1 = 1, b2 = 0.  48 bytes: three 16-byte LDS reads per cell.
-struct CellCoef {
+// parameter u, hl = Delta_i / (2 Delta_{i-1}) and hr = Delta_i / (2 Delta_{i+1}),
+// the weights of the four knots i-1..i+2 are
+//   w(-1) = -hl h10                           w(1) = h01 + el h10 + (er - hr) h11
+//   w(0)  = h00 + (hl - el) h10 - er h11      w(2) = hr h11
+// (finite-difference slopes: the mean of the adjacent secants inside the
+// table, where el = er = 1/2; the one secant at its ends: at the first cell
+// hl = 0 and el = 1, at the last hr = 0 and er = 1).  48 bytes: three 16-byte
+// LDS reads per cell.
+struct alignas(16) CellCoef {
   double t0;      // knot i
-  double t1;      // knot i+1
   double inv_t0;  // 1 / knot i
-  double invD;    // 1 / ln(t1 / t0)
-  double hl, hr;  // half ratios of the neighbouring cells' log-widths, or -1 at a table edge
+  double invD;    // 1 / ln(knot i+1 / knot i)
+  double hl, hr;  // half ratios of the neighbouring cells' log-widths, 0 at a table end
+  float el, er;   // 1/2, or 1 at a table end
 };
 
+// A Q^2 cell of any sub-grid: the cells of all sub-grids form one table in
+// increasing Q^2 (a threshold's knot starts the upper sub-grid's first cell),
+// so one search finds sub-grid and cell together.  80 bytes: an odd number of
+// 16-byte units, so that random cells spread over all LDS banks.
+struct alignas(16) QCell {
+  CellCoef c;
+  int row;   // grid row (of P values) of this cell's first stencil Q^2 knot at x knot 0
+  int nqp;   // rows between consecutive x knots
+  int kiq;   // sub-grid << 16 | cell within the sub-grid
+  int d;     // position of the cell's knot i in the stencil: 0 left end, 1 inside, 2 right end
+  int pad[4];
+};
+
+// An alpha_s cell: value at its first knot, difference to the second, and the
+// slopes at both times the cell's log-width (the table's values are fixed, so
+// the finite differences are formed once).  80 bytes, as QCell.
+struct alignas(16) AsCell {
+  double t0, inv_t0, invD;
+  double f0, df, d0, d1;
+  double pad[3];
+};
+
+// Entry i of the logarithm's table (see fast_log): inv = 1 / c_i, log = ln c_i.
+struct alignas(16) LogEntry {
+  double inv, log;
+};
+constexpr int kLogEntries = 128;
+constexpr int kLogOrigin = 0x3fe60000;  // high word of 0.6875, the smallest reduced argument
+
 // Knot search by bucket hints: positive doubles order like their IEEE-754
-// bit patterns, so the key (bits >> shift) of a query selects a bucket of a
-// 1D knot table; the bucket's hint is the largest cell index whose knot is
+// bit patterns, so the key (high word >> shift) of a query selects a bucket of
+// a 1D knot table; the bucket's hint is the largest cell index whose knot is
 // <= the bucket's smallest value, and at most two more knots lie inside any
 // bucket.  The cell of v is then the hint advanced over the next two knots
 // that are <= v -- the same index as a binary search with the same raw FP64
 // comparisons.  A table with no hint list (off < 0) is binary searched.
 struct HintAxis {
-  int off;        // first hint in MemberDev::hints, -1 for none
-  int n;          // buckets
-  int shift;      // key = (unsigned)(bits(v) >> shift)
-  unsigned key0;  // key of the first knot
+  int off;    // first hint in the table block's hints, -1 for none
+  int n;      // buckets
+  int shift;  // key = high word(v) >> shift
+  int key0;   // key of the first knot
 };
 
+// x axis of a sub-grid (used when the sub-grids' x knots differ).
 struct SubDesc {
-  int nx, nq;        // knot counts
-  int nxp, nqp;      // storage extents (>= 4; rows beyond the knots are zero)
-  int xk_off, qk_off;  // knot offsets (doubles) into MemberDev::knots
-  int xc_off, qc_off;  // cell offsets into MemberDev::cells
-  HintAxis xh, qh;     // knot-search hints of the two axes
-  int64_t val_off64;   // element offset of values[ix][iq][c] into v64 (row stride P64)
-  int64_t val_off32;   // element offset into v32 (row stride P32)
-  double qfirst;       // first Q^2 knot
+  int nx;
+  int xk_off, xc_off;  // knot and cell offsets into the table block's knots and cells
+  HintAxis xh;
 };
 
-// The point-location tables of a member (knots, cell coefficients, search
-// hints, sub-grid descriptors) are one contiguous device block of tbl_bytes,
-// copied whole into LDS by the kernels when it fits there.
+// The point-location tables of a member are one contiguous device block of
+// tbl_bytes -- knots (x tables, then the Q^2 knots of all sub-grids, thresholds
+// once), x cells, Q^2 cells, search hints, sub-grid x axes, logarithm table --
+// copied whole into LDS by the kernels when it fits there.  The grid values
+// are rows of P columns, row (k, ix, iq) at row_off_k + ix nqp_k + iq.
 struct MemberDev {
   int K;                 // sub-grids
   int P;                 // stored columns
   int P64, P32;          // row strides of v64 / v32 (zero padding; FP64 rows are whole 64/128-byte lines)
+  int rows;              // rows of all sub-grids
   int64_t elems64, elems32;  // value elements (padded) of v64 / v32
-  int nknots;            // total knots (all sub-grids, x then Q^2 each; shared x tables stored once)
-  int nknots_pad;        // nknots rounded up to an even count
   int tbl_bytes;         // bytes of the location-table block (multiple of 16)
-  int cells_off, hints_off, subs_off;  // byte offsets of cells, hints and sub-grid descriptors in it
+  int cells_off, qcells_off, hints_off, subs_off, logt_off;  // byte offsets in it
+  int nqk, qk_off;       // Q^2 knots of all sub-grids, their offset in the knots
+  HintAxis qh;
+  int shared_x;          // every sub-grid has sub-grid 0's x knots: the axis below
+  int nx, xk_off, xc_off;
+  HintAxis xh;
   double xmin, xmax;     // x range (shared by all sub-grids)
   double qmin, qmax;     // Q^2 range (first knot of sub-grid 0, last of K-1)
   const unsigned char* tables;  // device, the location-table block
-  const double* knots;   // device, = tables
-  const CellCoef* cells; // device, = tables + cells_off
-  const short* hints;    // device, = tables + hints_off
-  const SubDesc* subs;   // device, = tables + subs_off
   const double* v64;     // device, FP64 values
   const float* v32;      // device, FP32-rounded values
-  SubDesc sub[kMaxSub];
 };
 
 struct ReqCols {
-  int n;             // requested flavours
-  int col[kMaxReq];  // stored column, or -1 for a valid flavour absent from the grid
+  int n;                     // requested flavours
+  signed char col[kMaxReq];  // stored column (< 64), or -1 for a valid flavour absent from the grid
 };
 
 struct LaunchCfg {
@@ -102,18 +122,17 @@ struct LaunchCfg {
   int vector_cols;    // use G-wide column groups for all-column requests
 };
 
+// alpha_s table: the cells of all segments in increasing Q^2, one contiguous
+// device block -- knots [ncell + 1] (thresholds once, padded to an even
+// count), cells, hints, logarithm table -- of `bytes` bytes.
 struct AlphasDev {
-  int n;                   // knots
-  int nseg;
-  int nhints;              // search hints (all segments)
-  int seg_lo[kMaxSeg];     // first knot index of each segment
-  int seg_hi[kMaxSeg];     // last knot index of each segment
-  double seg_first[kMaxSeg];
-  HintAxis seg_hint[kMaxSeg];  // knot-search hints of each segment (off < 0: binary search)
-  const double* knots;     // device, n
-  const double* vals;      // device, n
-  const CellCoef* cells;   // device, cell j = [knot j, knot j+1] (within a segment)
-  const short* hints;      // device, nhints
+  int ncell;
+  int bytes;               // whole block (multiple of 16); the logarithm table is its tail
+  int cells_off, hints_off, logt_off;
+  HintAxis h;
+  double q_lo, q_hi;       // first and last knot
+  double a_lo, a_hi;       // constant values below and above
+  const unsigned char* tables;  // device
 };
 
 }  // namespace pdfmi
@@ -163,6 +182,8 @@ struct SurDev {
   const float* envd;  // [nx][16] envelope slopes d E / d ln x
   // inference trusts the network inside sub-grid k for txlo[k] <= x < txhi[k]
   // and tqlo[k] <= Q^2 < tqhi[k] (second to second-last knots) when trust[k]
+  int K;
+  double qfirst[kMaxSub];  // first Q^2 knot of each sub-grid
   int trust[kMaxSub];
   double txlo[kMaxSub], txhi[kMaxSub], tqlo[kMaxSub], tqhi[kMaxSub];
 };

@@ -531,8 +531,8 @@ __device__ __forceinline__ float env_at(const float* e, const float* d, int i, f
 __device__ __forceinline__ bool trusted(const SurDev& S, const MemberDev& m, double x, double q2) {
   if (!(x >= m.xmin && x <= m.xmax && q2 >= m.qmin && q2 <= m.qmax)) return false;
   int k = 0;
-  for (int j = 1; j < m.K; ++j)
-    if (m.sub[j].qfirst <= q2) k = j;
+  for (int j = 1; j < S.K; ++j)
+    if (S.qfirst[j] <= q2) k = j;
   return S.trust[k] && x >= S.txlo[k] && x < S.txhi[k] && q2 >= S.tqlo[k] && q2 < S.tqhi[k];
 }
 
@@ -608,11 +608,10 @@ __device__ __forceinline__ int kunit(int kp) {
   return ((kp >> 5) << 5) + (((kp >> 2) & 1) << 4) + (((kp >> 3) & 3) << 2) + (kp & 3);
 }
 
-// Location of one fallback point (what interp_point derives before its gathers).
+// Location of one fallback point.
 struct FbRec {
-  float w[4], v[4];
-  int base, sa, mode, pt;  // grid offset and x stride (elements), region bits, slot in the wave's queue
-  double p0, p1;           // extrapolation parameters
+  PointRec<float> r;
+  double p0, p1;  // extrapolation parameters
 };
 
 // LDS of k_sur_infer: the lo and hi halves of W2, W3 (64 x 64) and W4
@@ -701,7 +700,7 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const unsigned short* __rest
   auto frag = [&](const unsigned short* tile, int row, int col0) -> bf16x8 {
     return *reinterpret_cast<const bf16x8*>(tile + swz(row, col0));
   };
-  const Tables gtb{m.knots, m.cells, m.hints, m.subs};
+  const Tables gtb = tables_at(m.tables, m);
   const float* __restrict__ gvals = member_values<float>(m);
   const int R = rc.n;
 
@@ -834,11 +833,10 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const unsigned short* __rest
       if (l < nfb) {
         FbRec& fr = fbr[l];
         const int64_t pi = fq[l];
-        const PointLoc L = locate_point<float>(m, gtb, X[pi], Q2[pi], fr.w, fr.v);
-        fr.base = L.base;
-        fr.sa = L.sa;
-        fr.mode = L.mode;
-        fr.pt = l;
+        const double xf = X[pi], qf = Q2[pi];
+        const QLoc<float> Q = locate_q<float>(m, gtb, qf);
+        const PointLoc L = locate_x<float>(m, gtb, Q, xf, qf, fr.r.w, fr.r.v);
+        set_stencil(fr.r, Q, L, m.P32 * 4);
         fr.p0 = L.p0;
         fr.p1 = L.p1;
         bad = L.mode & kInvalid;
@@ -853,26 +851,24 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const unsigned short* __rest
         const FbRec& fr = fbr[k];
         const int c = scol[j];
         float val;
-        if (fr.mode & kInvalid) {
+        if (fr.r.o & kRecInvalid) {
           val = NAN;
         } else if (c < 0) {
           val = 0.0f;
+        } else if (!(fr.r.o & kRecSlow)) {
+          const float* f0 = gvals + c + fr.r.o / 4;
+          const int s1 = fr.r.s1 / 4, sa = fr.r.sa / 4, s3 = fr.r.s3 / 4;
+          const float* fx[4] = {f0, f0 + s1, f0 + s1 + sa, f0 + s1 + sa + s3};
+          float F[4][4];
+#pragma unroll
+          for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) F[a][b] = fx[a][b * m.P32];
+          val = interp_stencil<float>(F, fr.r.w, fr.r.v);
         } else {
-          const float* f = gvals + fr.base + c;
-          if (!(fr.mode & (kLowX | kLowQ | kHighQ))) {
-            float F[4][4];
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-              for (int b = 0; b < 4; ++b) F[a][b] = f[a * fr.sa + b * m.P32];
-            val = interp_stencil<float>(F, fr.w, fr.v);
-          } else {
-            const Wts wt{(double)fr.w[0], (double)fr.w[1], (double)fr.w[2], (double)fr.w[3],
-                         (double)fr.v[0], (double)fr.v[1], (double)fr.v[2], (double)fr.v[3]};
-            val = (float)extrap_entry<float>(f, fr.sa, m.P32, fr.mode, wt, fr.p0, fr.p1, invL01);
-          }
+          val = rec_extrapolate(fr.r, gvals + c, m.P32, fr.p0, fr.p1, invL01);
         }
-        out[fq[fr.pt] * R + j] = val;
+        out[fq[k] * R + j] = val;
       }
       // the rest of the queue (fewer than 64) to its front: the two ranges do not overlap
       const int rest = qn - nfb;
