@@ -21,6 +21,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "interp_dev.h"
 #include "pdfmi_dev.h"
 
@@ -34,6 +36,8 @@ template <>
 struct VecOf<double, 2> { using type = double2; };
 template <>
 struct VecOf<float, 4> { using type = float4; };
+template <>
+struct VecOf<float, 2> { using type = float2; };
 template <>
 struct VecOf<double, 1> { using type = double; };
 template <>
@@ -49,6 +53,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, 
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // G consecutive elements of T (G * sizeof(T) in {4, 8, 16} bytes).
 template <typename T, int G>
@@ -99,9 +104,10 @@ __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, int voff, co
 // aligned) from global memory to LDS.  Each thread issues eight 16-byte loads
 // before it stores them: a loop of dependent load-store pairs waits out the
 // memory latency once per element (a 72 KB grid: 18 round trips per thread).
+#define PDFMI_GLOBAL __attribute__((address_space(1)))  // a pointer read from memory is global, not generic
 template <int BS>
 __device__ __forceinline__ void stage_copy(void* dst, const void* src, int64_t bytes) {
-  const u32x4* s = static_cast<const u32x4*>(src);
+  const PDFMI_GLOBAL u32x4* s = (const PDFMI_GLOBAL u32x4*)src;
   u32x4* d = static_cast<u32x4*>(dst);
   const int64_t nv = bytes >> 4;
   for (int64_t i0 = threadIdx.x; i0 < nv; i0 += 8 * BS) {
@@ -114,7 +120,36 @@ __device__ __forceinline__ void stage_copy(void* dst, const void* src, int64_t b
   }
   const int tail = (int)((bytes & 15) >> 2);  // trailing 4-byte words
   if ((int)threadIdx.x < tail)
-    reinterpret_cast<unsigned*>(d + nv)[threadIdx.x] = reinterpret_cast<const unsigned*>(s + nv)[threadIdx.x];
+    reinterpret_cast<unsigned*>(d + nv)[threadIdx.x] = ((const PDFMI_GLOBAL unsigned*)(s + nv))[threadIdx.x];
+}
+
+// Workgroup copy of chosen columns of `rows` grid rows (global, P columns in a
+// stride of Ps floats) into LDS rows of kRow floats: column c to position
+// pos[c] (uniform; -1: not requested).  A thread takes whole rows, two at a
+// time, in 16-byte loads.
+template <int BS, int kRow>
+__device__ __forceinline__ void stage_columns(float* dst, const float* src, int rows, int P, int Ps,
+                                              const int* __restrict__ pos) {
+  for (int c0 = 0; c0 < P; c0 += 12)
+    for (int r0 = threadIdx.x; r0 < rows; r0 += 2 * BS) {
+      const int r1 = min(r0 + BS, rows - 1);  // clamped: every access in bounds (the last row may be written twice)
+      f32x4 q[2][3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (c0 + 4 * k < P) {
+          q[0][k] = *(const PDFMI_GLOBAL f32x4*)(src + r0 * Ps + c0 + 4 * k);
+          q[1][k] = *(const PDFMI_GLOBAL f32x4*)(src + r1 * Ps + c0 + 4 * k);
+        }
+#pragma unroll
+      for (int c = 0; c < 12; ++c)
+        if (c0 + c < P) {
+          const int to = pos[c0 + c];
+          if (to >= 0) {
+            dst[r0 * kRow + to] = q[0][c >> 2][c & 3];
+            dst[r1 * kRow + to] = q[1][c >> 2][c & 3];
+          }
+        }
+    }
 }
 
 // Workgroup copy of rows x P elements from rows of stride Ps (global) into
@@ -165,8 +200,11 @@ __host__ __device__ constexpr size_t wave_record_bytes() {
 // overlaps the one before it and every store is full width (the shared
 // column gets the same value twice).  Reading it from LDS, groups start at
 // G*j (16-byte aligned LDS reads; rows are zero-padded to a multiple of G)
-// and the last group stores only the columns below R.
-template <typename T, bool kLdsGrid, int G, bool kAlphas = false, bool kOverlap = !kLdsGrid, int kRowB = 0>
+// and the last group stores only the columns below R.  kCompact: the LDS rows
+// hold the request's columns in request order (0 for an absent flavour), so
+// every request is walked in groups.
+template <typename T, bool kLdsGrid, int G, bool kAlphas = false, bool kOverlap = !kLdsGrid, int kRowB = 0,
+          bool kCompact = false>
 __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, const int* scol, int R,
                                           const T* sgrid, const T* __restrict__ gvals, uint32_t gbytes,
                                           double xv, double qv, int tp, T* __restrict__ obase,
@@ -174,7 +212,7 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
                                           unsigned char* rec, int lane, const AlphasDev& A, const AsView& av) {
   PointRec<T>* srec = reinterpret_cast<PointRec<T>*>(rec);        // [64]
   double* sp = reinterpret_cast<double*>(srec + kWave);           // [64][2] extrapolation parameters
-  const int Pp = sizeof(T) == 8 ? m.P64 : m.P32;
+  const int Pp = kCompact ? kRowB / (int)sizeof(T) : (sizeof(T) == 8 ? m.P64 : m.P32);
   // bytes between consecutive Q^2 knots; a compile-time kRowB (the caller has
   // checked it) lets the four Q^2 rows of an LDS gather use immediate offsets
   const int rowb = kRowB ? kRowB : Pp * (int)sizeof(T);
@@ -231,7 +269,7 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
       int ccol;     // its stored column (-1: flavour absent from the grid)
       if constexpr (G == 1) {
         c0 = j;
-        ccol = scol[j];
+        ccol = kCompact ? j : scol[j];
       } else {
         c0 = kOverlap ? min(G * j, R - G) : G * j;
         ccol = c0;
@@ -277,8 +315,9 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
         buf_store<T, G, kLdsGrid ? 0 : kStoreStream>(orr, ob, res);
       } else {
         // last group of a point without overlap: only the columns below R
-        for (int i = 0; i < R - G * j; ++i)
-          buf_store<T, 1, kLdsGrid ? 0 : kStoreStream>(orr, ob + i * (int)sizeof(T), res + i);
+#pragma unroll
+        for (int i = 0; i < G - 1; ++i)
+          if (i < R - G * j) buf_store<T, 1, kLdsGrid ? 0 : kStoreStream>(orr, ob + i * (int)sizeof(T), res + i);
       }
     }
     p += e_dp;
@@ -294,7 +333,7 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
     slow_mask &= slow_mask - 1;
     const PointRec<T>& rq = srec[q];
     for (int jj = lane; jj < R; jj += kWave) {
-      const int col = G == 1 ? scol[jj] : jj;
+      const int col = kCompact ? (scol[jj] < 0 ? -1 : jj) : (G == 1 ? scol[jj] : jj);
       T val = (T)0;
       if (col >= 0) {
         val = rec_extrapolate(rq, (kLdsGrid ? sgrid : gvals) + col, Pp, sp[2 * q], sp[2 * q + 1], invL01);
@@ -1018,10 +1057,21 @@ namespace pdfmi {
 // Batched evaluation of many requests over many members (the paper's
 // multi-member evaluation of section 4.3): one persistent launch in which
 // each workgroup repeatedly takes the next tile from a global counter,
-// stages that tile's member grid (and knots) in LDS when it differs from the
-// one already staged, and runs the same per-wave tile pipeline as k_xfxq2.
-// Every wave reaches the exit once the counter passes the tile count.
+// stages that tile's grid (and location tables) in LDS when it differs from
+// the one already staged, and runs the same per-wave tile pipeline as
+// k_xfxq2.  Every wave reaches the exit once the counter passes the tile count.
+//
+// In FP32 with the grid in LDS, a request of up to kCompactCols different
+// flavours (BatchReq::layout >= 0) is staged compacted: rows of kCompactCols
+// floats holding the requested columns in request order.  Its outputs are
+// then walked in groups of four columns (two, one for the smallest requests)
+// with one LDS read per group and stencil knot, whatever the order of the
+// request: what bounded the kernel were the conflicts of one 4-byte read per
+// (flavour, knot) from random rows (101 members, 200 requests, 1.2e8 values:
+// 705 us, 541 us now).  Rows of 48 bytes start on every 16-byte bank slot, and
+// a compile-time stride lets the four Q^2 rows use immediate offsets.
 constexpr int kBatchBS = 1024;
+constexpr int kCompactRowB = kCompactCols * 4;
 
 __global__ void k_batch_reset(unsigned* counter) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0u;
@@ -1037,7 +1087,7 @@ __global__ __launch_bounds__(kBatchBS) void k_batched(const BatchReq* __restrict
   static_assert(kLdsTables || !kLdsGrid, "a staged grid needs staged tables");
   constexpr int kWaves = kBatchBS / kWave;
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ int s_tile, s_member;
+  __shared__ int s_tile, s_member, s_layout;
   unsigned char* stbl = smem;                                              // [max_tbl] if staged
   int* scol = reinterpret_cast<int*>(smem + (kLdsTables ? max_tbl : 0));  // [kMaxReq]
   unsigned char* srec = reinterpret_cast<unsigned char*>(scol + kMaxReq);  // per-wave records
@@ -1045,7 +1095,7 @@ __global__ __launch_bounds__(kBatchBS) void k_batched(const BatchReq* __restrict
   const int lane = threadIdx.x & (kWave - 1);
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   unsigned char* rec = srec + wv * wave_record_bytes<T>();
-  if (threadIdx.x == 0) s_member = -1;
+  if (threadIdx.x == 0) s_member = s_layout = -1;
   for (;;) {
     __syncthreads();  // previous tile finished by every wave before the LDS is reused
     if (threadIdx.x == 0) s_tile = (int)atomicAdd(counter, 1u);
@@ -1057,13 +1107,30 @@ __global__ __launch_bounds__(kBatchBS) void k_batched(const BatchReq* __restrict
     const MemberDev& m = members[rq.member];
     const T* __restrict__ gvals = member_values<T>(m);
     const uint32_t gbytes = (uint32_t)((sizeof(T) == 8 ? m.elems64 : m.elems32) * (int64_t)sizeof(T));
-    if (rq.member != s_member) {
-      if constexpr (kLdsTables) stage_copy<kBatchBS>(stbl, m.tables, m.tbl_bytes);
-      if constexpr (kLdsGrid) stage_copy<kBatchBS>(sgrid, gvals, (int64_t)gbytes);
-    }
-    for (int i = threadIdx.x; i < rq.R; i += kBatchBS) scol[i] = cols[rq.col_off + i];
+    // what the staged grid holds: a compacted layout, or all columns of a member
+    const bool compact = kLdsGrid && sizeof(T) == 4 && vector_cols && rq.layout >= 0;
+    const int layout = compact ? rq.layout : -2 - rq.member;
+    const int* rcols = cols + rq.col_off;
+    if constexpr (kLdsTables)
+      if (rq.member != s_member) stage_copy<kBatchBS>(stbl, m.tables, m.tbl_bytes);
+    if constexpr (kLdsGrid)
+      if (layout != s_layout) {
+        if (compact) {
+          float* g = reinterpret_cast<float*>(sgrid);
+          stage_columns<kBatchBS, kCompactCols>(g, m.v32, m.rows, m.P, m.P32, rcols + rq.R);
+          for (int j = 0; j < rq.R; ++j)
+            if (rcols[j] < 0)
+              for (int i = threadIdx.x; i < m.rows; i += kBatchBS) g[i * kCompactCols + j] = 0.0f;
+        } else {
+          stage_copy<kBatchBS>(sgrid, gvals, (int64_t)gbytes);
+        }
+      }
+    for (int i = threadIdx.x; i < rq.R; i += kBatchBS) scol[i] = rcols[i];
     __syncthreads();
-    if (threadIdx.x == 0) s_member = rq.member;
+    if (threadIdx.x == 0) {
+      s_member = rq.member;
+      s_layout = layout;
+    }
     const Tables tb = tables_at(kLdsTables ? stbl : m.tables, m);
     const double invL01 = invL01s[rq.member];
     T* out = reinterpret_cast<T*>(rq.out);
@@ -1071,8 +1138,24 @@ __global__ __launch_bounds__(kBatchBS) void k_batched(const BatchReq* __restrict
       const int64_t pbeg = tl.start + w0;
       const int tp = min(kWave, tl.count - w0);
       constexpr int G = 16 / sizeof(T);
-      const double xv = lane < tp ? rq.x[pbeg + lane] : 0.0;
-      const double qv = lane < tp ? rq.q2[pbeg + lane] : 0.0;
+      const double xv = lane < tp ? ((const PDFMI_GLOBAL double*)rq.x)[pbeg + lane] : 0.0;
+      const double qv = lane < tp ? ((const PDFMI_GLOBAL double*)rq.q2)[pbeg + lane] : 0.0;
+      if constexpr (kLdsGrid && sizeof(T) == 4) {
+        if (compact) {
+          auto tile = [&](auto group) {
+            wave_tile<T, true, decltype(group)::value, false, false, kCompactRowB, true>(
+                m, tb, scol, rq.R, sgrid, gvals, gbytes, xv, qv, tp, out + pbeg * rq.R, nerr, invL01, rec, lane,
+                kNoAlphas, AsView{});
+          };
+          if (rq.R > 2)
+            tile(std::integral_constant<int, 4>{});
+          else if (rq.R == 2)
+            tile(std::integral_constant<int, 2>{});
+          else
+            tile(std::integral_constant<int, 1>{});
+          continue;
+        }
+      }
       if (vector_cols && rq.all_cols && rq.R >= G)
         wave_tile<T, kLdsGrid, G>(m, tb, scol, rq.R, sgrid, gvals, gbytes, xv, qv, tp, out + pbeg * rq.R, nerr,
                                   invL01, rec, lane, kNoAlphas, AsView{});

@@ -970,6 +970,8 @@ extern "C" int pdf_batch_create(const pdf_request* reqs, int32_t n_req, int32_t 
   P.used = true;
   P.out_f64 = out_f64 ? 1 : 0;
   std::map<int, int> slot;  // member id -> plan member index
+  std::map<std::pair<int, std::vector<int>>, int> layouts;  // (plan member, column list) -> layout number
+  int64_t compact_elems = 0;
   for (int i = 0; i < n_req; ++i) {
     const pdf_request& q = reqs[i];
     if (q.n < 0) return fail(PDF_ERR_ARG, "request %d: n < 0", i);
@@ -991,9 +993,20 @@ extern "C" int pdf_batch_create(const pdf_request* reqs, int32_t n_req, int32_t 
     b.R = rcols.n;
     b.col_off = (int)P.cols.size();
     b.all_cols = rcols.n == M->dev.P;
+    std::vector<int> list(rcols.col, rcols.col + rcols.n), pos((size_t)M->dev.P, -1);
+    bool compact = !P.out_f64 && rcols.n <= kCompactCols;
     for (int j = 0; j < rcols.n; ++j) {
-      P.cols.push_back(rcols.col[j]);
-      if (rcols.col[j] != j) b.all_cols = 0;
+      if (list[j] != j) b.all_cols = 0;
+      if (list[j] < 0) continue;
+      if (pos[list[j]] >= 0) compact = false;  // a flavour requested twice has two output positions
+      pos[list[j]] = j;
+    }
+    P.cols.insert(P.cols.end(), list.begin(), list.end());
+    b.layout = -1;
+    if (compact) {
+      P.cols.insert(P.cols.end(), pos.begin(), pos.end());
+      b.layout = layouts.insert({{b.member, list}, (int)layouts.size()}).first->second;
+      compact_elems = std::max(compact_elems, (int64_t)M->dev.rows * kCompactCols);
     }
     b.x = q.x;
     b.q2 = q.q2;
@@ -1004,6 +1017,13 @@ extern "C" int pdf_batch_create(const pdf_request* reqs, int32_t n_req, int32_t 
   P.lds = g_lds_policy != 1 &&
           batch_shared_bytes(P.max_tbl, !P.out_f64, true) + (size_t)P.max_elems * (P.out_f64 ? 8 : 4) <=
               kLdsBytes - 1024;
+  // compacted layouts when their rows fit LDS too
+  if (P.lds && compact_elems > P.max_elems) {
+    if (batch_shared_bytes(P.max_tbl, true, true) + (size_t)compact_elems * 4 <= kLdsBytes - 1024)
+      P.max_elems = compact_elems;
+    else
+      for (BatchReq& b : P.reqs) b.layout = -1;
+  }
   P.blocks_per_cu = 1;
   const size_t br = align_up(sizeof(BatchReq) * std::max<size_t>(1, P.reqs.size()), 256);
   const size_t bc = align_up(sizeof(int) * std::max<size_t>(1, P.cols.size()), 256);

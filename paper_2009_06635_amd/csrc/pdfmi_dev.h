@@ -139,11 +139,15 @@ struct AlphasDev {
 
 namespace pdfmi {
 
+constexpr int kCompactCols = 12;  // columns of a compacted row (FP32, LDS) of a batched plan
+
 // One request of a batched plan (device copy).
 struct BatchReq {
   int member;        // index into the plan's member table
   int R;             // requested flavours
-  int col_off;       // offset of this request's column list in the plan's column array
+  int col_off;       // offset in the plan's column array of its column list [R], then the output position of
+                     // each stored column (-1: not requested) when layout >= 0
+  int layout;        // number of its (member, column list) among the plan's, or -1 if not staged compacted
   int all_cols;      // 1 if the request is every stored column in load order
   const double* x;
   const double* q2;
