@@ -826,6 +826,11 @@ int plan_tiles(Plan& P) {
     for (int64_t s0 = 0; s0 < P.reqs[r].n; s0 += P.tile_points)
       t.push_back(BatchTile{r, (int)std::min<int64_t>(P.tile_points, P.reqs[r].n - s0), s0});
   if ((int64_t)t.size() > (1LL << 30)) return fail(PDF_ERR_ARG, "too many tiles");
+  // the costliest tiles first (points times groups of four columns), so that
+  // the workgroups end together on small ones; equal tiles stay grouped
+  std::stable_sort(t.begin(), t.end(), [&](const BatchTile& a, const BatchTile& b) {
+    return (int64_t)a.count * ((P.reqs[a.req].R + 3) / 4) > (int64_t)b.count * ((P.reqs[b.req].R + 3) / 4);
+  });
   P.ntiles = (int)t.size();
   if (P.ntiles > P.tiles_cap) {
     if (P.d_tiles) (void)hipFree(P.d_tiles);
