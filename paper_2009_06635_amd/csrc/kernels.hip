@@ -153,17 +153,24 @@ __device__ __forceinline__ void stage_columns(float* dst, const float* src, int 
 }
 
 // Workgroup copy of rows x P elements from rows of stride Ps (global) into
-// rows of stride P (LDS), eight loads in flight per thread.
+// rows of stride P (LDS), eight loads in flight per thread; consecutive threads
+// on consecutive elements, (row, column) advanced without a division.
 template <int BS, typename T>
 __device__ __forceinline__ void stage_rows(T* dst, const T* src, int rows, int P, int Ps) {
   const int ne = rows * P;
+  const int drow = BS / P, dcol = BS - drow * P;
+  int row = (int)threadIdx.x / P, col = (int)threadIdx.x - row * P;
   for (int e0 = threadIdx.x; e0 < ne; e0 += 8 * BS) {
     T r[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      const int e = min(e0 + k * BS, ne - 1);  // clamped: every load in bounds
-      const int row = e / P;
-      r[k] = src[(int64_t)row * Ps + (e - row * P)];
+      r[k] = ((const PDFMI_GLOBAL T*)src)[min(row, rows - 1) * Ps + col];  // clamped: every load in bounds
+      row += drow;
+      col += dcol;
+      if (col >= P) {
+        col -= P;
+        ++row;
+      }
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
@@ -617,14 +624,22 @@ namespace pdfmi {
 constexpr int kMcThreads = 256;
 constexpr int kMcBlock = 1024;  // 4 points per thread: a 1e6-point chunk spans ~1000 blocks
 
+// Sum of 256 values in the order of a binary tree (t + 128, t + 64, ..., t + 1),
+// given values t, t + 64, t + 128, t + 192 in lane t of one wave: the first two
+// levels within the lane, the others across lanes.
+__device__ __forceinline__ double wave_tree_sum(double v0, double v1, double v2, double v3) {
+  double v = (v0 + v2) + (v1 + v3);
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) v += __shfl_down(v, s);
+  return v;  // in lane 0
+}
+
+// The same over a workgroup's 256 values, one barrier; the sum in thread 0.
 __device__ __forceinline__ double block_tree_sum(double v, double* sh) {
   sh[threadIdx.x] = v;
   __syncthreads();
-  for (int s = kMcThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
-  }
-  return sh[0];
+  const int t = threadIdx.x & 63;
+  return threadIdx.x < 64 ? wave_tree_sum(sh[t], sh[t + 64], sh[t + 128], sh[t + 192]) : 0.0;
 }
 
 // Stage 1 when the rows do not fit LDS (many flavours): the same order read
@@ -689,7 +704,14 @@ __global__ __launch_bounds__(kMcThreads) void k_mc_final(const double* __restric
                                                          double* __restrict__ sum_out) {
   __shared__ double sh[kMcThreads];
   double acc = 0.0;
-  for (int64_t i = threadIdx.x; i < np; i += kMcThreads) acc += partial[i];
+  for (int64_t i0 = threadIdx.x; i0 < np; i0 += 8 * kMcThreads) {  // eight loads in flight, added in order
+    double v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = partial[min(i0 + k * kMcThreads, np - 1)];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (i0 + k * kMcThreads < np) acc += v[k];
+  }
   const double s = block_tree_sum(acc, sh);
   if (threadIdx.x == 0) *sum_out = s;
 }
@@ -826,13 +848,14 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
                                                          const double* __restrict__ X2,
                                                          const double* __restrict__ Q2, int64_t n,
                                                          double* __restrict__ partial,
-                                                         unsigned long long* __restrict__ nerr, double invL01) {
+                                                         unsigned long long* __restrict__ nerr, double invL01,
+                                                         int split) {
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* stbl = smem;
   unsigned char* sas = smem + (kLdsTables ? m.tbl_bytes : 0);
   const int as_bytes = alphas_staged_bytes(A, kLdsTables);
-  double* tree = reinterpret_cast<double*>(sas + as_bytes);  // [4][256]
-  int* scol = reinterpret_cast<int*>(tree + kMcFusedBS);  // [kMaxReq]
+  double* tree = reinterpret_cast<double*>(sas + as_bytes);  // [4][256], twice when split
+  int* scol = reinterpret_cast<int*>(tree + (split ? 2 : 1) * kMcFusedBS);  // [kMaxReq]
   int* sstep = scol + kMaxReq;                            // [kMaxReq + 4] column-group steps (kGW > 1)
   T* sgrid = reinterpret_cast<T*>(sstep + kMaxReq + 4);   // 16-byte aligned: 2 kMaxReq + 4 ints
 
@@ -855,11 +878,12 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
   const int q = threadIdx.x / kMcThreads, t = threadIdx.x % kMcThreads;
   const int R = rc.n;
   const int64_t nmb = (n + kMcBlock - 1) / kMcBlock;
-  for (int64_t mb0 = (int64_t)blockIdx.x * 4; mb0 < nmb; mb0 += (int64_t)gridDim.x * 4) {
-    const int64_t mb = mb0 + q;
+  const int per_wg = split ? 1 : 4;  // blocks of points a workgroup has in hand
+  for (int64_t mb0 = (int64_t)blockIdx.x * per_wg; mb0 < nmb; mb0 += (int64_t)gridDim.x * per_wg) {
+    const int64_t mb = split ? mb0 : mb0 + q;
     const int64_t beg = mb * kMcBlock, end = min(beg + (int64_t)kMcBlock, n);
-    double acc = 0.0;
-    for (int k = 0; k < kMcBlock / kMcThreads; ++k) {
+    double acc = 0.0, as1 = 0.0;
+    for (int k = split ? q : 0; k < (split ? q + 1 : kMcBlock / kMcThreads); ++k) {
       const int64_t i = beg + t + (int64_t)kMcThreads * k;
       const bool live = mb < nmb && i < end;
       double x1 = 0.5, x2 = 0.5, q2 = 10.0;
@@ -979,25 +1003,53 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
           lum = fma((double)f1, (double)f2, lum);
         }
       }
-      if (live) acc = fma(as, lum, acc);
+      if (split) {
+        acc = live ? lum : 0.0;
+        as1 = live ? as : 0.0;
+      } else if (live) {
+        acc = fma(as, lum, acc);
+      }
+    }
+    if (split) {
+      // wave 0 adds the block's terms in the same order: thread t's points in
+      // increasing k, then the tree; meanwhile the others take the next block
+      __syncthreads();  // wave 0 has read the previous block's terms
+      tree[threadIdx.x] = acc;
+      tree[kMcFusedBS + threadIdx.x] = as1;
+      __syncthreads();
+      if (threadIdx.x < 64) {
+        double c[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          c[u] = 0.0;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int e = k * kMcThreads + u * 64 + t;
+            c[u] = fma(tree[kMcFusedBS + e], tree[e], c[u]);
+          }
+        }
+        const double v = wave_tree_sum(c[0], c[1], c[2], c[3]);
+        if (t == 0) partial[mb] = v;
+      }
+      continue;
     }
     // the tree of block_tree_sum, per quarter
     double* sh = tree + q * kMcThreads;
+    __syncthreads();  // the previous blocks' values have been read
     sh[t] = acc;
     __syncthreads();
-    for (int st = kMcThreads / 2; st > 0; st >>= 1) {
-      if (t < st) sh[t] += sh[t + st];
-      __syncthreads();
+    if (t < 64) {
+      const double v = wave_tree_sum(sh[t], sh[t + 64], sh[t + 128], sh[t + 192]);
+      if (t == 0 && mb < nmb) partial[mb] = v;
     }
-    if (t == 0 && mb < nmb) partial[mb] = sh[0];
-    __syncthreads();
   }
 }
 
 // LDS bytes of k_mc_fused (grid_elems > 0: the grid staged with row stride P).
 static size_t mc_fused_shared_bytes(const MemberDev& m, const AlphasDev& A, int64_t grid_elems, bool f32,
-                                    bool tables) {
-  return (tables ? (size_t)m.tbl_bytes : 0) + (size_t)alphas_staged_bytes(A, tables) + kMcFusedBS * 8 +
+                                    bool tables, bool split = false) {
+  return (tables ? (size_t)m.tbl_bytes : 0) + (size_t)alphas_staged_bytes(A, tables) +
+         (split ? 2 : 1) * kMcFusedBS * 8 +
          (2 * kMaxReq + 4) * 4 + (size_t)grid_elems * (f32 ? 4 : 8);
 }
 
@@ -1020,8 +1072,19 @@ hipError_t launch_mc_fused(const MemberDev& m, const ReqCols& rc, const AlphasDe
                      : lds_1 <= 160 * 1024          ? 2
                      : lds_0 <= 160 * 1024          ? 1
                                                     : 0;
-    const size_t shm = mode == 3 ? lds_g : mode == 2 ? lds_1 : mode == 1 ? lds_0
-                                                                          : mc_fused_shared_bytes(m, A, 0, f32, false);
+    size_t shm = mode == 3 ? lds_g : mode == 2 ? lds_1 : mode == 1 ? lds_0 : mc_fused_shared_bytes(m, A, 0, f32, false);
+    // One block of points per workgroup, its four points per thread over the
+    // four quarters, when that takes fewer rounds than four blocks per
+    // workgroup: rounds of 1024 points on the slots of the chip (300007 points,
+    // 293 blocks: 2 rounds instead of 4, FP32 55 -> 38 us; 1e6 points: 4
+    // either way, and then the barrier per round costs 3 %, 91 against 94 us).
+    auto rounds = [&](size_t bytes, int per_wg) {
+      const int64_t slots = (int64_t)n_cu * max(1, (int)(160 * 1024 / bytes));
+      return ((np + per_wg - 1) / per_wg + slots - 1) / slots * per_wg;
+    };
+    const size_t shm_split = shm + kMcFusedBS * 8;
+    const int split = shm_split <= 160 * 1024 && rounds(shm_split, 1) < rounds(shm, 4);
+    if (split) shm = shm_split;
     auto kernel = mode == 3   ? &k_mc_fused<T, true, kGW>
                   : mode == 2 ? &k_mc_fused<T, true, 1>
                   : mode == 1 ? &k_mc_fused<T, false, 1>
@@ -1030,9 +1093,9 @@ hipError_t launch_mc_fused(const MemberDev& m, const ReqCols& rc, const AlphasDe
     hipError_t e = allow_dynamic_lds(fn, shm);
     if (e != hipSuccess) return e;
     const int per_cu = max(1, (int)(160 * 1024 / shm));
-    const int64_t nb = min((np + 3) / 4, (int64_t)n_cu * per_cu);
+    const int64_t nb = min(split ? np : (np + 3) / 4, (int64_t)n_cu * per_cu);
     hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(kMcFusedBS), shm, s, m, rc, A, x1, x2, q2, n, partial, nerr,
-                       invL01);
+                       invL01, split);
   }
   hipLaunchKernelGGL(k_mc_final, dim3(1), dim3(kMcThreads), 0, s, partial, np, sum_out);
   return hipGetLastError();
