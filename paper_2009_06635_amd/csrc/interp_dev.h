@@ -367,9 +367,8 @@ static __device__ __noinline__ double extrap_entry(const T* f, int s1, int sa, i
 // others: weights and location side by side (80 bytes in FP64, 48 in FP32), so
 // that the 9-16 different records one load instruction reads fall in
 // different LDS banks.  Locations are bytes: the stencil's first row and the
-// steps between its x knots.  All are multiples of 16; the low bits carry the
-// point's state: bits 0 and 1 of o say outside the grid and invalid, and the
-// low four bits of s1 and s3 hold the mode of a point that is either.
+// steps between its x knots.  All are multiples of 4; bits 0 and 1 of o say
+// outside the grid and invalid (the mode of a point outside is kept apart).
 template <typename T>
 struct PointRec {
   T w[4];
@@ -384,24 +383,19 @@ __device__ __forceinline__ void set_stencil(PointRec<T>& r, const QLoc<T>& Q, co
   r.sa = (int)__umul24((unsigned)Q.nqp, (unsigned)rowb);
   r.s1 = L.s1 ? r.sa : 0;
   r.s3 = L.s3 ? r.sa : 0;
-  if (L.mode) {
-    r.o |= L.mode & kInvalid ? kRecInvalid : kRecSlow;
-    r.s1 |= L.mode & 15;  // region
-    r.s3 |= (L.mode & kXHigh ? 1 : 0) | ((L.mode >> 8) & 3) << 1;
-  }
+  if (L.mode) r.o |= L.mode & kInvalid ? kRecInvalid : kRecSlow;
 }
 
-// One column of a point outside the grid (kRecSlow); col0 points at the
-// column's entry of grid row 0.
+// One column of a point outside the grid (kRecSlow) with its mode and
+// extrapolation parameters; col0 points at the column's entry of grid row 0.
 template <typename T>
-__device__ __forceinline__ T rec_extrapolate(const PointRec<T>& r, const T* col0, int Pp, double p0, double p1,
-                                             double invL01) {
-  const int mode = (r.s1 & 15) | (r.s3 & 1 ? kXHigh : 0) | ((r.s3 >> 1) & 3) << 8;
+__device__ __forceinline__ T rec_extrapolate(const PointRec<T>& r, int mode, double p0, double p1, const T* col0,
+                                             int Pp, double invL01) {
   const int es = (int)sizeof(T);
   const Wts wt{(double)r.w[0], (double)r.w[1], (double)r.w[2], (double)r.w[3],
                (double)r.v[0], (double)r.v[1], (double)r.v[2], (double)r.v[3]};
-  const T* f = reinterpret_cast<const T*>(reinterpret_cast<const unsigned char*>(col0) + (r.o & ~15));
-  return (T)extrap_entry<T>(f, (r.s1 & ~15) / es, r.sa / es, (r.s3 & ~15) / es, Pp, mode, wt, p0, p1, invL01);
+  const T* f = reinterpret_cast<const T*>(reinterpret_cast<const unsigned char*>(col0) + (r.o & ~3));
+  return (T)extrap_entry<T>(f, r.s1 / es, r.sa / es, r.s3 / es, Pp, mode, wt, p0, p1, invL01);
 }
 
 }  // namespace pdfmi

@@ -192,7 +192,7 @@ __device__ constexpr AlphasDev kNoAlphas{};
 
 template <typename T>
 __host__ __device__ constexpr size_t wave_record_bytes() {
-  return (size_t)kWave * (sizeof(PointRec<T>) + 16);
+  return (size_t)kWave * (sizeof(PointRec<T>) + 16 + 4);
 }
 
 // One wave's 64-point tile [pbeg, pbeg + tp): phase 1 (one lane per point,
@@ -219,6 +219,7 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
                                           unsigned char* rec, int lane, const AlphasDev& A, const AsView& av) {
   PointRec<T>* srec = reinterpret_cast<PointRec<T>*>(rec);        // [64]
   double* sp = reinterpret_cast<double*>(srec + kWave);           // [64][2] extrapolation parameters
+  int* smode = reinterpret_cast<int*>(sp + 2 * kWave);            // [64] modes of the points outside the grid
   const int Pp = kCompact ? kRowB / (int)sizeof(T) : (sizeof(T) == 8 ? m.P64 : m.P32);
   // bytes between consecutive Q^2 knots; a compile-time kRowB (the caller has
   // checked it) lets the four Q^2 rows of an LDS gather use immediate offsets
@@ -242,9 +243,10 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
     bad = L.mode & kInvalid;
     slow = L.mode & kSlow;
     set_stencil(r, Q, L, rowb);
-    if (L.mode) {
+    if (slow) {
       sp[2 * lane] = L.p0;
       sp[2 * lane + 1] = L.p1;
+      smode[lane] = L.mode;
     }
     srec[lane] = r;
   }
@@ -340,10 +342,10 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
     slow_mask &= slow_mask - 1;
     const PointRec<T>& rq = srec[q];
     for (int jj = lane; jj < R; jj += kWave) {
-      const int col = kCompact ? (scol[jj] < 0 ? -1 : jj) : (G == 1 ? scol[jj] : jj);
+      const int col = kCompact || G > 1 ? (scol[jj] < 0 ? -1 : jj) : scol[jj];
       T val = (T)0;
       if (col >= 0) {
-        val = rec_extrapolate(rq, (kLdsGrid ? sgrid : gvals) + col, Pp, sp[2 * q], sp[2 * q + 1], invL01);
+        val = rec_extrapolate(rq, smode[q], sp[2 * q], sp[2 * q + 1], (kLdsGrid ? sgrid : gvals) + col, Pp, invL01);
       }
       obase[q * R + jj] = val;
     }
@@ -571,12 +573,38 @@ static bool all_columns(const MemberDev& m, const ReqCols& rc, int G) {
   return true;
 }
 
+// Copy of the requested columns of `rows` grid rows (stride Ps) in request
+// order, rows of Rp values; absent flavours and padding are 0.
+template <typename T>
+__global__ void k_compact(const T* __restrict__ src, int64_t elems, int Ps, ReqCols rc, int Rp, T* __restrict__ dst) {
+  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (e >= elems) return;
+  const int64_t row = e / Rp;
+  const int j = (int)(e - row * Rp);
+  const int c = j < rc.n ? rc.col[j] : -1;
+  dst[e] = c >= 0 ? src[row * Ps + c] : (T)0;
+}
+
+hipError_t launch_compact(const MemberDev& m, const ReqCols& rc, bool f32, int Rp, void* dst, hipStream_t s) {
+  const int64_t elems = (int64_t)m.rows * Rp;
+  const dim3 nb((unsigned)((elems + 255) / 256));
+  if (f32)
+    hipLaunchKernelGGL(k_compact<float>, nb, dim3(256), 0, s, m.v32, elems, m.P32, rc, Rp, static_cast<float*>(dst));
+  else
+    hipLaunchKernelGGL(k_compact<double>, nb, dim3(256), 0, s, m.v64, elems, m.P64, rc, Rp,
+                       static_cast<double*>(dst));
+  return hipGetLastError();
+}
+
 // A, aout: the alpha_s table and output of a fused evaluation, or null.
+// compact: the member's values are a copy compacted to the request (rc.col[j]
+// is j, or -1 for an absent flavour): walked in groups like a request for all
+// columns.
 hipError_t launch_xfxq2_f64(const MemberDev& m, const ReqCols& rc, const double* x, const double* q2, int64_t n,
                             double* out, unsigned long long* nerr, int lds_grid_elems, double invL01,
-                            const LaunchCfg& cfg, const AlphasDev* A, double* aout, hipStream_t s) {
+                            const LaunchCfg& cfg, const AlphasDev* A, double* aout, bool compact, hipStream_t s) {
   const AsOut ao{aout ? A : nullptr, aout};
-  const bool vec = cfg.vector_cols && all_columns(m, rc, 2);
+  const bool vec = cfg.vector_cols && (compact ? rc.n >= 2 : all_columns(m, rc, 2));
   if (aout)
     return vec ? launch_xfxq2_g<double, 2, true>(m, rc, x, q2, n, out, nerr, lds_grid_elems, invL01, cfg, ao, s)
                : launch_xfxq2_g<double, 1, true>(m, rc, x, q2, n, out, nerr, lds_grid_elems, invL01, cfg, ao, s);
@@ -586,9 +614,12 @@ hipError_t launch_xfxq2_f64(const MemberDev& m, const ReqCols& rc, const double*
 
 hipError_t launch_xfxq2_f32(const MemberDev& m, const ReqCols& rc, const double* x, const double* q2, int64_t n,
                             float* out, unsigned long long* nerr, int lds_grid_elems, double invL01,
-                            const LaunchCfg& cfg, const AlphasDev* A, double* aout, hipStream_t s) {
+                            const LaunchCfg& cfg, const AlphasDev* A, double* aout, bool compact, hipStream_t s) {
   const AsOut ao{aout ? A : nullptr, aout};
-  const bool vec = cfg.vector_cols && all_columns(m, rc, 4);
+  const bool vec = cfg.vector_cols && (compact ? rc.n >= 4 : all_columns(m, rc, 4));
+  if (!vec && compact && rc.n >= 2)
+    return aout ? launch_xfxq2_g<float, 2, true>(m, rc, x, q2, n, out, nerr, lds_grid_elems, invL01, cfg, ao, s)
+                : launch_xfxq2_g<float, 2, false>(m, rc, x, q2, n, out, nerr, lds_grid_elems, invL01, cfg, ao, s);
   if (aout)
     return vec ? launch_xfxq2_g<float, 4, true>(m, rc, x, q2, n, out, nerr, lds_grid_elems, invL01, cfg, ao, s)
                : launch_xfxq2_g<float, 1, true>(m, rc, x, q2, n, out, nerr, lds_grid_elems, invL01, cfg, ao, s);

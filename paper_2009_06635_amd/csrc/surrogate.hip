@@ -609,10 +609,23 @@ __device__ __forceinline__ int kunit(int kp) {
 }
 
 // Location of one fallback point.
+// Rows here are whole 16-byte units, so the low four bits of the record's s1
+// and s3 are free: they hold the mode of a point outside the grid.
 struct FbRec {
   PointRec<float> r;
   double p0, p1;  // extrapolation parameters
 };
+__device__ __forceinline__ void fb_set_mode(FbRec& f, int mode) {
+  f.r.s1 |= mode & 15;  // region
+  f.r.s3 |= (mode & kXHigh ? 1 : 0) | ((mode >> 8) & 3) << 1;
+}
+__device__ __forceinline__ float fb_extrapolate(const FbRec& f, const float* col0, int Pp, double invL01) {
+  const int mode = (f.r.s1 & 15) | (f.r.s3 & 1 ? kXHigh : 0) | ((f.r.s3 >> 1) & 3) << 8;
+  PointRec<float> r = f.r;
+  r.s1 &= ~15;
+  r.s3 &= ~15;
+  return rec_extrapolate(r, mode, f.p0, f.p1, col0, Pp, invL01);
+}
 
 // LDS of k_sur_infer: the lo and hi halves of W2, W3 (64 x 64) and W4
 // (16 x 64) with their columns in kunit order, [nx] ln x knots (double),
@@ -837,6 +850,7 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const unsigned short* __rest
         const QLoc<float> Q = locate_q<float>(m, gtb, qf);
         const PointLoc L = locate_x<float>(m, gtb, Q, xf, qf, fr.r.w, fr.r.v);
         set_stencil(fr.r, Q, L, m.P32 * 4);
+        fb_set_mode(fr, L.mode);
         fr.p0 = L.p0;
         fr.p1 = L.p1;
         bad = L.mode & kInvalid;
@@ -866,7 +880,7 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const unsigned short* __rest
             for (int b = 0; b < 4; ++b) F[a][b] = fx[a][b * m.P32];
           val = interp_stencil<float>(F, fr.r.w, fr.r.v);
         } else {
-          val = rec_extrapolate(fr.r, gvals + c, m.P32, fr.p0, fr.p1, invL01);
+          val = fb_extrapolate(fr, gvals + c, m.P32, invL01);
         }
         out[fq[k] * R + j] = val;
       }
