@@ -554,8 +554,16 @@ static hipError_t launch_xfxq2_g(const MemberDev& m, const ReqCols& rc, const do
   }
   if (tables_fit(m) && n >= kStageTablesMinPoints) {
     const size_t shm = shared_bytes(m, f32, kBlockTables, true) + as_bytes;
+    // two workgroups are resident per compute unit; more than that are
+    // launched only while every wave still has about three tiles of its own,
+    // so that the staging of the tables is paid once for several tiles (FP32,
+    // 1.2e6 points: 84 us with one tile per wave, 73 with five) and long
+    // launches keep a queue that evens out the end (FP64, 1e7 points: 817 us
+    // with two workgroups per compute unit, 767 with 24 or more)
     const int64_t ntiles = (n + kBlockTables - 1) / kBlockTables;
-    const int64_t nb = min(ntiles, (int64_t)n_cu * cfg.blocks_per_cu);
+    const int64_t per_cu = ntiles / (3 * (int64_t)n_cu);
+    const int64_t nb =
+        min(ntiles, (int64_t)n_cu * min((int64_t)cfg.blocks_per_cu, max((int64_t)2, per_cu & ~(int64_t)1)));
     return launch_one<T, G, kBlockTables, false, true, kAlphas>(m, rc, x, q2, n, out, nerr, 0, invL01, nb, shm, ao, s);
   }
   const size_t shm = shared_bytes(m, f32, kBlockGlobal, false) + alphas_lds_bytes(ao.A, false);
