@@ -69,6 +69,7 @@ hipError_t launch_mc_fused(const MemberDev&, const ReqCols&, const AlphasDev&, c
 hipError_t launch_fk_contract(const double* F, const double* FK, int nrep, int ndat, int64_t K, double* T, int S,
                               double* ws, hipStream_t s);
 int fk_slices(int nrep, int ndat, int64_t K, int n_cu);
+int fk_limit_slices(int nrep, int ndat, int64_t K, int n_cu);
 size_t fk_scratch_bytes();
 hipError_t fk_scratch_setup(int device, double** out);
 }  // namespace pdfmi
@@ -1944,11 +1945,12 @@ extern "C" int pdf_fk_contract_noalloc(const double* pdf, const double* fk, int3
   int rc = ensure_device();
   if (rc != PDF_OK) return rc;
   if (nrep == 0 || ndat == 0) return PDF_OK;
-  const int S = fk_slices(nrep, ndat, K, g_ncu);
-  const size_t need = S > 1 ? (size_t)S * nrep * ndat * sizeof(double) : 0;
+  const int L = fk_limit_slices(nrep, ndat, K, g_ncu);
+  const size_t need = L > 1 ? (size_t)L * nrep * ndat * sizeof(double) : 0;
   if (need > fk_scratch_bytes())
     return fail(PDF_ERR_ARG, "partial sums of %d K slices x %d x %d doubles need %zu bytes, above the %zu-byte scratch",
-                S, nrep, ndat, need, fk_scratch_bytes());
+                L, nrep, ndat, need, fk_scratch_bytes());
+  const int S = fk_slices(nrep, ndat, K, g_ncu);  // its partial sums always fit
   // every partial sum is written by the contraction kernel before the reduction reads it: nothing to clear
   hipError_t e = launch_fk_contract(pdf, fk, nrep, ndat, K, out, S, g_fk_scratch, (hipStream_t)stream);
   if (e != hipSuccess) return fail_hip(e, "launch fk contraction");
