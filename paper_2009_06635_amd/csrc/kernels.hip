@@ -1161,7 +1161,9 @@ namespace pdfmi {
 // each workgroup repeatedly takes the next tile from a global counter,
 // stages that tile's grid (and location tables) in LDS when it differs from
 // the one already staged, and runs the same per-wave tile pipeline as
-// k_xfxq2.  Every wave reaches the exit once the counter passes the tile count.
+// k_xfxq2.  Every wave reaches the exit once the counter passes the tile count;
+// the last workgroup to leave zeroes it for the next run (a reset kernel before
+// each run cost 5 us).
 //
 // In FP32 with the grid in LDS, a request of up to kCompactCols different
 // flavours (BatchReq::layout >= 0) is staged compacted: rows of kCompactCols
@@ -1172,22 +1174,22 @@ namespace pdfmi {
 // (flavour, knot) from random rows (101 members, 200 requests, 1.2e8 values:
 // 705 us, 541 us now).  Rows of 48 bytes start on every 16-byte bank slot, and
 // a compile-time stride lets the four Q^2 rows use immediate offsets.
-constexpr int kBatchBS = 1024;
+// Threads of a workgroup: one per compute unit with the grid in LDS, else two
+// of half the size, so that a plan of few points spreads over more of them
+// (100 members x 2415 points, FP64: tiles of 512 points on 500 of 512 slots
+// instead of 200 tiles of up to 2048 on 256).
+constexpr int batch_threads(bool lds_grid) { return lds_grid ? 1024 : 512; }
 constexpr int kCompactRowB = kCompactCols * 4;
 
-__global__ void k_batch_reset(unsigned* counter) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0u;
-}
-
 template <typename T, bool kLdsGrid, bool kLdsTables>
-__global__ __launch_bounds__(kBatchBS) void k_batched(const BatchReq* __restrict__ reqs, const int* __restrict__ cols,
+__global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const BatchReq* __restrict__ reqs, const int* __restrict__ cols,
                                                       const BatchTile* __restrict__ tiles, int ntiles,
                                                       const MemberDev* __restrict__ members,
                                                       const double* __restrict__ invL01s, unsigned* counter,
                                                       unsigned long long* __restrict__ nerr, int max_tbl,
                                                       int vector_cols) {
   static_assert(kLdsTables || !kLdsGrid, "a staged grid needs staged tables");
-  constexpr int kWaves = kBatchBS / kWave;
+  constexpr int kBS = batch_threads(kLdsGrid), kWaves = kBS / kWave;
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_tile, s_member, s_layout;
   unsigned char* stbl = smem;                                              // [max_tbl] if staged
@@ -1203,7 +1205,15 @@ __global__ __launch_bounds__(kBatchBS) void k_batched(const BatchReq* __restrict
     if (threadIdx.x == 0) s_tile = (int)atomicAdd(counter, 1u);
     __syncthreads();
     const int t = __builtin_amdgcn_readfirstlane(s_tile);
-    if (t >= ntiles) break;
+    if (t >= ntiles) {
+      // counter[0] the next tile, counter[1] the workgroups that have left: no
+      // other workgroup reads either once all have
+      if (threadIdx.x == 0 && atomicAdd(counter + 1, 1u) == gridDim.x - 1) {
+        atomicExch(counter, 0u);
+        atomicExch(counter + 1, 0u);
+      }
+      break;
+    }
     const BatchTile tl = tiles[t];
     const BatchReq rq = reqs[tl.req];
     const MemberDev& m = members[rq.member];
@@ -1214,20 +1224,20 @@ __global__ __launch_bounds__(kBatchBS) void k_batched(const BatchReq* __restrict
     const int layout = compact ? rq.layout : -2 - rq.member;
     const int* rcols = cols + rq.col_off;
     if constexpr (kLdsTables)
-      if (rq.member != s_member) stage_copy<kBatchBS>(stbl, m.tables, m.tbl_bytes);
+      if (rq.member != s_member) stage_copy<kBS>(stbl, m.tables, m.tbl_bytes);
     if constexpr (kLdsGrid)
       if (layout != s_layout) {
         if (compact) {
           float* g = reinterpret_cast<float*>(sgrid);
-          stage_columns<kBatchBS, kCompactCols>(g, m.v32, m.rows, m.P, m.P32, rcols + rq.R);
+          stage_columns<kBS, kCompactCols>(g, m.v32, m.rows, m.P, m.P32, rcols + rq.R);
           for (int j = 0; j < rq.R; ++j)
             if (rcols[j] < 0)
-              for (int i = threadIdx.x; i < m.rows; i += kBatchBS) g[i * kCompactCols + j] = 0.0f;
+              for (int i = threadIdx.x; i < m.rows; i += kBS) g[i * kCompactCols + j] = 0.0f;
         } else {
-          stage_copy<kBatchBS>(sgrid, gvals, (int64_t)gbytes);
+          stage_copy<kBS>(sgrid, gvals, (int64_t)gbytes);
         }
       }
-    for (int i = threadIdx.x; i < rq.R; i += kBatchBS) scol[i] = rcols[i];
+    for (int i = threadIdx.x; i < rq.R; i += kBS) scol[i] = rcols[i];
     __syncthreads();
     if (threadIdx.x == 0) {
       s_member = rq.member;
@@ -1278,11 +1288,10 @@ static bool batch_tables(bool lds, int max_tbl) { return lds || (size_t)max_tbl 
 
 size_t batch_shared_bytes(int max_tbl, bool f32, bool lds) {
   return (batch_tables(lds, max_tbl) ? (size_t)max_tbl : 0) + kMaxReq * 4 +
-         (kBatchBS / kWave) * (f32 ? wave_record_bytes<float>() : wave_record_bytes<double>());
+         (batch_threads(lds) / kWave) * (f32 ? wave_record_bytes<float>() : wave_record_bytes<double>());
 }
 
-// Kernel node parameters of one batched run: the counter reset and the
-// persistent kernel (used for direct launches and for building a hipGraph).
+// Kernel node parameters of one batched run (used for direct launches and for building a hipGraph).
 
 template <typename T>
 static const void* batch_fn(bool lds, bool tables) {
@@ -1291,14 +1300,16 @@ static const void* batch_fn(bool lds, bool tables) {
                 : reinterpret_cast<const void*>(&k_batched<T, false, false>);
 }
 
-BatchLaunch batch_launch_params(bool f32, bool lds, int max_tbl, int64_t max_elems, int n_cu, int blocks_per_cu,
-                                int ntiles) {
+// Workgroups of a batched run that are resident at once.
+int batch_slots(bool lds, int n_cu) { return n_cu * (1024 / batch_threads(lds)); }
+
+BatchLaunch batch_launch_params(bool f32, bool lds, int max_tbl, int64_t max_elems, int n_cu, int ntiles) {
   BatchLaunch L{};
-  L.reset_fn = reinterpret_cast<const void*>(&k_batch_reset);
   L.shm = batch_shared_bytes(max_tbl, f32, lds) + (lds ? (size_t)max_elems * (f32 ? 4 : 8) : 0);
   const bool tables = batch_tables(lds, max_tbl);
   L.main_fn = f32 ? batch_fn<float>(lds, tables) : batch_fn<double>(lds, tables);
-  const int64_t g = min((int64_t)ntiles, (int64_t)n_cu * blocks_per_cu);
+  L.block = (unsigned)batch_threads(lds);
+  const int64_t g = min((int64_t)ntiles, (int64_t)batch_slots(lds, n_cu));
   L.grid = (unsigned)max((int64_t)1, g);
   return L;
 }
@@ -1307,11 +1318,8 @@ hipError_t batch_prepare(const BatchLaunch& L) {
   return allow_dynamic_lds(L.main_fn, L.shm);
 }
 
-hipError_t batch_launch(const BatchLaunch& L, void** args, unsigned* counter, hipStream_t s) {
-  void* rargs[] = {&counter};
-  hipError_t e = hipLaunchKernel(L.reset_fn, dim3(1), dim3(64), rargs, 0, s);
-  if (e != hipSuccess) return e;
-  return hipLaunchKernel(L.main_fn, dim3(L.grid), dim3(kBatchBS), args, L.shm, s);
+hipError_t batch_launch(const BatchLaunch& L, void** args, hipStream_t s) {
+  return hipLaunchKernel(L.main_fn, dim3(L.grid), dim3(L.block), args, L.shm, s);
 }
 
 }  // namespace pdfmi

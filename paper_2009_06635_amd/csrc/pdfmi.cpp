@@ -34,10 +34,10 @@ hipError_t launch_locate(const MemberDev&, const double*, const double*, int64_t
 hipError_t launch_alphas(const AlphasDev&, const double*, int64_t, double*, unsigned long long*, int, hipStream_t);
 int64_t mc_partials(int64_t n);
 size_t batch_shared_bytes(int max_tbl, bool f32, bool lds);
-BatchLaunch batch_launch_params(bool f32, bool lds, int max_tbl, int64_t max_elems, int n_cu, int blocks_per_cu,
-                                int ntiles);
+BatchLaunch batch_launch_params(bool f32, bool lds, int max_tbl, int64_t max_elems, int n_cu, int ntiles);
+int batch_slots(bool lds, int n_cu);
 hipError_t batch_prepare(const BatchLaunch& L);
-hipError_t batch_launch(const BatchLaunch& L, void** args, unsigned* counter, hipStream_t s);
+hipError_t batch_launch(const BatchLaunch& L, void** args, hipStream_t s);
 int sur_nparams();
 int sur_halves();
 constexpr int kSurMaxEnvKnots = 512;   // the inference kernel stages the envelope in LDS
@@ -895,7 +895,6 @@ struct Plan {
   bool used = false;
   int out_f64 = 0;
   int tile_points = 4096;
-  int blocks_per_cu = 1;
   int vector_cols = 1;
   int use_graph = 0;
   bool lds = false;
@@ -914,7 +913,8 @@ struct Plan {
   int* d_cols = nullptr;
   MemberDev* d_members = nullptr;
   double* d_invL01 = nullptr;
-  unsigned* d_counter = nullptr;
+  unsigned* d_counter = nullptr;   // next tile, workgroups that have left
+  void* compact = nullptr;         // compacted copies of members' values (FP64 plans)
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   // kernel argument storage (addresses handed to hipLaunchKernel / graph nodes)
@@ -935,6 +935,7 @@ void plan_release(Plan& P) {
   plan_free_graph(P);
   if (P.dmem) (void)hipFree(P.dmem);
   if (P.d_tiles) (void)hipFree(P.d_tiles);
+  if (P.compact) (void)hipFree(P.compact);
   P = Plan();
 }
 
@@ -951,9 +952,19 @@ int plan_tiles(Plan& P) {
   std::vector<int> order(P.reqs.size());
   for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return P.reqs[a].member < P.reqs[b].member; });
+  // a plan of few points takes smaller tiles than asked for, down to one pass
+  // of a workgroup, while there are fewer tiles than workgroups could run
+  int tp = P.tile_points;
+  const int slots = batch_slots(P.lds, g_ncu), pass = P.lds ? 1024 : 512;
+  auto tiles_of = [&](int points) {
+    int64_t c = 0;
+    for (const BatchReq& r : P.reqs) c += (r.n + points - 1) / points;
+    return c;
+  };
+  while (tp > pass && tiles_of(tp) < slots) tp = std::max(pass, (tp / 2 + 63) / 64 * 64);
   for (int r : order)
-    for (int64_t s0 = 0; s0 < P.reqs[r].n; s0 += P.tile_points)
-      t.push_back(BatchTile{r, (int)std::min<int64_t>(P.tile_points, P.reqs[r].n - s0), s0});
+    for (int64_t s0 = 0; s0 < P.reqs[r].n; s0 += tp)
+      t.push_back(BatchTile{r, (int)std::min<int64_t>(tp, P.reqs[r].n - s0), s0});
   if ((int64_t)t.size() > (1LL << 30)) return fail(PDF_ERR_ARG, "too many tiles");
   // the costliest tiles first (points times groups of four columns), so that
   // the workgroups end together on small ones; equal tiles stay grouped
@@ -976,7 +987,7 @@ int plan_tiles(Plan& P) {
 }
 
 BatchLaunch plan_params(const Plan& P) {
-  return batch_launch_params(!P.out_f64, P.lds, P.max_tbl, P.max_elems, g_ncu, P.blocks_per_cu, P.ntiles);
+  return batch_launch_params(!P.out_f64, P.lds, P.max_tbl, P.max_elems, g_ncu, P.ntiles);
 }
 
 void plan_args(Plan& P) {
@@ -1001,22 +1012,14 @@ int plan_build_graph(Plan& P) {
   hipError_t e = batch_prepare(L);
   if (e != hipSuccess) return fail_hip(e, "hipFuncSetAttribute(batched)");
   if ((e = hipGraphCreate(&P.graph, 0)) != hipSuccess) return fail_hip(e, "hipGraphCreate");
-  hipKernelNodeParams r{};
-  void* rargs[] = {&P.d_counter};
-  r.func = const_cast<void*>(L.reset_fn);
-  r.gridDim = dim3(1);
-  r.blockDim = dim3(64);
-  r.sharedMemBytes = 0;
-  r.kernelParams = rargs;
-  hipGraphNode_t n1, n2;
-  if ((e = hipGraphAddKernelNode(&n1, P.graph, nullptr, 0, &r)) != hipSuccess) return fail_hip(e, "graph node");
+  hipGraphNode_t node;
   hipKernelNodeParams k{};
   k.func = const_cast<void*>(L.main_fn);
   k.gridDim = dim3(L.grid);
-  k.blockDim = dim3(1024);
+  k.blockDim = dim3(L.block);
   k.sharedMemBytes = (unsigned)L.shm;
   k.kernelParams = P.args;
-  if ((e = hipGraphAddKernelNode(&n2, P.graph, &n1, 1, &k)) != hipSuccess) return fail_hip(e, "graph node");
+  if ((e = hipGraphAddKernelNode(&node, P.graph, nullptr, 0, &k)) != hipSuccess) return fail_hip(e, "graph node");
   if ((e = hipGraphInstantiate(&P.exec, P.graph, nullptr, nullptr, 0)) != hipSuccess)
     return fail_hip(e, "hipGraphInstantiate");
   return PDF_OK;
@@ -1037,7 +1040,7 @@ int plan_run(Plan& P, hipStream_t s) {
   const BatchLaunch L = plan_params(P);
   hipError_t e = batch_prepare(L);
   if (e != hipSuccess) return fail_hip(e, "hipFuncSetAttribute(batched)");
-  e = batch_launch(L, P.args, P.d_counter, s);
+  e = batch_launch(L, P.args, s);
   if (e != hipSuccess) return fail_hip(e, "launch batched");
   return PDF_OK;
 }
@@ -1095,7 +1098,74 @@ extern "C" int pdf_batch_tune_cache(const char* path) {
   return PDF_OK;
 }
 
-extern "C" int pdf_batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, int32_t* plan_out) {
+namespace {
+// Plans with FP64 outputs read the grids from global memory: a request for
+// some of the stored flavours, or in another order, or with absent ones, gets
+// a copy of the member's values compacted to it (see Layout), so that it is
+// walked in 16-byte groups.  The plan keeps the copies, at most kPlanCompact
+// bytes; requests beyond that, and one-shot calls, read the member's rows.
+constexpr size_t kPlanCompact = (size_t)256 << 20;
+
+struct PlanBuilder {
+  std::map<int, int> slot;  // member id -> plan member index
+  std::map<std::pair<int, std::vector<int>>, int> layouts;  // (plan member, column list) -> layout number
+  std::map<std::pair<int, std::vector<int>>, int> copies;   // the same -> plan member index of the compacted copy
+  size_t copied = 0;
+  int64_t compact_elems = 0;
+
+  int add_member(Plan& P, const MemberDev& d, const Member& M) {
+    P.members.push_back(d);
+    P.invL01.push_back(M.invL01);
+    P.max_tbl = std::max(P.max_tbl, d.tbl_bytes);
+    P.max_elems = std::max(P.max_elems, P.out_f64 ? d.elems64 : d.elems32);
+    return (int)P.members.size() - 1;
+  }
+
+  struct Copy {
+    const Member* from;
+    ReqCols rc;
+    int to;         // plan member index
+    size_t offset;  // bytes into the copies' memory
+  };
+  std::vector<Copy> todo;
+
+  // Plan member index of the copy for this request, or -1 to read the member's
+  // rows.  Rows of an even number of values (16-byte groups stay aligned where
+  // the grids fit LDS), never longer than the member's own.
+  int copy_of(Plan& P, int member, const Member& M, const ReqCols& rc, const std::vector<int>& list) {
+    const auto key = std::make_pair(member, list);
+    const auto it = copies.find(key);
+    if (it != copies.end()) return it->second;
+    const int stride = rc.n > 12 ? (rc.n + 15) & ~15 : (rc.n + 1) & ~1;
+    const size_t bytes = align_up((size_t)M.dev.rows * stride * sizeof(double), 256);
+    if (stride > M.dev.P64 || copied + bytes > kPlanCompact) return -1;
+    MemberDev d = M.dev;
+    d.P = rc.n;
+    d.P64 = stride;
+    d.elems64 = (int64_t)M.dev.rows * stride;
+    const int to = add_member(P, d, M);
+    todo.push_back({&M, rc, to, copied});
+    copied += bytes;
+    return copies[key] = to;
+  }
+
+  // Allocates and fills the copies.
+  hipError_t fill(Plan& P) {
+    if (todo.empty()) return hipSuccess;
+    hipError_t e = hipMalloc(&P.compact, copied);
+    for (size_t i = 0; i < todo.size() && e == hipSuccess; ++i) {
+      MemberDev& d = P.members[todo[i].to];
+      double* dst = reinterpret_cast<double*>(static_cast<unsigned char*>(P.compact) + todo[i].offset);
+      d.v64 = dst;
+      e = launch_compact(todo[i].from->dev, todo[i].rc, false, d.P64, dst, nullptr);
+    }
+    return e == hipSuccess ? hipStreamSynchronize(nullptr) : e;
+  }
+};
+
+constexpr int kRetryPlain = 1;  // no memory for the copies: build the plan without them
+
+int batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, bool copies, int32_t* plan_out) {
   if (!plan_out || (n_req > 0 && !reqs) || n_req < 0) return fail(PDF_ERR_ARG, "bad argument");
   std::lock_guard<std::mutex> lock(g_mu);
   int rc = ensure_init();
@@ -1103,27 +1173,25 @@ extern "C" int pdf_batch_create(const pdf_request* reqs, int32_t n_req, int32_t 
   Plan P;
   P.used = true;
   P.out_f64 = out_f64 ? 1 : 0;
-  std::map<int, int> slot;  // member id -> plan member index
-  std::map<std::pair<int, std::vector<int>>, int> layouts;  // (plan member, column list) -> layout number
-  int64_t compact_elems = 0;
+  PlanBuilder B;
   for (int i = 0; i < n_req; ++i) {
     const pdf_request& q = reqs[i];
-    if (q.n < 0) return fail(PDF_ERR_ARG, "request %d: n < 0", i);
-    if (q.n > 0 && (!q.x || !q.q2 || !q.out)) return fail(PDF_ERR_ARG, "request %d: null device pointer", i);
     Member* M = get_member(q.member);
-    if (!M) return fail(PDF_ERR_MEMBER, "request %d: unknown member %d", i, q.member);
+    if (q.n < 0)
+      rc = fail(PDF_ERR_ARG, "request %d: n < 0", i);
+    else if (q.n > 0 && (!q.x || !q.q2 || !q.out))
+      rc = fail(PDF_ERR_ARG, "request %d: null device pointer", i);
+    else if (!M)
+      rc = fail(PDF_ERR_MEMBER, "request %d: unknown member %d", i, q.member);
+    if (rc != PDF_OK) return rc;
     ReqCols rcols{};
     if ((rc = build_req(*M, q.pids, q.n_pids, rcols)) != PDF_OK) return rc;
-    if (!slot.count(q.member)) {
-      slot[q.member] = (int)P.members.size();
-      P.members.push_back(M->dev);
+    if (!B.slot.count(q.member)) {
+      B.slot[q.member] = B.add_member(P, M->dev, *M);
       P.member_ids.push_back({q.member, M->gen});
-      P.invL01.push_back(M->invL01);
-      P.max_tbl = std::max(P.max_tbl, M->dev.tbl_bytes);
-      P.max_elems = std::max(P.max_elems, P.out_f64 ? M->dev.elems64 : M->dev.elems32);
     }
     BatchReq b{};
-    b.member = slot[q.member];
+    b.member = B.slot[q.member];
     b.R = rcols.n;
     b.col_off = (int)P.cols.size();
     b.all_cols = rcols.n == M->dev.P;
@@ -1139,8 +1207,17 @@ extern "C" int pdf_batch_create(const pdf_request* reqs, int32_t n_req, int32_t 
     b.layout = -1;
     if (compact) {
       P.cols.insert(P.cols.end(), pos.begin(), pos.end());
-      b.layout = layouts.insert({{b.member, list}, (int)layouts.size()}).first->second;
-      compact_elems = std::max(compact_elems, (int64_t)M->dev.rows * kCompactCols);
+      b.layout = B.layouts.insert({{b.member, list}, (int)B.layouts.size()}).first->second;
+      B.compact_elems = std::max(B.compact_elems, (int64_t)M->dev.rows * kCompactCols);
+    }
+    if (copies && P.out_f64 && !b.all_cols && b.R >= 2 && q.n > 0) {
+      const int c = B.copy_of(P, b.member, *M, rcols, list);
+      if (c >= 0) {
+        b.member = c;
+        b.all_cols = 1;
+        for (int j = 0; j < b.R; ++j)
+          if (list[j] >= 0) P.cols[b.col_off + j] = j;
+      }
     }
     b.x = q.x;
     b.q2 = q.q2;
@@ -1148,29 +1225,42 @@ extern "C" int pdf_batch_create(const pdf_request* reqs, int32_t n_req, int32_t 
     b.n = q.n;
     P.reqs.push_back(b);
   }
+  if (B.fill(P) != hipSuccess) {
+    (void)hipGetLastError();
+    plan_release(P);
+    return kRetryPlain;
+  }
   P.lds = g_lds_policy != 1 &&
           batch_shared_bytes(P.max_tbl, !P.out_f64, true) + (size_t)P.max_elems * (P.out_f64 ? 8 : 4) <=
               kLdsBytes - 1024;
   // compacted layouts when their rows fit LDS too
-  if (P.lds && compact_elems > P.max_elems) {
-    if (batch_shared_bytes(P.max_tbl, true, true) + (size_t)compact_elems * 4 <= kLdsBytes - 1024)
-      P.max_elems = compact_elems;
+  if (P.lds && B.compact_elems > P.max_elems) {
+    if (batch_shared_bytes(P.max_tbl, true, true) + (size_t)B.compact_elems * 4 <= kLdsBytes - 1024)
+      P.max_elems = B.compact_elems;
     else
       for (BatchReq& b : P.reqs) b.layout = -1;
   }
-  P.blocks_per_cu = 1;
   const size_t br = align_up(sizeof(BatchReq) * std::max<size_t>(1, P.reqs.size()), 256);
   const size_t bc = align_up(sizeof(int) * std::max<size_t>(1, P.cols.size()), 256);
   const size_t bm = align_up(sizeof(MemberDev) * std::max<size_t>(1, P.members.size()), 256);
   const size_t bi = align_up(sizeof(double) * std::max<size_t>(1, P.invL01.size()), 256);
   hipError_t e = hipMalloc(&P.dmem, br + bc + bm + bi + 256);
-  if (e != hipSuccess) return fail_hip(e, "hipMalloc(plan)");
+  if (e != hipSuccess) {
+    plan_release(P);
+    return fail_hip(e, "hipMalloc(plan)");
+  }
   unsigned char* b = static_cast<unsigned char*>(P.dmem);
   P.d_reqs = reinterpret_cast<BatchReq*>(b);
   P.d_cols = reinterpret_cast<int*>(b + br);
   P.d_members = reinterpret_cast<MemberDev*>(b + br + bc);
   P.d_invL01 = reinterpret_cast<double*>(b + br + bc + bm);
   P.d_counter = reinterpret_cast<unsigned*>(b + br + bc + bm + bi);
+  // the tile counter starts at zero; every run leaves it so
+  const unsigned zero[2] = {0u, 0u};
+  if ((e = hipMemcpy(P.d_counter, zero, sizeof zero, hipMemcpyHostToDevice)) != hipSuccess) {
+    plan_release(P);
+    return fail_hip(e, "hipMemcpy(plan)");
+  }
   if (!P.reqs.empty() && (e = hipMemcpy(P.d_reqs, P.reqs.data(), sizeof(BatchReq) * P.reqs.size(),
                                         hipMemcpyHostToDevice)) != hipSuccess) {
     plan_release(P);
@@ -1201,6 +1291,13 @@ extern "C" int pdf_batch_create(const pdf_request* reqs, int32_t n_req, int32_t 
   g_plans.push_back(P);
   *plan_out = (int32_t)(g_plans.size() - 1);
   return PDF_OK;
+}
+
+}  // namespace
+
+extern "C" int pdf_batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, int32_t* plan_out) {
+  const int rc = batch_create(reqs, n_req, out_f64, true, plan_out);
+  return rc == kRetryPlain ? batch_create(reqs, n_req, out_f64, false, plan_out) : rc;
 }
 
 extern "C" int pdf_batch_configure(int32_t plan, int32_t tile_points, int32_t vector_cols, int32_t use_graph) {
@@ -1321,7 +1418,7 @@ extern "C" int pdf_batch_destroy(int32_t plan) {
 namespace {
 int batched_one_shot(const pdf_request* reqs, int32_t n_req, int32_t out_f64, pdf_stream_t stream) {
   int32_t plan = -1;
-  int rc = pdf_batch_create(reqs, n_req, out_f64, &plan);
+  int rc = batch_create(reqs, n_req, out_f64, false, &plan);
   if (rc != PDF_OK) return rc;
   rc = pdf_batch_run(plan, stream);
   if (rc == PDF_OK) {

@@ -163,11 +163,10 @@ struct BatchTile {
   int64_t start;
 };
 
-// Kernel node parameters of one batched run (counter reset + persistent kernel).
+// Kernel node parameters of one batched run (the persistent kernel).
 struct BatchLaunch {
-  const void* reset_fn;
   const void* main_fn;
-  unsigned grid;
+  unsigned grid, block;
   size_t shm;
 };
 
