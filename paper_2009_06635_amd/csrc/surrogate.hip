@@ -34,6 +34,7 @@
 namespace pdfmi {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kH = 64;   // hidden width
@@ -503,17 +504,12 @@ struct EnvW {
   float h00, h10, h01, h11;
 };
 
-__device__ __forceinline__ EnvW env_weights(const double* lxk, int nx, double lx) {
-  int lo = 0, hi = nx - 2;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (lxk[mid] <= lx) lo = mid; else hi = mid - 1;
-  }
-  const double D = lxk[lo + 1] - lxk[lo];
-  const double t = fmin(fmax((lx - lxk[lo]) / D, 0.0), 1.0);
+// Weights of cell i, of width D, at cell parameter u.
+__device__ __forceinline__ EnvW env_cell(int i, double u, double D) {
+  const double t = fmin(fmax(u, 0.0), 1.0);
   const double s = 1.0 - t, t2 = t * t, s2 = s * s;  // factored basis: no cancellation near t = 0, 1
   EnvW w;
-  w.i = lo;
+  w.i = i;
   w.h00 = (float)(s2 * (1.0 + 2.0 * t));
   w.h10 = (float)(t * s2 * D);
   w.h01 = (float)(t2 * (3.0 - 2.0 * t));
@@ -521,11 +517,32 @@ __device__ __forceinline__ EnvW env_weights(const double* lxk, int nx, double lx
   return w;
 }
 
+__device__ __forceinline__ EnvW env_weights(const double* lxk, int nx, double lx) {
+  int lo = 0, hi = nx - 2;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (lxk[mid] <= lx) lo = mid; else hi = mid - 1;
+  }
+  const double D = lxk[lo + 1] - lxk[lo];
+  return env_cell(lo, (lx - lxk[lo]) / D, D);
+}
+
 // E_c at the point whose weights are w (tables [nx][kO] of values and slopes)
 __device__ __forceinline__ float env_at(const float* e, const float* d, int i, float h00, float h10, float h01,
                                         float h11, int c) {
   const int a = i * kO + c, b = a + kO;
   return fmaf(h00, e[a], fmaf(h10, d[a], fmaf(h01, e[b], h11 * d[b])));
+}
+
+// Columns c .. c + 3 (c a multiple of 4), by 16-byte reads.
+__device__ __forceinline__ f32x4 env_at4(const float* e, const float* d, int i, f32x4 h, int c) {
+  const int a = i * kO + c;
+  const f32x4 e0 = *reinterpret_cast<const f32x4*>(e + a), d0 = *reinterpret_cast<const f32x4*>(d + a);
+  const f32x4 e1 = *reinterpret_cast<const f32x4*>(e + a + kO), d1 = *reinterpret_cast<const f32x4*>(d + a + kO);
+  f32x4 r;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) r[q] = fmaf(h[0], e0[q], fmaf(h[1], d0[q], fmaf(h[2], e1[q], h[3] * d1[q])));
+  return r;
 }
 
 __device__ __forceinline__ bool trusted(const SurDev& S, const MemberDev& m, double x, double q2) {
@@ -575,30 +592,44 @@ __global__ void k_gather_samples(const float* __restrict__ in_all, const float* 
 
 // ---------------------------------------------------------------------------------------
 // Fused inference.  Each wave takes 64 consecutive points: their inputs,
-// fallback flags and envelope weights are prepared one lane per point, then
-// the network runs on four 16-point sub-tiles with the activations kept in
-// registers from layer to layer.  Each layer is formed transposed on the
-// matrix cores, h' = tanh(W h + b) with the weights as the A operand and the
-// 16 points' activations as the B operand, three products per operand pair:
-// lane (r, g) then receives units 16 t + 4 g + i (t, i = 0..3) of point r,
-// which are the 16 values it supplies to the next layer's B operand when
-// that layer's 64-deep k index k' = 32 s + 8 g + i stands for unit
+// fallback flags and envelope weights are prepared one lane per point (cell
+// and logarithms from the member's location tables), then the network runs on
+// two sub-tiles of 32 points with the activations kept in registers from
+// layer to layer.  Each layer is formed transposed on the matrix cores,
+// h' = tanh(W h + b) with the weights as the A operand and two columns of 16
+// points' activations as B operands, three products per operand pair: lane
+// (r, g) then receives units 16 t + 4 g + i (t, i = 0..3) of point r, which
+// are the 16 values it supplies to the next layer's B operand when that
+// layer's 64-deep k index k' = 32 s + 8 g + i stands for unit
 // kunit(k') = 16 (2 s + i / 4) + 4 g + i % 4.  The weight columns are staged
 // in LDS in that order (once per workgroup), so no activation passes through
-// LDS.  Layer 1 (two inputs) runs on the VALUs straight into that layout.
-// The outputs times the envelope go to a 16 x 16 LDS tile from which the
-// requested columns are stored point-major, consecutive lanes on consecutive
-// values.  Points in the fallback domain are queued per wave and evaluated
-// 64 at a time by the FP32 interpolator: each is located once (one lane per
-// point: sub-grid, cells, weights), after which one lane per (point,
+// LDS.  Layer 1 is one FP32 matrix product per 16 units, of (W1, b1) with
+// (u, v, 1).  The argument scale of tanh_scaled is folded into the staged
+// weights and biases, and the biases start the accumulators.  The outputs
+// times the envelope go to a 32 x 16 LDS tile from which the requested
+// columns are stored point-major, consecutive lanes on consecutive values,
+// by a walk that is laid out once per workgroup.  Points in the fallback
+// domain are queued per wave and evaluated 64 at a time by the FP32
+// interpolator over what the network wrote: each is located once (one lane
+// per point: sub-grid, cells, weights), after which one lane per (point,
 // requested column) gathers its 4x4 stencil.
+//
+// What bounds it is the vector work of the activations: 192 per point, each
+// an exp2 and a reciprocal at half rate and 5.5 more instructions.  10^7
+// points of 11 columns: 1215 us with 16-point sub-tiles, layer 1 and the bias
+// on the vector units, the halves split by unpacking and two library FP64
+// logarithms and a binary search per point; 1027 us with each weight fragment
+// read for 32 points, layer 1 on the matrix cores and the table lookups;
+// 924 us with the folded scale, the split by dot products and the output walk.
 //
 // LDS rows of 64 BF16 values (the weight halves) hold their eight 16-byte
 // chunks in the order chunk ^ (row & 7), so the 16 rows an operand read
 // touches spread over the banks.  Blocks of 16 waves fill the CU's LDS
-// (4 waves per SIMD, at most 128 VGPRs).
+// (4 waves per SIMD, at most 128 VGPRs; 12 waves without register spills
+// measured 936 us against 908).
 constexpr int kSurWaves = 16;
-constexpr int kSurRec = 8;   // floats per point record: u, v, h00, h10 D, h01, h11 D, cell, fallback
+constexpr int kSurPts = 32;  // points of a sub-tile: two MFMA columns of 16
+constexpr int kSurRec = 8;   // floats per point record: u, v, h00, h10 D, h01, h11 D, cell, (unused)
 
 __device__ __forceinline__ int swz(int row, int col) {  // element offset of (row, col) in a swizzled [.][64] tile
   return row * kH + ((((col >> 3) ^ row) & 7) << 3) + (col & 7);
@@ -606,6 +637,20 @@ __device__ __forceinline__ int swz(int row, int col) {  // element offset of (ro
 // Hidden unit that the k index k' of a layer's B operand stands for (see above).
 __device__ __forceinline__ int kunit(int kp) {
   return ((kp >> 5) << 5) + (((kp >> 2) & 1) << 4) + (((kp >> 3) & 3) << 2) + (kp & 3);
+}
+
+// Four activations tanh from their scaled arguments, split, into values o .. o + 3 of an operand.
+__device__ __forceinline__ void act4(f32x4 z, bf16x8& hi, bf16x8& lo, int o, bf16x2 m0, bf16x2 m1) {
+#pragma unroll
+  for (int i = 0; i < 4; i += 2) {
+    const float v0 = tanh_scaled(z[i]), v1 = tanh_scaled(z[i + 1]);
+    const bf16x2 h = {(__bf16)v0, (__bf16)v1};
+    hi[o + i] = h[0];
+    hi[o + i + 1] = h[1];
+    // v - hi (exact) as a dot product with (-1, 0) or (0, -1): no unpacking of the two halves
+    lo[o + i] = (__bf16)__builtin_amdgcn_fdot2_f32_bf16(h, m0, v0, false);
+    lo[o + i + 1] = (__bf16)__builtin_amdgcn_fdot2_f32_bf16(h, m1, v1, false);
+  }
 }
 
 // Location of one fallback point.
@@ -629,15 +674,15 @@ __device__ __forceinline__ float fb_extrapolate(const FbRec& f, const float* col
 
 // LDS of k_sur_infer: the lo and hi halves of W2, W3 (64 x 64) and W4
 // (16 x 64) with their columns in kunit order, [nx] ln x knots (double),
-// [nx][16] envelope values and slopes, W1 and b1-b3 times 2 log2(e) (the
-// argument scale of tanh_scaled), b4; then per wave a 5 KB area (4 KB for
-// the output tile, later the fallback records; 1 KB for the fallback queue)
-// and the point records.
+// [nx][16] envelope values and slopes, b2 and b3 times 2 log2(e) (the
+// argument scale of tanh_scaled; also in W2, W3), b4, the output walk; then
+// per wave a 5 KB area (4 KB for the output tile, later the fallback records;
+// 1 KB for the fallback queue) and the point records.
 constexpr size_t kSurWaveArea = 4096 + 128 * 8;  // output tile or fallback records, then the fallback queue
 constexpr size_t kSurWTile = (size_t)2 * (2 * kH * kH + kO * kH);  // one half of W2, W3, W4 (BF16)
 __host__ __device__ static inline size_t sur_head_bytes(int nx) {
-  const size_t b = 2 * kSurWTile + (size_t)8 * nx +
-                   (size_t)4 * (2 * nx * kO + 2 * kH + 3 * kH + kO + kMaxReq);
+  const size_t b = 2 * kSurWTile + (size_t)8 * (nx + (nx & 1)) +
+                   (size_t)4 * (2 * nx * kO + 2 * kH + kO + kMaxReq) + (size_t)2 * kSurPts * kMaxReq;
   return (b + 15) & ~(size_t)15;
 }
 constexpr size_t kSurWaveBytes = kSurWaveArea + 64 * kSurRec * 4;
@@ -652,9 +697,8 @@ int sur_infer_waves(int nx) {
 size_t sur_infer_shared_bytes(int nx, int waves) { return sur_head_bytes(nx) + (size_t)waves * kSurWaveBytes; }
 
 __global__ __launch_bounds__(64 * kSurWaves) __attribute__((amdgpu_waves_per_eu(4)))
-void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const unsigned short* __restrict__ Pb,
-                 const float* __restrict__ Pf, const double* __restrict__ X, const double* __restrict__ Q2,
-                 int64_t n, float* __restrict__ out, double invL01, unsigned long long* __restrict__ nerr) {
+void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const float* __restrict__ Pf,
+                 const double* __restrict__ X, const double* __restrict__ Q2, int64_t n, float* __restrict__ out, double invL01, unsigned long long* __restrict__ nerr) {
   extern __shared__ __align__(16) unsigned char sraw[];
   const int BS = blockDim.x, nwav = BS >> 6;
   unsigned short* sw2l = reinterpret_cast<unsigned short*>(sraw);  // [kH][kH] swizzled (16-byte chunks)
@@ -664,18 +708,17 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const unsigned short* __rest
   unsigned short* sw3h = sw2h + kH * kH;
   unsigned short* sw4h = sw3h + kH * kH;
   double* slxk = reinterpret_cast<double*>(sw4h + kO * kH);  // [nx]
-  float* senv = reinterpret_cast<float*>(slxk + S.nx);     // [nx][kO]
+  float* senv = reinterpret_cast<float*>(slxk + S.nx + (S.nx & 1));  // [nx][kO], 16-byte aligned
   float* senvd = senv + S.nx * kO;                         // [nx][kO]
-  float* sw1 = senvd + S.nx * kO;                          // [kH][2]
-  float* sb1 = sw1 + 2 * kH;
-  float* sb2 = sb1 + kH;
+  float* sb2 = senvd + S.nx * kO;
   float* sb3 = sb2 + kH;
   float* sb4 = sb3 + kH;                                   // [kO]
   int* scol = reinterpret_cast<int*>(sb4 + kO);            // [kMaxReq] stored column of each requested flavour
+  unsigned short* swalk = reinterpret_cast<unsigned short*>(scol + kMaxReq);  // [kSurPts][R] offset in the output tile
   unsigned char* waves = sraw + sur_head_bytes(S.nx);
   const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, r = l & 15, g = l >> 4;
   unsigned char* area = waves + (size_t)wv * kSurWaveArea;
-  float* so = reinterpret_cast<float*>(area);                         // [16][kO] output tile
+  float* so = reinterpret_cast<float*>(area);                         // [kSurPts][kO] output tile
   FbRec* fbr = reinterpret_cast<FbRec*>(area);                        // [64] fallback records
   int64_t* fq = reinterpret_cast<int64_t*>(area + 4096);              // [128] queued fallback points
   static_assert(64 * sizeof(FbRec) <= 4096, "fallback records fit the wave area");
@@ -686,29 +729,39 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const unsigned short* __rest
     senv[i] = S.env[i];
     senvd[i] = S.envd[i];
   }
-  for (int i = threadIdx.x; i < 2 * kH; i += BS) sw1[i] = kTwoLog2e * Pf[kOffW1 + i];
   for (int i = threadIdx.x; i < kH; i += BS) {
-    sb1[i] = kTwoLog2e * Pf[kOffB1 + i];
     sb2[i] = kTwoLog2e * Pf[kOffB2 + i];
     sb3[i] = kTwoLog2e * Pf[kOffB3 + i];
   }
   for (int i = threadIdx.x; i < kO; i += BS) sb4[i] = Pf[kOffB4 + i];
   for (int i = threadIdx.x; i < rc.n; i += BS) scol[i] = rc.col[i];
-  const unsigned short* Pl = Pb + kNParams;  // lo halves
+  for (int i = threadIdx.x; i < kSurPts * rc.n; i += BS) {
+    const int pt = i / rc.n, c = rc.col[i - pt * rc.n];
+    swalk[i] = (unsigned short)(c < 0 ? 0xffff : pt * kO + c);
+  }
   for (int i = threadIdx.x; i < kH * kH; i += BS) {  // stored column kp of row n holds W[n][kunit(kp)]
     const int row = i / kH, kp = i % kH, src = row * kH + kunit(kp);
-    sw2l[swz(row, kp)] = Pl[kOffW2 + src];
-    sw3l[swz(row, kp)] = Pl[kOffW3 + src];
-    sw2h[swz(row, kp)] = Pb[kOffW2 + src];
-    sw3h[swz(row, kp)] = Pb[kOffW3 + src];
+    const int o = swz(row, kp);
+    split_bits(kTwoLog2e * Pf[kOffW2 + src], sw2h[o], sw2l[o]);
+    split_bits(kTwoLog2e * Pf[kOffW3 + src], sw3h[o], sw3l[o]);
   }
   for (int i = threadIdx.x; i < kO * kH; i += BS) {
-    const int row = i / kH, kp = i % kH, src = row * kH + kunit(kp);
-    sw4l[swz(row, kp)] = Pl[kOffW4 + src];
-    sw4h[swz(row, kp)] = Pb[kOffW4 + src];
+    const int row = i / kH, kp = i % kH, o = swz(row, kp);
+    split_bits(Pf[kOffW4 + row * kH + kunit(kp)], sw4h[o], sw4l[o]);
   }
   __syncthreads();
 
+  // layer 1 as the FP32 product [W1 | b1 | 0] (u, v, 1, 0): this lane's A operand, row 16 t + r, k = g
+  float w1[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int j = 16 * t + r;
+    w1[t] = g == 3 ? 0.0f : kTwoLog2e * Pf[g == 2 ? kOffB1 + j : kOffW1 + 2 * j + g];
+  }
+
+  unsigned mb0 = 0x0000bf80u, mb1 = 0xbf800000u;  // BF16 (-1, 0) and (0, -1), in registers
+  asm("" : "+s"(mb0), "+s"(mb1));
+  const bf16x2 m0 = __builtin_bit_cast(bf16x2, mb0), m1 = __builtin_bit_cast(bf16x2, mb1);
   // an 8-value chunk (16 bytes) of a swizzled LDS row, as an operand fragment
   auto frag = [&](const unsigned short* tile, int row, int col0) -> bf16x8 {
     return *reinterpret_cast<const bf16x8*>(tile + swz(row, col0));
@@ -730,10 +783,13 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const unsigned short* __rest
       xr = X[p0 + l];
       qr = Q2[p0 + l];
       fb = !trusted(S, m, xr, qr);
-      const double lx = log(xr), lq = log(qr);
-      pr[0] = (float)(2.0 * (lx - S.lx0) * S.ilx - 1.0);
-      pr[1] = (float)(2.0 * (lq - S.lq0) * S.ilq - 1.0);
-      const EnvW ew = env_weights(slxk, S.nx, fb ? S.lx0 : lx);
+      // x cell and ln x from the member's location tables (any x gives a cell in range)
+      const int ei = find_cell(gtb.knots + m.xk_off, m.nx, xr, m.xh, gtb.hints);
+      const CellCoef& c = entry<CellCoef>(gtb.cells, m.xc_off + ei);
+      const double l = fast_log(xr * c.inv_t0, gtb.logt);
+      pr[0] = (float)(2.0 * (slxk[ei] + l - S.lx0) * S.ilx - 1.0);
+      pr[1] = (float)(2.0 * (fast_log(qr, gtb.logt) - S.lq0) * S.ilq - 1.0);
+      const EnvW ew = env_cell(ei, l * c.invD, slxk[ei + 1] - slxk[ei]);
       pr[2] = ew.h00;
       pr[3] = ew.h10;
       pr[4] = ew.h01;
@@ -743,88 +799,88 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const unsigned short* __rest
       pr[0] = pr[1] = pr[2] = pr[3] = pr[4] = pr[5] = 0.0f;
       pr[6] = __int_as_float(0);
     }
-    pr[7] = fb ? 1.0f : 0.0f;
     const unsigned long long fbmask = __ballot(fb);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (int q0 = 0; q0 < np; q0 += 16) {
-      // layer 1 straight into the B layout: lane (r, g) holds unit kunit(32 s + 8 g + i) of point q0 + r
-      const float u = rec[(q0 + r) * kSurRec], v = rec[(q0 + r) * kSurRec + 1];
-      bf16x8 bh[2], bl[2];
+    for (int q0 = 0; q0 < np; q0 += kSurPts) {
+      // B operands (hi, lo) of the two columns of 16 points: bh[p][s][i] is unit kunit(32 s + 8 g + i) of
+      // point q0 + 16 p + r
+      bf16x8 bh[2][2], bl[2][2];
+      // layer 1: lane (k = g, column r) supplies u, v, 1, 0 and receives units 16 t + 4 g + i of point r
 #pragma unroll
-      for (int s = 0; s < 2; ++s)
+      for (int p = 0; p < 2; ++p) {
+        const float in = g < 2 ? rec[(q0 + 16 * p + r) * kSurRec + g] : (g == 2 ? 1.0f : 0.0f);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int j = kunit(32 * s + 8 * g + i);
-          unsigned short hb, lb;
-          split_bits(tanh_scaled(fmaf(sw1[2 * j], u, fmaf(sw1[2 * j + 1], v, sb1[j]))), hb, lb);
-          bh[s][i] = __builtin_bit_cast(__bf16, hb);
-          bl[s][i] = __builtin_bit_cast(__bf16, lb);
-        }
-      // layers 2 and 3: lane (r, g) receives units 16 t + 4 g + i of point q0 + r
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            const f32x4 z = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[2 * s + t], in, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            act4(z, bh[p][s], bl[p][s], 4 * t, m0, m1);
+          }
+      }
+      // layers 2 and 3: each weight fragment read once for both columns
 #pragma unroll
       for (int layer = 0; layer < 2; ++layer) {
         const float* bias = layer == 0 ? sb2 : sb3;
         const unsigned short* wh = layer == 0 ? sw2h : sw3h;
         const unsigned short* wl = layer == 0 ? sw2l : sw3l;
-        float h[4][4];
+        bf16x8 nh[2][2], nl[2][2];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+          const f32x4 bv = *reinterpret_cast<const f32x4*>(bias + 16 * t + 4 * g);
+          f32x4 acc[2] = {bv, bv};
 #pragma unroll
           for (int s = 0; s < 2; ++s) {
-            const bf16x8 ah = frag(wh, 16 * t + r, 32 * s + 8 * g);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[s], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[s], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(wl, 16 * t + r, 32 * s + 8 * g), bh[s], acc, 0, 0, 0);
+            const bf16x8 ah = frag(wh, 16 * t + r, 32 * s + 8 * g), al = frag(wl, 16 * t + r, 32 * s + 8 * g);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) acc[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[p][s], acc[p], 0, 0, 0);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) acc[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[p][s], acc[p], 0, 0, 0);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) acc[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[p][s], acc[p], 0, 0, 0);
           }
 #pragma unroll
-          for (int i = 0; i < 4; ++i) h[t][i] = tanh_scaled(fmaf(acc[i], kTwoLog2e, bias[16 * t + 4 * g + i]));
+          for (int p = 0; p < 2; ++p) act4(acc[p], nh[p][t >> 1], nl[p][t >> 1], 4 * (t & 1), m0, m1);
         }
-        // the next layer's B operand: k' = 32 s + 8 g + i is unit 16 (2 s + i / 4) + 4 g + i % 4
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int p = 0; p < 2; ++p)
 #pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            unsigned short hb, lb;
-            split_bits(h[2 * s + (i >> 2)][i & 3], hb, lb);
-            bh[s][i] = __builtin_bit_cast(__bf16, hb);
-            bl[s][i] = __builtin_bit_cast(__bf16, lb);
+          for (int s = 0; s < 2; ++s) {
+            bh[p][s] = nh[p][s];
+            bl[p][s] = nl[p][s];
           }
       }
-      // layer 4: lane (r, g) gets y[output 4 g + i][point q0 + r]; times the envelope into the output tile
-      f32x4 y = {0.f, 0.f, 0.f, 0.f};
+      // layer 4: lane (r, g) gets y[output 4 g + i][point]; times the envelope into the output tile
+      const f32x4 b4 = *reinterpret_cast<const f32x4*>(sb4 + 4 * g);
+      f32x4 y[2] = {b4, b4};
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
-        const bf16x8 ah = frag(sw4h, r, 32 * s + 8 * g);
-        y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[s], y, 0, 0, 0);
-        y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[s], y, 0, 0, 0);
-        y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(sw4l, r, 32 * s + 8 * g), bh[s], y, 0, 0, 0);
-      }
-      {
-        const float* pq = rec + (q0 + r) * kSurRec;
-        const int ei = __float_as_int(pq[6]);
-        float yo[4];
+        const bf16x8 ah = frag(sw4h, r, 32 * s + 8 * g), al = frag(sw4l, r, 32 * s + 8 * g);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int c = 4 * g + i;
-          yo[i] = (y[i] + sb4[c]) * env_at(senv, senvd, ei, pq[2], pq[3], pq[4], pq[5], c);
+        for (int p = 0; p < 2; ++p) {
+          y[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh[p][s], y[p], 0, 0, 0);
+          y[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl[p][s], y[p], 0, 0, 0);
+          y[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[p][s], y[p], 0, 0, 0);
         }
-        *reinterpret_cast<float4*>(so + r * kO + 4 * g) = make_float4(yo[0], yo[1], yo[2], yo[3]);
+      }
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const float* pq = rec + (q0 + 16 * p + r) * kSurRec;
+        const f32x4 hw = {pq[2], pq[3], pq[4], pq[5]};
+        *reinterpret_cast<f32x4*>(so + (16 * p + r) * kO + 4 * g) =
+            y[p] * env_at4(senv, senvd, __float_as_int(pq[6]), hw, 4 * g);
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      // requested columns of the network's points, point-major
-      const int nq = min(16, np - q0);
-      // lane (point l / 16 + 4 k, requested flavour j0 + l % 16), flavours in chunks of 16: no division
-      for (int j0 = 0; j0 < R; j0 += 16) {
-        const int j = j0 + (l & 15);
-        const int c = j < R ? scol[j] : -1;
-        for (int pt = l >> 4; pt < nq; pt += 4)
-          if (j < R && rec[(q0 + pt) * kSurRec + 7] == 0.0f)
-            out[(p0 + q0 + pt) * R + j] = c >= 0 ? so[pt * kO + c] : 0.0f;
+      // requested columns, point-major: consecutive lanes on consecutive values (a fallback point's are
+      // written over below, by this wave)
+      const int ne = min(kSurPts, np - q0) * R;
+      float* o = out + (p0 + q0) * R;
+      for (int e = l; e < ne; e += 64) {
+        const int w = swalk[e];
+        o[e] = w != 0xffff ? so[w] : 0.0f;
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
@@ -999,7 +1055,7 @@ hipError_t sur_infer(const SurDev& S, const MemberDev& m, const ReqCols& rc, con
   if (blocks > 0) {
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&k_sur_infer), shm);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sur_infer, dim3((unsigned)blocks), dim3(64 * waves), shm, s, S, m, rc, b.Pb, b.P, x, q2, n,
+    hipLaunchKernelGGL(k_sur_infer, dim3((unsigned)blocks), dim3(64 * waves), shm, s, S, m, rc, b.P, x, q2, n,
                        out, invL01, nerr);
   }
   return hipGetLastError();
