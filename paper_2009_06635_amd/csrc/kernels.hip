@@ -181,7 +181,7 @@ __device__ __forceinline__ void stage_rows(T* dst, const T* src, int rows, int P
 }
 
 // x*f for a set of flavours; see file header.  out is point-major [n][R].
-// Each wave works on its own 64-point tiles with no workgroup barrier after
+// Each wave works on its own tiles of 64 points (fewer in small calls) with no workgroup barrier after
 // the initial staging, so the knot searches and log transforms of some waves
 // overlap the stencil gathers of others.  In-grid entries run a branch-free
 // gather + FMA loop; the rare extrapolated points of a tile are finished
@@ -372,7 +372,7 @@ template <typename T, bool kLdsGrid, int G, int BS, bool kLdsTables, bool kAlpha
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(kAlphas ? 4 : PDFMI_WAVES_PER_EU)))
 void k_xfxq2(MemberDev m, ReqCols rc, const double* __restrict__ X, const double* __restrict__ Q2, int64_t n,
              T* __restrict__ out, unsigned long long* __restrict__ nerr, int lds_grid_elems, double invL01,
-             AlphasDev A, double* __restrict__ aout) {
+             AlphasDev A, double* __restrict__ aout, int tile_pts) {
   static_assert(kLdsTables || !kLdsGrid, "a staged grid needs staged tables");
   constexpr int kWaves = BS / kWave;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -397,19 +397,20 @@ void k_xfxq2(MemberDev m, ReqCols rc, const double* __restrict__ X, const double
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   unsigned char* rec = srec + wv * wave_record_bytes<T>();
   const int R = rc.n;
-  const int64_t ntiles = (n + kWave - 1) / kWave;
+  const int pts = kLdsTables ? kWave : tile_pts;  // points of a tile, at most kWave
+  const int64_t ntiles = (n + pts - 1) / pts;
   const int64_t stride = (int64_t)gridDim.x * kWaves;
   int64_t tile = (int64_t)blockIdx.x * kWaves + wv;
   // the next tile's (x, Q^2) are loaded before the current tile is processed
   double xc = 0.0, qc = 0.0;
-  if (tile < ntiles && tile * kWave + lane < n) {
-    xc = X[tile * kWave + lane];
-    qc = Q2[tile * kWave + lane];
+  if (tile < ntiles && tile * pts + lane < n) {
+    xc = X[tile * pts + lane];
+    qc = Q2[tile * pts + lane];
   }
   for (; tile < ntiles; tile += stride) {
-    const int64_t pbeg = tile * kWave;
-    const int tp = (int)min((int64_t)kWave, n - pbeg);
-    const int64_t nxt = pbeg + stride * kWave + lane;
+    const int64_t pbeg = tile * pts;
+    const int tp = (int)min((int64_t)pts, n - pbeg);
+    const int64_t nxt = pbeg + stride * pts + lane;
     double xn = 0.0, qn = 0.0;
     if (nxt < n) {
       xn = X[nxt];
@@ -506,11 +507,20 @@ static size_t shared_bytes(const MemberDev& m, bool f32, int bs, bool tables) {
          (bs / kWave) * (f32 ? wave_record_bytes<float>() : wave_record_bytes<double>());
 }
 constexpr int kBlockGlobal = 256;   // tables and grid read from global memory
-// Below this many points each workgroup sees only a few tiles, and staging the
-// whole location table (tens of KB) costs more than reading the few entries
-// each point needs from global memory: the tables are then read in place
-// (measured: 1e3 and 1e4 points 15-20 % faster; at 1e5 points staging wins).
-constexpr int64_t kStageTablesMinPoints = 32768;
+// Small calls read the tables in place (staging tens of KB costs a workgroup
+// more than the few entries its points need) and are bound by latency: the
+// kernel arguments, the table reads of the location and then one gather round
+// after another.  Their tiles are halved until the call has kSmallWaves waves
+// per compute unit, down to the 8 points whose column groups fill about one
+// round.  A call that has that many full tiles stages the tables.  Measured on
+// 256 compute units, FP64, 11 and 13 columns (64-point tiles, staged from
+// 32768 points on, then this rule): 10^3 points 8.2 -> 5.7 and 11.7 -> 7.9 us,
+// 10^4 8.5 -> 5.8 and 15.4 -> 9.1, 65000 11.1 -> 8.7 and 20.0 -> 13.9; at 10^5
+// staged full tiles take 11.2 and 19.2, in place 11.7 and 19.2, staged tiles
+// of 32 points 11.7 and 19.0.  8 or 16 waves per compute unit: 32000 points
+// 7.5 against 6.9 us.
+constexpr int kSmallWaves = 4;
+constexpr int kMinTilePts = 8;
 constexpr int kBlockTables = 512;   // tables staged in LDS, grid read from global memory
 constexpr int kBlockLds = 1024;     // tables and grid staged once per workgroup in LDS
 size_t xfxq2_shared_bytes(const MemberDev& m, bool f32) {
@@ -527,13 +537,13 @@ struct AsOut {
 template <typename T, int G, int BS, bool kLdsGrid, bool kLdsTables, bool kAlphas>
 static hipError_t launch_one(const MemberDev& m, const ReqCols& rc, const double* x, const double* q2, int64_t n,
                              T* out, unsigned long long* nerr, int lds_grid_elems, double invL01, int64_t nb,
-                             size_t shm, const AsOut& ao, hipStream_t s) {
+                             size_t shm, const AsOut& ao, hipStream_t s, int tile_pts = kWave) {
   const void* fn = reinterpret_cast<const void*>(&k_xfxq2<T, kLdsGrid, G, BS, kLdsTables, kAlphas>);
   hipError_t e = allow_dynamic_lds(fn, shm);
   if (e != hipSuccess) return e;
   const AlphasDev A = ao.A ? *ao.A : AlphasDev{};
   hipLaunchKernelGGL((k_xfxq2<T, kLdsGrid, G, BS, kLdsTables, kAlphas>), dim3((unsigned)nb), dim3(BS), shm, s, m, rc, x, q2,
-                     n, out, nerr, lds_grid_elems, invL01, A, ao.aout);
+                     n, out, nerr, lds_grid_elems, invL01, A, ao.aout, tile_pts);
   return hipGetLastError();
 }
 
@@ -552,7 +562,8 @@ static hipError_t launch_xfxq2_g(const MemberDev& m, const ReqCols& rc, const do
     return launch_one<T, G, kBlockLds, true, true, kAlphas>(m, rc, x, q2, n, out, nerr, lds_grid_elems, invL01, nb, shm, ao,
                                                    s);
   }
-  if (tables_fit(m) && n >= kStageTablesMinPoints) {
+  const int64_t full = (int64_t)n_cu * kSmallWaves * kWave;  // points that give every small wave a full tile
+  if (tables_fit(m) && n >= full) {
     const size_t shm = shared_bytes(m, f32, kBlockTables, true) + as_bytes;
     // two workgroups are resident per compute unit; more than that are
     // launched only while every wave still has about three tiles of its own,
@@ -567,9 +578,13 @@ static hipError_t launch_xfxq2_g(const MemberDev& m, const ReqCols& rc, const do
     return launch_one<T, G, kBlockTables, false, true, kAlphas>(m, rc, x, q2, n, out, nerr, 0, invL01, nb, shm, ao, s);
   }
   const size_t shm = shared_bytes(m, f32, kBlockGlobal, false) + alphas_lds_bytes(ao.A, false);
-  const int64_t ntiles = (n + kBlockGlobal - 1) / kBlockGlobal;
+  int tile_pts = kWave;
+  for (int64_t f = full; tile_pts > kMinTilePts && n < f; f /= 2) tile_pts /= 2;
+  const int block_pts = kBlockGlobal / kWave * tile_pts;
+  const int64_t ntiles = (n + block_pts - 1) / block_pts;
   const int64_t nb = min(ntiles, (int64_t)n_cu * cfg.blocks_per_cu);
-  return launch_one<T, G, kBlockGlobal, false, false, kAlphas>(m, rc, x, q2, n, out, nerr, 0, invL01, nb, shm, ao, s);
+  return launch_one<T, G, kBlockGlobal, false, false, kAlphas>(m, rc, x, q2, n, out, nerr, 0, invL01, nb, shm, ao, s,
+                                                               tile_pts);
 }
 
 // The vectorised kernel serves requests for every stored column in load order.
