@@ -8,6 +8,8 @@
 
 #include "pdfmi_dev.h"
 
+#define PDFMI_GLOBAL __attribute__((address_space(1)))  // a pointer read from memory is global, not generic
+
 namespace pdfmi {
 
 // Point-location tables as a kernel reads them: from LDS (staged copy of the
@@ -250,44 +252,6 @@ __device__ __forceinline__ PointLoc locate_x(const MemberDev& m, const Tables& t
   return L;
 }
 
-// a^b for a > 0 as exp(b ln a): the bases here are positive ratios, and a
-// few ulps of exp and log stay far inside the FP64 parity bound, at a
-// fraction of the general pow's cost (the extrapolated points of a tile run
-// these formulas on a few of the wave's lanes).
-__device__ __forceinline__ double pos_pow(double a, double b) { return exp(b * log(a)); }
-// Two-anchor continuation (log-linear when both anchors exceed 1e-3).
-__device__ __forceinline__ double cont_low(double f0, double f1, double s) {
-  return (f0 > 1e-3 && f1 > 1e-3) ? f0 * pos_pow(f1 / f0, s) : f0 + s * (f1 - f0);
-}
-__device__ __forceinline__ double cont_high(double f0, double f1, double s) {
-  return (f0 > 1e-3 && f1 > 1e-3) ? f1 * pos_pow(f1 / f0, s) : f1 + s * (f1 - f0);
-}
-// Below Q^2_min: f0 * r^(gamma r + 1 - r), gamma from the first two Q^2 knots.
-__device__ __forceinline__ double low_q(double f0, double f1, double r, double invL01, bool xhigh) {
-  const bool use_gamma = f0 > 1e-5 && f1 > 1e-5 && !xhigh;
-  if (!use_gamma) return f0 * r;
-  const double lr = log(r);
-  const double gamma = log(f1 / f0) * invL01;
-  return f0 * exp((gamma * r + 1.0 - r) * lr);
-}
-
-// Extrapolated value from anchor values (rare path, FP64 combination):
-//   x below x_min only:      a0, a1 = rows x_0, x_1 interpolated in Q^2
-//   Q^2 outside, x inside:   a0, a1 = anchor Q^2 rows interpolated in x
-//   corners:                 a0, a1 (x_0, x_1 on the lower anchor row),
-//                            a2, a3 (x_0, x_1 on the upper anchor row)
-static __device__ __noinline__ double extrapolate(int mode, double a0, double a1, double a2, double a3, double p0,
-                                           double p1, double invL01) {
-  const bool lowx = mode & kLowX, lowq = mode & kLowQ, highq = mode & kHighQ;
-  const bool xhigh = mode & kXHigh;
-  if (lowx && !(lowq || highq)) return cont_low(a0, a1, p0);
-  if (!lowx) return lowq ? low_q(a0, a1, p0, invL01, xhigh) : cont_high(a0, a1, p0);
-  // corners: continue in x on the two anchor rows first, then in Q^2
-  const double g0 = cont_low(a0, a1, p1);
-  const double g1 = cont_low(a2, a3, p1);
-  return lowq ? low_q(g0, g1, p0, invL01, xhigh) : cont_high(g0, g1, p0);
-}
-
 template <typename T>
 __device__ __forceinline__ const T* member_values(const MemberDev& m);
 template <>
@@ -318,49 +282,73 @@ __device__ __forceinline__ T interp_stencil(const T F[4][4], const T w[4], const
   return acc;
 }
 
-// Extrapolated value of one column (rare path).  f points at the column's
-// entry of the stencil's first row; s1, sa, s3 are the steps between its x
-// knots and Pp the stride between Q^2 knots (elements).  Only the anchor knots
-// the formula needs are read:
-//   x below x_min only:     rows x_0, x_1 interpolated in Q^2
-//   Q^2 outside, x inside:  the two anchor Q^2 rows interpolated in x
-//   corners:                the four anchor knot values
-// (below x_min the cell is the first one: x_0 and x_1 are the stencil's
-// second and third x knot)
-struct Wts {
-  double w0, w1, w2, w3, v0, v1, v2, v3;
-};
+// Two-anchor continuation from f0 by the parameter s (log-linear when both
+// anchors exceed 1e-3); `from` is the anchor the parameter counts from.
+// Powers are exp(b ln a): the bases are positive ratios, and a few ulps of
+// exp and log stay far inside the FP64 parity bound.
+__device__ __forceinline__ double continued(double from, double f0, double f1, double s, const LogEntry* lt) {
+  return (f0 > 1e-3 && f1 > 1e-3) ? from * exp(s * fast_log(f1 / f0, lt)) : from + s * (f1 - f0);
+}
 
-template <typename T>
-static __device__ __noinline__ double extrap_entry(const T* f, int s1, int sa, int s3, int Pp, int mode, Wts wt, double p0,
-                                            double p1, double invL01) {
-  const double w[4] = {wt.w0, wt.w1, wt.w2, wt.w3};
-  const double v[4] = {wt.v0, wt.v1, wt.v2, wt.v3};
-  const T* fx[4] = {f, f + s1, f + s1 + sa, f + s1 + sa + s3};
+// Extrapolated value of one column (rare path, FP64 combination).  f points at
+// the column's entry of the stencil's first row; s1, sa, s3 are the steps
+// between its x knots and Pp the stride between Q^2 knots (elements).  Only the
+// anchor knots the formula needs are read:
+//   x below x_min only:     a0, a1 = rows x_0, x_1 interpolated in Q^2
+//   Q^2 outside, x inside:  a0, a1 = the two anchor Q^2 rows interpolated in x
+//   corners:                x_0, x_1 on the lower and on the upper anchor row,
+//                           continued in x to a0 and a1
+// (below x_min the cell is the first one: x_0 and x_1 are the stencil's
+// second and third x knot).  Then from a0, a1: the two-anchor continuation, or
+// below Q^2_min f0 r^(gamma r + 1 - r) with gamma from the first two Q^2 knots.
+// Lanes of one wave hold points of different regions: the regions share one
+// gather of four anchor pairs, one division, one exponential and at most two
+// logarithms instead of a branch each.
+// A call (its arguments in registers): inlined, it would cost the callers'
+// common path registers.  kGlobal: f is in global memory.
+template <typename T, bool kGlobal>
+static __device__ __noinline__ double extrap_entry(const T* fp, int s1, int sa, int s3, int Pp, int mode, T w0, T w1, T w2,
+                                                   T w3, T v0, T v1, T v2, T v3, double p0, double p1, double invL01,
+                                                   const LogEntry* lt) {
+  using Ptr = std::conditional_t<kGlobal, const PDFMI_GLOBAL T*, const T*>;
+  const Ptr f = (Ptr)fp;
   const bool lowx = mode & kLowX, lowq = mode & kLowQ, highq = mode & kHighQ;
-  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-  if (lowx && !(lowq || highq)) {
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      a0 += v[b] * (double)fx[1][b * Pp];
-      a1 += v[b] * (double)fx[2][b * Pp];
-    }
-  } else {
-    const int ra = lowq ? 0 : (mode >> 8) & 3;
-    if (!lowx) {
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        a0 += w[a] * (double)fx[a][ra * Pp];
-        a1 += w[a] * (double)fx[a][(ra + 1) * Pp];
-      }
-    } else {
-      a0 = (double)fx[1][ra * Pp];
-      a1 = (double)fx[2][ra * Pp];
-      a2 = (double)fx[1][(ra + 1) * Pp];
-      a3 = (double)fx[2][(ra + 1) * Pp];
-    }
+  const bool xonly = lowx && !(lowq || highq), corner = lowx && !xonly;
+  const int r0 = lowq ? 0 : ((mode >> 8) & 3) * Pp;  // lower anchor row
+  // terms of a0 (offset, weight); a1 has the same at `step`
+  const int o0 = xonly ? s1 : (corner ? s1 + r0 : r0);
+  const int o1 = xonly ? s1 + Pp : (corner ? o0 : r0 + s1);
+  const int o2 = xonly ? s1 + 2 * Pp : (corner ? o0 : r0 + s1 + sa);
+  const int o3 = xonly ? s1 + 3 * Pp : (corner ? o0 : r0 + s1 + sa + s3);
+  const int step = lowx ? sa : Pp;
+  const double c0 = (double)(xonly ? v0 : w0), c1 = (double)(xonly ? v1 : w1);
+  const double c2 = (double)(xonly ? v2 : w2), c3 = (double)(xonly ? v3 : w3);
+  const double f00 = (double)f[o0], f10 = (double)f[o0 + step];
+  double a0 = c0 * f00, a1 = c0 * f10;
+  a0 = fma(c1, (double)f[o1], a0);
+  a1 = fma(c1, (double)f[o1 + step], a1);
+  a0 = fma(c2, (double)f[o2], a0);
+  a1 = fma(c2, (double)f[o2 + step], a1);
+  a0 = fma(c3, (double)f[o3], a0);
+  a1 = fma(c3, (double)f[o3 + step], a1);
+  if (corner) {
+    a0 = continued(f00, f00, f10, p1, lt);
+    const double f01 = (double)f[o0 + Pp], f11 = (double)f[o0 + Pp + step];
+    a1 = continued(f01, f01, f11, p1, lt);
   }
-  return extrapolate(mode, a0, a1, a2, a3, p0, p1, invL01);
+  const double from = highq ? a1 : a0;
+  const double least = lowq ? 1e-5 : 1e-3;
+  double val = lowq ? a0 * p0 : from + p0 * (a1 - a0);
+  if (a0 > least && a1 > least && !(lowq && (mode & kXHigh))) {
+    const double lr = fast_log(a1 / a0, lt);
+    double e = p0 * lr;
+    if (lowq) {
+      const double gamma = lr * invL01;
+      e = (gamma * p0 + 1.0 - p0) * fast_log(p0, lt);
+    }
+    val = from * exp(e);
+  }
+  return val;
 }
 
 // Per-point record of a located point, written by one lane and read by
@@ -377,6 +365,15 @@ struct PointRec {
 };
 constexpr int kRecSlow = 1, kRecInvalid = 2;
 
+// A point outside the grid, kept until enough of them fill a wave.
+template <typename T>
+struct SlowRec {
+  PointRec<T> r;
+  double p0, p1;  // extrapolation parameters
+  int mode, pad;
+  T* out;         // the point's output row
+};
+
 template <typename T>
 __device__ __forceinline__ void set_stencil(PointRec<T>& r, const QLoc<T>& Q, const PointLoc& L, int rowb) {
   r.o = (int)__umul24((unsigned)L.row, (unsigned)rowb);
@@ -388,14 +385,13 @@ __device__ __forceinline__ void set_stencil(PointRec<T>& r, const QLoc<T>& Q, co
 
 // One column of a point outside the grid (kRecSlow) with its mode and
 // extrapolation parameters; col0 points at the column's entry of grid row 0.
-template <typename T>
+template <typename T, bool kGlobal>
 __device__ __forceinline__ T rec_extrapolate(const PointRec<T>& r, int mode, double p0, double p1, const T* col0,
-                                             int Pp, double invL01) {
+                                             int Pp, double invL01, const LogEntry* lt) {
   const int es = (int)sizeof(T);
-  const Wts wt{(double)r.w[0], (double)r.w[1], (double)r.w[2], (double)r.w[3],
-               (double)r.v[0], (double)r.v[1], (double)r.v[2], (double)r.v[3]};
   const T* f = reinterpret_cast<const T*>(reinterpret_cast<const unsigned char*>(col0) + (r.o & ~3));
-  return (T)extrap_entry<T>(f, r.s1 / es, r.sa / es, r.s3 / es, Pp, mode, wt, p0, p1, invL01);
+  return (T)extrap_entry<T, kGlobal>(f, r.s1 / es, r.sa / es, r.s3 / es, Pp, mode, r.w[0], r.w[1], r.w[2], r.w[3], r.v[0],
+                                     r.v[1], r.v[2], r.v[3], p0, p1, invL01, lt);
 }
 
 }  // namespace pdfmi

@@ -104,7 +104,6 @@ __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t r, int voff, co
 // aligned) from global memory to LDS.  Each thread issues eight 16-byte loads
 // before it stores them: a loop of dependent load-store pairs waits out the
 // memory latency once per element (a 72 KB grid: 18 round trips per thread).
-#define PDFMI_GLOBAL __attribute__((address_space(1)))  // a pointer read from memory is global, not generic
 template <int BS>
 __device__ __forceinline__ void stage_copy(void* dst, const void* src, int64_t bytes) {
   const PDFMI_GLOBAL u32x4* s = (const PDFMI_GLOBAL u32x4*)src;
@@ -184,20 +183,49 @@ __device__ __forceinline__ void stage_rows(T* dst, const T* src, int rows, int P
 // Each wave works on its own tiles of 64 points (fewer in small calls) with no workgroup barrier after
 // the initial staging, so the knot searches and log transforms of some waves
 // overlap the stencil gathers of others.  In-grid entries run a branch-free
-// gather + FMA loop; the rare extrapolated points of a tile are finished
-// afterwards, one point at a time across the wave.
+// gather + FMA loop; the rare points outside the grid wait in the wave's list
+// until they fill a pass.
 constexpr int kWave = 64;
 
 __device__ constexpr AlphasDev kNoAlphas{};
 
 template <typename T>
 __host__ __device__ constexpr size_t wave_record_bytes() {
-  return (size_t)kWave * (sizeof(PointRec<T>) + 16 + 4);
+  return (size_t)kWave * (sizeof(PointRec<T>) + 16 + 4);  // located points, then the points outside the grid
+}
+// Points outside the grid that a wave holds: 11 in FP64, 16 in FP32.
+template <typename T>
+constexpr int kSlowSlots = (int)(kWave * 20 / sizeof(SlowRec<T>));
+
+// The outputs of the wave's ns points outside the grid, one lane per (point,
+// requested column).  One point at a time across the wave left 64 - R lanes
+// idle and paid each region's branch and a call with its weights in scratch
+// memory: 1 % of the points outside cost 10^7 points of 13 columns 67 us (FP64
+// with alpha_s, 711 -> 778) and 10 % 606; with the list 32 and 167.  col0:
+// column 0 of grid row 0; colmap: stored column of each requested flavour, -1
+// if absent (kCompact: rows in request order).
+template <typename T, bool kGlobal, bool kCompact = false>
+__device__ __forceinline__ void finish_slow(const SlowRec<T>* q, int ns, int R, const int* colmap, const T* col0,
+                                            int Pp, double invL01, const LogEntry* lt, int lane) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  for (int e = lane; e < ns * R; e += kWave) {
+    const int k = e / R, j = e - k * R;
+    const int c = colmap[j];
+    T val = (T)0;
+    if (c >= 0) val = rec_extrapolate<T, kGlobal>(q[k].r, q[k].mode, q[k].p0, q[k].p1, col0 + (kCompact ? j : c), Pp, invL01, lt);
+    ((PDFMI_GLOBAL T*)q[k].out)[j] = val;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // One wave's 64-point tile [pbeg, pbeg + tp): phase 1 (one lane per point,
 // (xv, qv) = this lane's point) into the wave's LDS record, then the in-grid
-// outputs, then the extrapolated points.  obase = output row of point pbeg.
+// outputs, then the waiting points outside the grid (nslow of them before and
+// after) if no further one has room in a pass.  obase = output row of point pbeg.
 //
 // Phase 2 walks the tile's outputs with consecutive lanes on consecutive
 // output addresses: one lane per (point, flavour) for a flavour subset
@@ -216,10 +244,10 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
                                           const T* sgrid, const T* __restrict__ gvals, uint32_t gbytes,
                                           double xv, double qv, int tp, T* __restrict__ obase,
                                           unsigned long long* __restrict__ nerr, double invL01,
-                                          unsigned char* rec, int lane, const AlphasDev& A, const AsView& av) {
-  PointRec<T>* srec = reinterpret_cast<PointRec<T>*>(rec);        // [64]
-  double* sp = reinterpret_cast<double*>(srec + kWave);           // [64][2] extrapolation parameters
-  int* smode = reinterpret_cast<int*>(sp + 2 * kWave);            // [64] modes of the points outside the grid
+                                          unsigned char* rec, int& nslow, int lane, const AlphasDev& A,
+                                          const AsView& av) {
+  PointRec<T>* srec = reinterpret_cast<PointRec<T>*>(rec);            // [64]
+  SlowRec<T>* sslow = reinterpret_cast<SlowRec<T>*>(srec + kWave);    // [kSlowSlots] points outside the grid
   const int Pp = kCompact ? kRowB / (int)sizeof(T) : (sizeof(T) == 8 ? m.P64 : m.P32);
   // bytes between consecutive Q^2 knots; a compile-time kRowB (the caller has
   // checked it) lets the four Q^2 rows of an LDS gather use immediate offsets
@@ -236,23 +264,40 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
     if (qb && lane == 0) atomicAdd(nerr, (unsigned long long)__popcll(qb));
   }
   bool bad = false, slow = false;
+  PointRec<T> r;
+  PointLoc L;
   if (lane < tp) {
-    PointRec<T> r;
     const QLoc<T> Q = locate_q<T>(m, tb, qv);
-    const PointLoc L = locate_x<T>(m, tb, Q, xv, qv, r.w, r.v);
+    L = locate_x<T>(m, tb, Q, xv, qv, r.w, r.v);
     bad = L.mode & kInvalid;
     slow = L.mode & kSlow;
     set_stencil(r, Q, L, rowb);
-    if (slow) {
-      sp[2 * lane] = L.p0;
-      sp[2 * lane + 1] = L.p1;
-      smode[lane] = L.mode;
-    }
     srec[lane] = r;
   }
   const unsigned long long bal = __ballot(bad);
   if (bal && lane == 0) atomicAdd(nerr, (unsigned long long)__popcll(bal));
+  // points outside the grid: into the wave's list, which is worked off after the tile's other outputs when
+  // it has as many as one pass over the wave takes, and at the wave's end
   unsigned long long slow_mask = __ballot(slow);
+  while (slow_mask) {
+    if (nslow == kSlowSlots<T>) {
+      finish_slow<T, !kLdsGrid, kCompact>(sslow, nslow, R, scol, kLdsGrid ? sgrid : gvals, Pp, invL01, tb.logt, lane);
+      nslow = 0;
+    }
+    const int rank = __popcll(slow_mask & ((1ull << lane) - 1));
+    const int take = min(kSlowSlots<T> - nslow, (int)__popcll(slow_mask));
+    const bool mine = (slow_mask >> lane & 1) && rank < take;
+    if (mine) {
+      SlowRec<T>& d = sslow[nslow + rank];
+      d.r = r;
+      d.p0 = L.p0;
+      d.p1 = L.p1;
+      d.mode = L.mode;
+      d.out = obase + lane * R;
+    }
+    slow_mask &= ~__ballot(mine);
+    nslow += take;
+  }
   // records written by this wave are read back by other lanes of the same wave
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -336,19 +381,9 @@ __device__ __forceinline__ void wave_tile(const MemberDev& m, const Tables& tb, 
       ++p;
     }
   }
-  // extrapolated points of the tile, one at a time across the wave
-  while (slow_mask) {
-    const int q = __builtin_ctzll(slow_mask);
-    slow_mask &= slow_mask - 1;
-    const PointRec<T>& rq = srec[q];
-    for (int jj = lane; jj < R; jj += kWave) {
-      const int col = kCompact || G > 1 ? (scol[jj] < 0 ? -1 : jj) : scol[jj];
-      T val = (T)0;
-      if (col >= 0) {
-        val = rec_extrapolate(rq, smode[q], sp[2 * q], sp[2 * q + 1], (kLdsGrid ? sgrid : gvals) + col, Pp, invL01);
-      }
-      obase[q * R + jj] = val;
-    }
+  if (nslow * R > kWave - R) {  // no room for another point in one pass
+    finish_slow<T, !kLdsGrid, kCompact>(sslow, nslow, R, scol, kLdsGrid ? sgrid : gvals, Pp, invL01, tb.logt, lane);
+    nslow = 0;
   }
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -403,6 +438,7 @@ void k_xfxq2(MemberDev m, ReqCols rc, const double* __restrict__ X, const double
   int64_t tile = (int64_t)blockIdx.x * kWaves + wv;
   // the next tile's (x, Q^2) are loaded before the current tile is processed
   double xc = 0.0, qc = 0.0;
+  int nslow = 0;  // points outside the grid that wait (uniform over the wave)
   if (tile < ntiles && tile * pts + lane < n) {
     xc = X[tile * pts + lane];
     qc = Q2[tile * pts + lane];
@@ -418,10 +454,13 @@ void k_xfxq2(MemberDev m, ReqCols rc, const double* __restrict__ X, const double
     }
     if constexpr (kAlphas) av.out = aout + pbeg;
     wave_tile<T, kLdsGrid, G, kAlphas>(m, tb, scol, R, sgrid, gvals, gbytes, xc, qc, tp, out + pbeg * R, nerr, invL01, rec,
-                              lane, A, av);
+                                       nslow, lane, A, av);
     xc = xn;
     qc = qn;
   }
+  if (nslow > 0)
+    finish_slow<T, !kLdsGrid>(reinterpret_cast<const SlowRec<T>*>(rec + kWave * sizeof(PointRec<T>)), nslow, R, scol,
+                            kLdsGrid ? sgrid : gvals, sizeof(T) == 8 ? m.P64 : m.P32, invL01, tb.logt, lane);
 }
 
 // Location only (sub-grid, cells, region), one lane per point.
@@ -879,7 +918,7 @@ __device__ __forceinline__ McOrigin mc_origin(const PointLoc& L, int nqp, int P)
 // flavour's column of grid row 0; P is the row stride of the values read.
 template <typename T, bool kMaySlow>
 __device__ __forceinline__ T mc_value(const T* g, const PointLoc& L, const McOrigin& o, const T w[4], const T v[4],
-                                      int P, int col, double invL01) {
+                                      int P, int col, double invL01, const LogEntry* lt) {
   if (L.mode & kInvalid) return (T)NAN;
   if (col < 0) return (T)0;
   if (!kMaySlow || !(L.mode & (kLowX | kLowQ | kHighQ))) {
@@ -890,10 +929,8 @@ __device__ __forceinline__ T mc_value(const T* g, const PointLoc& L, const McOri
       for (int b = 0; b < 4; ++b) F[a][b] = g[o.x[a] + b * P];
     return interp_stencil<T>(F, w, v);
   }
-  const Wts wt{(double)w[0], (double)w[1], (double)w[2], (double)w[3],
-               (double)v[0], (double)v[1], (double)v[2], (double)v[3]};
-  return (T)extrap_entry<T>(g + o.x[0], o.x[1] - o.x[0], o.x[2] - o.x[1], o.x[3] - o.x[2], P, L.mode, wt, L.p0, L.p1,
-                            invL01);
+  return (T)extrap_entry<T, false>(g + o.x[0], o.x[1] - o.x[0], o.x[2] - o.x[1], o.x[3] - o.x[2], P, L.mode, w[0], w[1],
+                                   w[2], w[3], v[0], v[1], v[2], v[3], L.p0, L.p1, invL01, lt);
 }
 
 template <typename T, bool kLdsGrid, int kGW, bool kLdsTables = true>
@@ -1043,8 +1080,8 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
       } else if (!((L1.mode | L2.mode) & (kLowX | kLowQ | kHighQ))) {
         for (int j = 0; j < R; ++j) {
           const int col = scol[j];
-          const T f1 = mc_value<T, false>(grid + col, L1, o1, w1, v, P, col, invL01);
-          const T f2 = mc_value<T, false>(grid + col, L2, o2, w2, v, P, col, invL01);
+          const T f1 = mc_value<T, false>(grid + col, L1, o1, w1, v, P, col, invL01, tb.logt);
+          const T f2 = mc_value<T, false>(grid + col, L2, o2, w2, v, P, col, invL01, tb.logt);
           lum = fma((double)f1, (double)f2, lum);
         }
       } else {
@@ -1052,8 +1089,8 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
         // extrapolation formulas
         for (int j = 0; j < R; ++j) {
           const int col = scol[j];
-          const T f1 = mc_value<T, true>(grid + col, L1, o1, w1, v, P, col, invL01);
-          const T f2 = mc_value<T, true>(grid + col, L2, o2, w2, v, P, col, invL01);
+          const T f1 = mc_value<T, true>(grid + col, L1, o1, w1, v, P, col, invL01, tb.logt);
+          const T f2 = mc_value<T, true>(grid + col, L2, o2, w2, v, P, col, invL01, tb.logt);
           lum = fma((double)f1, (double)f2, lum);
         }
       }
@@ -1261,6 +1298,7 @@ __global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const Batch
     const Tables tb = tables_at(kLdsTables ? stbl : m.tables, m);
     const double invL01 = invL01s[rq.member];
     T* out = reinterpret_cast<T*>(rq.out);
+    int nslow = 0;
     for (int w0 = wv * kWave; w0 < tl.count; w0 += kWaves * kWave) {
       const int64_t pbeg = tl.start + w0;
       const int tp = min(kWave, tl.count - w0);
@@ -1271,8 +1309,8 @@ __global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const Batch
         if (compact) {
           auto tile = [&](auto group) {
             wave_tile<T, true, decltype(group)::value, false, false, kCompactRowB, true>(
-                m, tb, scol, rq.R, sgrid, gvals, gbytes, xv, qv, tp, out + pbeg * rq.R, nerr, invL01, rec, lane,
-                kNoAlphas, AsView{});
+                m, tb, scol, rq.R, sgrid, gvals, gbytes, xv, qv, tp, out + pbeg * rq.R, nerr, invL01, rec, nslow,
+                lane, kNoAlphas, AsView{});
           };
           if (rq.R > 2)
             tile(std::integral_constant<int, 4>{});
@@ -1285,14 +1323,22 @@ __global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const Batch
       }
       if (vector_cols && rq.all_cols && rq.R >= G)
         wave_tile<T, kLdsGrid, G>(m, tb, scol, rq.R, sgrid, gvals, gbytes, xv, qv, tp, out + pbeg * rq.R, nerr,
-                                  invL01, rec, lane, kNoAlphas, AsView{});
+                                  invL01, rec, nslow, lane, kNoAlphas, AsView{});
       else if (kLdsGrid && sizeof(T) == 4 && m.P32 == 12)  // 9-12 stored flavours in FP32: 48-byte rows
         wave_tile<T, kLdsGrid, 1, false, !kLdsGrid, 48>(m, tb, scol, rq.R, sgrid, gvals, gbytes, xv, qv, tp,
-                                                        out + pbeg * rq.R, nerr, invL01, rec, lane, kNoAlphas,
+                                                        out + pbeg * rq.R, nerr, invL01, rec, nslow, lane, kNoAlphas,
                                                         AsView{});
       else
         wave_tile<T, kLdsGrid, 1>(m, tb, scol, rq.R, sgrid, gvals, gbytes, xv, qv, tp, out + pbeg * rq.R, nerr,
-                                  invL01, rec, lane, kNoAlphas, AsView{});
+                                  invL01, rec, nslow, lane, kNoAlphas, AsView{});
+    }
+    if (nslow > 0) {
+      const SlowRec<T>* q = reinterpret_cast<const SlowRec<T>*>(rec + kWave * sizeof(PointRec<T>));
+      const T* g0 = kLdsGrid ? sgrid : gvals;
+      if (compact)
+        finish_slow<T, !kLdsGrid, true>(q, nslow, rq.R, scol, g0, kCompactCols, invL01, tb.logt, lane);
+      else
+        finish_slow<T, !kLdsGrid>(q, nslow, rq.R, scol, g0, sizeof(T) == 8 ? m.P64 : m.P32, invL01, tb.logt, lane);
     }
   }
 }

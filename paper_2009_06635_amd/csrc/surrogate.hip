@@ -664,12 +664,13 @@ __device__ __forceinline__ void fb_set_mode(FbRec& f, int mode) {
   f.r.s1 |= mode & 15;  // region
   f.r.s3 |= (mode & kXHigh ? 1 : 0) | ((mode >> 8) & 3) << 1;
 }
-__device__ __forceinline__ float fb_extrapolate(const FbRec& f, const float* col0, int Pp, double invL01) {
+__device__ __forceinline__ float fb_extrapolate(const FbRec& f, const float* col0, int Pp, double invL01,
+                                                const LogEntry* lt) {
   const int mode = (f.r.s1 & 15) | (f.r.s3 & 1 ? kXHigh : 0) | ((f.r.s3 >> 1) & 3) << 8;
   PointRec<float> r = f.r;
   r.s1 &= ~15;
   r.s3 &= ~15;
-  return rec_extrapolate(r, mode, f.p0, f.p1, col0, Pp, invL01);
+  return rec_extrapolate<float, true>(r, mode, f.p0, f.p1, col0, Pp, invL01, lt);
 }
 
 // LDS of k_sur_infer: the lo and hi halves of W2, W3 (64 x 64) and W4
@@ -936,7 +937,7 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const float* __restrict__ Pf
             for (int b = 0; b < 4; ++b) F[a][b] = fx[a][b * m.P32];
           val = interp_stencil<float>(F, fr.r.w, fr.r.v);
         } else {
-          val = fb_extrapolate(fr, gvals + c, m.P32, invL01);
+          val = fb_extrapolate(fr, gvals + c, m.P32, invL01, gtb.logt);
         }
         out[fq[k] * R + j] = val;
       }
