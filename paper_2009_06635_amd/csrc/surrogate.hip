@@ -35,6 +35,7 @@ namespace pdfmi {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kH = 64;   // hidden width
@@ -620,7 +621,8 @@ __global__ void k_gather_samples(const float* __restrict__ in_all, const float* 
 // on the vector units, the halves split by unpacking and two library FP64
 // logarithms and a binary search per point; 1027 us with each weight fragment
 // read for 32 points, layer 1 on the matrix cores and the table lookups;
-// 924 us with the folded scale, the split by dot products and the output walk.
+// 924 us with the folded scale, the split by dot products and the output walk;
+// 895 us with 16-byte staging, all tables in flight together.
 //
 // LDS rows of 64 BF16 values (the weight halves) hold their eight 16-byte
 // chunks in the order chunk ^ (row & 7), so the 16 rows an operand read
@@ -629,6 +631,13 @@ __global__ void k_gather_samples(const float* __restrict__ in_all, const float* 
 // measured 936 us against 908).
 constexpr int kSurWaves = 16;
 constexpr int kSurPts = 32;  // points of a sub-tile: two MFMA columns of 16
+// Tiles go to the workgroups first and to their waves second, and calls of up
+// to this many 32-point tiles per compute unit take tiles of 32: a wave alone
+// needs about 3 us per 32 points, sixteen on one compute unit 24.  (16 tiles of
+// 64 points to each workgroup in turn: 1000 points on one compute unit, 32.3
+// us a call, now 12.2; 10^5 34.5 -> 22.5; 3 10^5 58 -> 38.5.  With 64-point
+// tiles 1000 points take 17 us; from 10^5 points on it makes no difference.)
+constexpr int kSurSmallWaves = 8;
 constexpr int kSurRec = 8;   // floats per point record: u, v, h00, h10 D, h01, h11 D, cell, (unused)
 
 __device__ __forceinline__ int swz(int row, int col) {  // element offset of (row, col) in a swizzled [.][64] tile
@@ -699,7 +708,7 @@ size_t sur_infer_shared_bytes(int nx, int waves) { return sur_head_bytes(nx) + (
 
 __global__ __launch_bounds__(64 * kSurWaves) __attribute__((amdgpu_waves_per_eu(4)))
 void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const float* __restrict__ Pf,
-                 const double* __restrict__ X, const double* __restrict__ Q2, int64_t n, float* __restrict__ out, double invL01, unsigned long long* __restrict__ nerr) {
+                 const double* __restrict__ X, const double* __restrict__ Q2, int64_t n, float* __restrict__ out, double invL01, unsigned long long* __restrict__ nerr, int tile_pts) {
   extern __shared__ __align__(16) unsigned char sraw[];
   const int BS = blockDim.x, nwav = BS >> 6;
   unsigned short* sw2l = reinterpret_cast<unsigned short*>(sraw);  // [kH][kH] swizzled (16-byte chunks)
@@ -725,30 +734,60 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const float* __restrict__ Pf
   static_assert(64 * sizeof(FbRec) <= 4096, "fallback records fit the wave area");
   float* rec = reinterpret_cast<float*>(waves + (size_t)nwav * kSurWaveArea) + wv * 64 * kSurRec;
 
-  for (int i = threadIdx.x; i < S.nx; i += BS) slxk[i] = S.lxk[i];
-  for (int i = threadIdx.x; i < S.nx * kO; i += BS) {
-    senv[i] = S.env[i];
-    senvd[i] = S.envd[i];
+  // staging, 16 bytes a load and the first of every table in flight together
+  // (four stored columns kp .. kp + 3 of row n hold W[n][kunit(kp)] and the
+  // three units after it)
+  const f32x4* e4 = reinterpret_cast<const f32x4*>(S.env);
+  const f32x4* d4 = reinterpret_cast<const f32x4*>(S.envd);
+  const int ne4 = S.nx * kO / 4;
+  auto unit4 = [&](int off, int i) {  // chunk i of the matrix at off, in stored order
+    return *reinterpret_cast<const f32x4*>(Pf + off + (i / (kH / 4)) * kH + kunit(4 * (i % (kH / 4))));
+  };
+  auto stage4 = [&](f32x4 w, unsigned short* hi, unsigned short* lo, int i) {
+    bf16x4 h, l4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      h[q] = (__bf16)w[q];
+      l4[q] = (__bf16)(w[q] - (float)h[q]);
+    }
+    const int o = swz(i / (kH / 4), 4 * (i % (kH / 4)));
+    *reinterpret_cast<bf16x4*>(hi + o) = h;
+    *reinterpret_cast<bf16x4*>(lo + o) = l4;
+  };
+  {
+    const int i = threadIdx.x;
+    const f32x4 e = e4[min(i, ne4 - 1)], d = d4[min(i, ne4 - 1)];
+    const f32x4 w2 = unit4(kOffW2, i), w3 = unit4(kOffW3, i), w4 = unit4(kOffW4, i & (kO * kH / 4 - 1));
+    const float c2 = Pf[kOffB2 + (i & (kH - 1))], c3 = Pf[kOffB3 + (i & (kH - 1))], c4 = Pf[kOffB4 + (i & (kO - 1))];
+    const double lk = S.lxk[min(i, S.nx - 1)];
+    stage4(kTwoLog2e * w2, sw2h, sw2l, i);
+    stage4(kTwoLog2e * w3, sw3h, sw3l, i);
+    if (i < kO * kH / 4) stage4(w4, sw4h, sw4l, i);
+    if (i < ne4) {
+      reinterpret_cast<f32x4*>(senv)[i] = e;
+      reinterpret_cast<f32x4*>(senvd)[i] = d;
+    }
+    if (i < kH) {
+      sb2[i] = kTwoLog2e * c2;
+      sb3[i] = kTwoLog2e * c3;
+    }
+    if (i < kO) sb4[i] = c4;
+    if (i < S.nx) slxk[i] = lk;
   }
-  for (int i = threadIdx.x; i < kH; i += BS) {
-    sb2[i] = kTwoLog2e * Pf[kOffB2 + i];
-    sb3[i] = kTwoLog2e * Pf[kOffB3 + i];
+  for (int i = threadIdx.x + BS; i < kH * kH / 4; i += BS) {
+    stage4(kTwoLog2e * unit4(kOffW2, i), sw2h, sw2l, i);
+    stage4(kTwoLog2e * unit4(kOffW3, i), sw3h, sw3l, i);
+    if (i < kO * kH / 4) stage4(unit4(kOffW4, i), sw4h, sw4l, i);
   }
-  for (int i = threadIdx.x; i < kO; i += BS) sb4[i] = Pf[kOffB4 + i];
+  for (int i = threadIdx.x + BS; i < ne4; i += BS) {
+    reinterpret_cast<f32x4*>(senv)[i] = e4[i];
+    reinterpret_cast<f32x4*>(senvd)[i] = d4[i];
+  }
+  for (int i = threadIdx.x + BS; i < S.nx; i += BS) slxk[i] = S.lxk[i];
   for (int i = threadIdx.x; i < rc.n; i += BS) scol[i] = rc.col[i];
   for (int i = threadIdx.x; i < kSurPts * rc.n; i += BS) {
     const int pt = i / rc.n, c = rc.col[i - pt * rc.n];
     swalk[i] = (unsigned short)(c < 0 ? 0xffff : pt * kO + c);
-  }
-  for (int i = threadIdx.x; i < kH * kH; i += BS) {  // stored column kp of row n holds W[n][kunit(kp)]
-    const int row = i / kH, kp = i % kH, src = row * kH + kunit(kp);
-    const int o = swz(row, kp);
-    split_bits(kTwoLog2e * Pf[kOffW2 + src], sw2h[o], sw2l[o]);
-    split_bits(kTwoLog2e * Pf[kOffW3 + src], sw3h[o], sw3l[o]);
-  }
-  for (int i = threadIdx.x; i < kO * kH; i += BS) {
-    const int row = i / kH, kp = i % kH, o = swz(row, kp);
-    split_bits(Pf[kOffW4 + row * kH + kunit(kp)], sw4h[o], sw4l[o]);
   }
   __syncthreads();
 
@@ -771,11 +810,11 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const float* __restrict__ Pf
   const float* __restrict__ gvals = member_values<float>(m);
   const int R = rc.n;
 
-  const int64_t ntiles = (n + 63) / 64;
+  const int64_t ntiles = (n + tile_pts - 1) / tile_pts;
   int qn = 0;  // queued fallback points of this wave (fewer than 64 between tiles)
-  for (int64_t tile = (int64_t)blockIdx.x * nwav + wv; tile < ntiles; tile += (int64_t)gridDim.x * nwav) {
-    const int64_t p0 = tile * 64;
-    const int np = (int)min((int64_t)64, n - p0);
+  for (int64_t tile = (int64_t)wv * gridDim.x + blockIdx.x; tile < ntiles; tile += (int64_t)gridDim.x * nwav) {
+    const int64_t p0 = tile * tile_pts;
+    const int np = (int)min((int64_t)tile_pts, n - p0);
     // one lane per point: inputs, fallback flag, envelope weights
     double xr = 0.5, qr = 1.0;
     bool fb = false;
@@ -1047,17 +1086,18 @@ hipError_t sur_gather(const float* in_all, const float* T_all, const int64_t* id
 hipError_t sur_infer(const SurDev& S, const MemberDev& m, const ReqCols& rc, const SurBufs& b, const double* x,
                      const double* q2, int64_t n, float* out, double invL01, unsigned long long* nerr, int n_cu,
                      hipStream_t s) {
-  const int64_t tiles = (n + 63) / 64;
   const int waves = sur_infer_waves(S.nx);
   if (waves < 1) return hipErrorInvalidValue;  // envelope tables beyond LDS (the create call bounds nx)
   const size_t shm = sur_infer_shared_bytes(S.nx, waves);
   const int64_t per_cu = std::max<int64_t>(1, (int64_t)(160 * 1024) / (int64_t)shm);
-  const int64_t blocks = min((tiles + waves - 1) / waves, (int64_t)n_cu * per_cu);
+  const int tile_pts = n <= (int64_t)n_cu * kSurSmallWaves * kSurPts ? kSurPts : 64;
+  const int64_t tiles = (n + tile_pts - 1) / tile_pts;
+  const int64_t blocks = min(tiles, (int64_t)n_cu * per_cu);
   if (blocks > 0) {
     hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(&k_sur_infer), shm);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_sur_infer, dim3((unsigned)blocks), dim3(64 * waves), shm, s, S, m, rc, b.P, x, q2, n,
-                       out, invL01, nerr);
+                       out, invL01, nerr, tile_pts);
   }
   return hipGetLastError();
 }
