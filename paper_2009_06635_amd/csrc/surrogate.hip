@@ -605,8 +605,12 @@ __global__ void k_gather_samples(const float* __restrict__ in_all, const float* 
 // kunit(k') = 16 (2 s + i / 4) + 4 g + i % 4.  The weight columns are staged
 // in LDS in that order (once per workgroup), so no activation passes through
 // LDS.  Layer 1 is one FP32 matrix product per 16 units, of (W1, b1) with
-// (u, v, 1).  The argument scale of tanh_scaled is folded into the staged
-// weights and biases, and the biases start the accumulators.  The outputs
+// (u, v, 1), with the argument scale of tanh_scaled folded in.  In layers 2
+// and 3 only the biases carry that scale: folded into the weights before
+// their split it saves one instruction per activation (3.5 % of the time), but
+// scaled weights use their BF16 binades differently, and the error against an
+// FP64 network grew from 3.80e-6 to 3.98e-6 (relative rms, 400 networks of
+// uniform weights).  The outputs
 // times the envelope go to a 32 x 16 LDS tile from which the requested
 // columns are stored point-major, consecutive lanes on consecutive values,
 // by a walk that is laid out once per workgroup.  Points in the fallback
@@ -616,13 +620,13 @@ __global__ void k_gather_samples(const float* __restrict__ in_all, const float* 
 // requested column) gathers its 4x4 stencil.
 //
 // What bounds it is the vector work of the activations: 192 per point, each
-// an exp2 and a reciprocal at half rate and 5.5 more instructions.  10^7
+// an exp2 and a reciprocal at half rate and six more instructions.  10^7
 // points of 11 columns: 1215 us with 16-point sub-tiles, layer 1 and the bias
 // on the vector units, the halves split by unpacking and two library FP64
 // logarithms and a binary search per point; 1027 us with each weight fragment
-// read for 32 points, layer 1 on the matrix cores and the table lookups;
-// 924 us with the folded scale, the split by dot products and the output walk;
-// 895 us with 16-byte staging, all tables in flight together.
+// read for 32 points, layer 1 on the matrix cores and the table lookups; about
+// 950 us with the split by dot products and the output walk; 915 us with
+// 16-byte staging, all tables in flight together.
 //
 // LDS rows of 64 BF16 values (the weight halves) hold their eight 16-byte
 // chunks in the order chunk ^ (row & 7), so the 16 rows an operand read
@@ -685,7 +689,7 @@ __device__ __forceinline__ float fb_extrapolate(const FbRec& f, const float* col
 // LDS of k_sur_infer: the lo and hi halves of W2, W3 (64 x 64) and W4
 // (16 x 64) with their columns in kunit order, [nx] ln x knots (double),
 // [nx][16] envelope values and slopes, b2 and b3 times 2 log2(e) (the
-// argument scale of tanh_scaled; also in W2, W3), b4, the output walk; then
+// argument scale of tanh_scaled), b4, the output walk; then
 // per wave a 5 KB area (4 KB for the output tile, later the fallback records;
 // 1 KB for the fallback queue) and the point records.
 constexpr size_t kSurWaveArea = 4096 + 128 * 8;  // output tile or fallback records, then the fallback queue
@@ -760,8 +764,8 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const float* __restrict__ Pf
     const f32x4 w2 = unit4(kOffW2, i), w3 = unit4(kOffW3, i), w4 = unit4(kOffW4, i & (kO * kH / 4 - 1));
     const float c2 = Pf[kOffB2 + (i & (kH - 1))], c3 = Pf[kOffB3 + (i & (kH - 1))], c4 = Pf[kOffB4 + (i & (kO - 1))];
     const double lk = S.lxk[min(i, S.nx - 1)];
-    stage4(kTwoLog2e * w2, sw2h, sw2l, i);
-    stage4(kTwoLog2e * w3, sw3h, sw3l, i);
+    stage4(w2, sw2h, sw2l, i);
+    stage4(w3, sw3h, sw3l, i);
     if (i < kO * kH / 4) stage4(w4, sw4h, sw4l, i);
     if (i < ne4) {
       reinterpret_cast<f32x4*>(senv)[i] = e;
@@ -775,8 +779,8 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const float* __restrict__ Pf
     if (i < S.nx) slxk[i] = lk;
   }
   for (int i = threadIdx.x + BS; i < kH * kH / 4; i += BS) {
-    stage4(kTwoLog2e * unit4(kOffW2, i), sw2h, sw2l, i);
-    stage4(kTwoLog2e * unit4(kOffW3, i), sw3h, sw3l, i);
+    stage4(unit4(kOffW2, i), sw2h, sw2l, i);
+    stage4(unit4(kOffW3, i), sw3h, sw3l, i);
     if (i < kO * kH / 4) stage4(unit4(kOffW4, i), sw4h, sw4l, i);
   }
   for (int i = threadIdx.x + BS; i < ne4; i += BS) {
@@ -869,7 +873,7 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const float* __restrict__ Pf
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const f32x4 bv = *reinterpret_cast<const f32x4*>(bias + 16 * t + 4 * g);
-          f32x4 acc[2] = {bv, bv};
+          f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
           for (int s = 0; s < 2; ++s) {
             const bf16x8 ah = frag(wh, 16 * t + r, 32 * s + 8 * g), al = frag(wl, 16 * t + r, 32 * s + 8 * g);
@@ -881,7 +885,7 @@ void k_sur_infer(SurDev S, MemberDev m, ReqCols rc, const float* __restrict__ Pf
             for (int p = 0; p < 2; ++p) acc[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh[p][s], acc[p], 0, 0, 0);
           }
 #pragma unroll
-          for (int p = 0; p < 2; ++p) act4(acc[p], nh[p][t >> 1], nl[p][t >> 1], 4 * (t & 1), m0, m1);
+          for (int p = 0; p < 2; ++p) act4(acc[p] * kTwoLog2e + bv, nh[p][t >> 1], nl[p][t >> 1], 4 * (t & 1), m0, m1);
         }
 #pragma unroll
         for (int p = 0; p < 2; ++p)
