@@ -485,7 +485,9 @@ __global__ __launch_bounds__(256) void k_locate(MemberDev m, const double* __res
 // threshold, the upper segment owns it), FP64 knot search, cubic Hermite in
 // ln Q^2 with one-sided slopes at segment ends, constant outside the knots.
 // The table block (at most 28 KB) is staged in LDS once per workgroup; four
-// independent evaluations in flight per lane.
+// independent evaluations in flight per lane.  Vector work (61 % busy) and the
+// 16 bytes per point bound it: 10^7 points 86.5 us with the library's logarithm
+// and per-segment searches, 37 now; moving the bytes alone takes 31.
 __global__ __launch_bounds__(256) void k_alphas(AlphasDev A, const double* __restrict__ Q2, int64_t n,
                                                 double* __restrict__ out, unsigned long long* __restrict__ nerr) {
   extern __shared__ __align__(16) unsigned char sas[];
@@ -607,9 +609,9 @@ static hipError_t launch_xfxq2_g(const MemberDev& m, const ReqCols& rc, const do
     // two workgroups are resident per compute unit; more than that are
     // launched only while every wave still has about three tiles of its own,
     // so that the staging of the tables is paid once for several tiles (FP32,
-    // 1.2e6 points: 84 us with one tile per wave, 73 with five) and long
-    // launches keep a queue that evens out the end (FP64, 1e7 points: 817 us
-    // with two workgroups per compute unit, 767 with 24 or more)
+    // 1.2e6 points: 72 us with one tile per wave, 63 with five) and long
+    // launches keep a queue that evens out the end (FP64, 1e7 points: 760 us
+    // with two workgroups per compute unit, 726 with 16 or more)
     const int64_t ntiles = (n + kBlockTables - 1) / kBlockTables;
     const int64_t per_cu = ntiles / (3 * (int64_t)n_cu);
     const int64_t nb =
@@ -1167,8 +1169,8 @@ hipError_t launch_mc_fused(const MemberDev& m, const ReqCols& rc, const AlphasDe
     // One block of points per workgroup, its four points per thread over the
     // four quarters, when that takes fewer rounds than four blocks per
     // workgroup: rounds of 1024 points on the slots of the chip (300007 points,
-    // 293 blocks: 2 rounds instead of 4, FP32 55 -> 38 us; 1e6 points: 4
-    // either way, and then the barrier per round costs 3 %, 91 against 94 us).
+    // 293 blocks: 2 rounds instead of 4, FP32 55 -> 38 us then, 32 now; 1e6 points:
+    // 4 either way, and then the barrier per round costs 3 %, 91 against 94 us).
     auto rounds = [&](size_t bytes, int per_wg) {
       const int64_t slots = (int64_t)n_cu * max(1, (int)(160 * 1024 / bytes));
       return ((np + per_wg - 1) / per_wg + slots - 1) / slots * per_wg;
@@ -1216,8 +1218,9 @@ namespace pdfmi {
 // tile pipeline as k_xfxq2.  A wave's first points are loaded before the
 // staging and the next ones before the current are evaluated (with the first
 // tile from the counter too and points loaded where they are used, 100 members
-// x 2415 points in FP64, one tile each, took 37.8 us, now 31).  Every wave reaches the exit once the counter passes the tile count;
-// the last workgroup to leave zeroes it for the next run (a reset kernel before
+// x 2415 points in FP64, one tile each, took 37.8 us, now 31).  Every wave
+// reaches the exit once the counter passes the tile count; the last workgroup
+// to leave zeroes it for the next run (a reset kernel before
 // each run cost 5 us).
 //
 // In FP32 with the grid in LDS, a request of up to kCompactCols different

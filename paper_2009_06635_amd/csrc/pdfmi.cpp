@@ -667,7 +667,7 @@ extern "C" int pdf_load_alphas(int32_t n, const double* q2k, const double* a) {
 // and kLayoutBytes each), and later calls of that request walk them in
 // 16-byte groups like a request for all columns: fewer lines per point (5 of
 // 13 columns in FP64: 9 instead of 16) and fewer, wider loads.  5 flavours at
-// 3e6 points of the three-sub-grid set in FP64: 208 us without, 135 us with;
+// 3e6 points of the three-sub-grid set in FP64: 201 us without, 116 us with;
 // making the copy takes about 50 us, which a call of two million points
 // gains back.  Returns the member to evaluate (m or a copy of it in `alt`
 // whose values are the layout's), with rc renumbered.
