@@ -217,7 +217,8 @@ int pdf_batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, in
  * (1: columns in groups of up to 16 bytes where the grid in LDS or the
  * request allows it; 0: one lane per (point, flavour)),
  * use_graph (1: pdf_batch_run replays a hipGraph holding the persistent
- * kernel, built on first use).  A change of tile_points
+ * kernel, after the counter reset if it takes tiles from the counter, built
+ * on first use).  A change of tile_points
  * rebuilds the tile table and first waits for the device to be idle (a run
  * of the plan may still be reading the old table).
  */

@@ -1219,9 +1219,13 @@ namespace pdfmi {
 // staging and the next ones before the current are evaluated (with the first
 // tile from the counter too and points loaded where they are used, 100 members
 // x 2415 points in FP64, one tile each, took 37.8 us, now 31).  Every wave
-// reaches the exit once the counter passes the tile count; the last workgroup
-// to leave zeroes it for the next run (a reset kernel before
-// each run cost 5 us).
+// reaches the exit once the counter passes the tile count.  A small kernel
+// zeroes the counter before each run (about 4 us), except for a plan that has
+// no more tiles than workgroups, which needs none.  Letting the last workgroup
+// zero it for the next run would save that, but two runs of one plan on
+// different streams may overlap, and then each must still evaluate every tile.
+// (Tiles dealt out in a fixed order instead: 514 us against 490 for the
+// 101-member plan.)
 //
 // In FP32 with the grid in LDS, a request of up to kCompactCols different
 // flavours (BatchReq::layout >= 0) is staged compacted: rows of kCompactCols
@@ -1238,6 +1242,10 @@ namespace pdfmi {
 // instead of 200 tiles of up to 2048 on 256).
 constexpr int batch_threads(bool lds_grid) { return lds_grid ? 1024 : 512; }
 constexpr int kCompactRowB = kCompactCols * 4;
+
+__global__ void k_batch_reset(unsigned* counter) {
+  if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0u;
+}
 
 template <typename T, bool kLdsGrid, bool kLdsTables>
 __global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const BatchReq* __restrict__ reqs, const int* __restrict__ cols,
@@ -1259,16 +1267,7 @@ __global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const Batch
   unsigned char* rec = srec + wv * wave_record_bytes<T>();
   int staged_member = -1, staged_layout = -1;  // layouts are >= 0, or <= -2 for all columns of a member
   // the first tile is the workgroup's own, the others come from the counter
-  for (int t = (int)blockIdx.x;; t = __builtin_amdgcn_readfirstlane(s_tile)) {
-    if (t >= ntiles) {
-      // counter[0] the next tile, counter[1] the workgroups that have left: no
-      // other workgroup reads either once all have
-      if (threadIdx.x == 0 && atomicAdd(counter + 1, 1u) == gridDim.x - 1) {
-        atomicExch(counter, 0u);
-        atomicExch(counter + 1, 0u);
-      }
-      break;
-    }
+  for (int t = (int)blockIdx.x; t < ntiles; t = __builtin_amdgcn_readfirstlane(s_tile)) {
     const BatchTile tl = tiles[t];
     const BatchReq rq = reqs[tl.req];
     const MemberDev& m = members[rq.member];
@@ -1354,6 +1353,7 @@ __global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const Batch
       else
         finish_slow<T, !kLdsGrid>(q, nslow, rq.R, scol, g0, sizeof(T) == 8 ? m.P64 : m.P32, invL01, tb.logt, lane);
     }
+    if (ntiles <= (int)gridDim.x) break;
     if (threadIdx.x == 0) s_tile = (int)(gridDim.x + atomicAdd(counter, 1u));
     __syncthreads();  // the next tile is known, and every wave has left this one's LDS
   }
@@ -1388,6 +1388,7 @@ BatchLaunch batch_launch_params(bool f32, bool lds, int max_tbl, int64_t max_ele
   L.block = (unsigned)batch_threads(lds);
   const int64_t g = min((int64_t)ntiles, (int64_t)batch_slots(lds, n_cu));
   L.grid = (unsigned)max((int64_t)1, g);
+  L.reset_fn = ntiles > (int)L.grid ? reinterpret_cast<const void*>(&k_batch_reset) : nullptr;
   return L;
 }
 
@@ -1395,7 +1396,12 @@ hipError_t batch_prepare(const BatchLaunch& L) {
   return allow_dynamic_lds(L.main_fn, L.shm);
 }
 
-hipError_t batch_launch(const BatchLaunch& L, void** args, hipStream_t s) {
+hipError_t batch_launch(const BatchLaunch& L, void** args, unsigned* counter, hipStream_t s) {
+  if (L.reset_fn) {
+    void* rargs[] = {&counter};
+    const hipError_t e = hipLaunchKernel(L.reset_fn, dim3(1), dim3(64), rargs, 0, s);
+    if (e != hipSuccess) return e;
+  }
   return hipLaunchKernel(L.main_fn, dim3(L.grid), dim3(L.block), args, L.shm, s);
 }
 

@@ -37,7 +37,7 @@ size_t batch_shared_bytes(int max_tbl, bool f32, bool lds);
 BatchLaunch batch_launch_params(bool f32, bool lds, int max_tbl, int64_t max_elems, int n_cu, int ntiles);
 int batch_slots(bool lds, int n_cu);
 hipError_t batch_prepare(const BatchLaunch& L);
-hipError_t batch_launch(const BatchLaunch& L, void** args, hipStream_t s);
+hipError_t batch_launch(const BatchLaunch& L, void** args, unsigned* counter, hipStream_t s);
 int sur_nparams();
 int sur_halves();
 constexpr int kSurMaxEnvKnots = 512;   // the inference kernel stages the envelope in LDS
@@ -913,7 +913,7 @@ struct Plan {
   int* d_cols = nullptr;
   MemberDev* d_members = nullptr;
   double* d_invL01 = nullptr;
-  unsigned* d_counter = nullptr;   // next tile, workgroups that have left
+  unsigned* d_counter = nullptr;   // tiles taken after each workgroup's first
   void* compact = nullptr;         // compacted copies of members' values (FP64 plans)
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -1012,14 +1012,25 @@ int plan_build_graph(Plan& P) {
   hipError_t e = batch_prepare(L);
   if (e != hipSuccess) return fail_hip(e, "hipFuncSetAttribute(batched)");
   if ((e = hipGraphCreate(&P.graph, 0)) != hipSuccess) return fail_hip(e, "hipGraphCreate");
-  hipGraphNode_t node;
+  hipGraphNode_t reset, node;
+  if (L.reset_fn) {
+    hipKernelNodeParams r{};
+    void* rargs[] = {&P.d_counter};
+    r.func = const_cast<void*>(L.reset_fn);
+    r.gridDim = dim3(1);
+    r.blockDim = dim3(64);
+    r.sharedMemBytes = 0;
+    r.kernelParams = rargs;
+    if ((e = hipGraphAddKernelNode(&reset, P.graph, nullptr, 0, &r)) != hipSuccess) return fail_hip(e, "graph node");
+  }
   hipKernelNodeParams k{};
   k.func = const_cast<void*>(L.main_fn);
   k.gridDim = dim3(L.grid);
   k.blockDim = dim3(L.block);
   k.sharedMemBytes = (unsigned)L.shm;
   k.kernelParams = P.args;
-  if ((e = hipGraphAddKernelNode(&node, P.graph, nullptr, 0, &k)) != hipSuccess) return fail_hip(e, "graph node");
+  if ((e = hipGraphAddKernelNode(&node, P.graph, L.reset_fn ? &reset : nullptr, L.reset_fn ? 1 : 0, &k)) != hipSuccess)
+    return fail_hip(e, "graph node");
   if ((e = hipGraphInstantiate(&P.exec, P.graph, nullptr, nullptr, 0)) != hipSuccess)
     return fail_hip(e, "hipGraphInstantiate");
   return PDF_OK;
@@ -1040,7 +1051,7 @@ int plan_run(Plan& P, hipStream_t s) {
   const BatchLaunch L = plan_params(P);
   hipError_t e = batch_prepare(L);
   if (e != hipSuccess) return fail_hip(e, "hipFuncSetAttribute(batched)");
-  e = batch_launch(L, P.args, s);
+  e = batch_launch(L, P.args, P.d_counter, s);
   if (e != hipSuccess) return fail_hip(e, "launch batched");
   return PDF_OK;
 }
@@ -1255,12 +1266,6 @@ int batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, bool c
   P.d_members = reinterpret_cast<MemberDev*>(b + br + bc);
   P.d_invL01 = reinterpret_cast<double*>(b + br + bc + bm);
   P.d_counter = reinterpret_cast<unsigned*>(b + br + bc + bm + bi);
-  // the tile counter starts at zero; every run leaves it so
-  const unsigned zero[2] = {0u, 0u};
-  if ((e = hipMemcpy(P.d_counter, zero, sizeof zero, hipMemcpyHostToDevice)) != hipSuccess) {
-    plan_release(P);
-    return fail_hip(e, "hipMemcpy(plan)");
-  }
   if (!P.reqs.empty() && (e = hipMemcpy(P.d_reqs, P.reqs.data(), sizeof(BatchReq) * P.reqs.size(),
                                         hipMemcpyHostToDevice)) != hipSuccess) {
     plan_release(P);

@@ -165,6 +165,7 @@ struct BatchTile {
 
 // Kernel node parameters of one batched run (the persistent kernel).
 struct BatchLaunch {
+  const void* reset_fn;  // zeroes the tile counter; null if the run needs none
   const void* main_fn;
   unsigned grid, block;
   size_t shm;
