@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "interp_dev.h"
+#include "layouts.h"
 #include "pdfmi_dev.h"
 
 namespace pdfmi {
@@ -400,6 +401,12 @@ __host__ __device__ static inline int alphas_staged_bytes(const AlphasDev& A, bo
   return member_tables ? A.logt_off : A.bytes;
 }
 
+// LDS bytes of a staged grid, up to the 16-byte aligned table behind it.
+template <typename T>
+__host__ __device__ constexpr size_t grid_lds_bytes(int elems) {
+  return ((size_t)elems * sizeof(T) + 15) & ~(size_t)15;
+}
+
 // LDS layout of k_xfxq2 and k_batched: [location tables][column map][per-wave
 // records][grid values], the tables only when they are staged (kLdsTables)
 // and the grid only when it is staged (kLdsGrid, which implies kLdsTables).
@@ -415,8 +422,8 @@ void k_xfxq2(MemberDev m, ReqCols rc, const double* __restrict__ X, const double
   int* scol = reinterpret_cast<int*>(smem + (kLdsTables ? m.tbl_bytes : 0));
   unsigned char* srec = reinterpret_cast<unsigned char*>(scol + kMaxReq);
   T* sgrid = reinterpret_cast<T*>(srec + kWaves * wave_record_bytes<T>());
-  // alpha_s table (fused alpha_s output only), after the staged grid
-  unsigned char* sas = reinterpret_cast<unsigned char*>(sgrid) + (kLdsGrid ? (size_t)lds_grid_elems * sizeof(T) : 0);
+  // alpha_s table (fused alpha_s output only), after the staged grid, 16-byte aligned
+  unsigned char* sas = reinterpret_cast<unsigned char*>(sgrid) + (kLdsGrid ? grid_lds_bytes<T>(lds_grid_elems) : 0);
   AsView av{sas, nullptr, nullptr};
   if constexpr (kAlphas) stage_copy<BS>(sas, A.tables, alphas_staged_bytes(A, kLdsTables));
   if constexpr (kLdsTables) stage_copy<BS>(stbl, m.tables, m.tbl_bytes);
@@ -596,7 +603,7 @@ static hipError_t launch_xfxq2_g(const MemberDev& m, const ReqCols& rc, const do
   const bool f32 = sizeof(T) == 4;
   const size_t as_bytes = alphas_lds_bytes(ao.A, true);
   if (lds_grid_elems > 0) {
-    const size_t shm = shared_bytes(m, f32, kBlockLds, true) + (size_t)lds_grid_elems * sizeof(T) + as_bytes;
+    const size_t shm = shared_bytes(m, f32, kBlockLds, true) + grid_lds_bytes<T>(lds_grid_elems) + as_bytes;
     const int per_cu = (int)(160 * 1024 / shm) > 0 ? (int)(160 * 1024 / shm) : 1;
     const int64_t ntiles = (n + kBlockLds - 1) / kBlockLds;
     const int64_t nb = min(ntiles, (int64_t)n_cu * per_cu);
@@ -668,7 +675,7 @@ hipError_t launch_xfxq2_f64(const MemberDev& m, const ReqCols& rc, const double*
                             double* out, unsigned long long* nerr, int lds_grid_elems, double invL01,
                             const LaunchCfg& cfg, const AlphasDev* A, double* aout, bool compact, hipStream_t s) {
   const AsOut ao{aout ? A : nullptr, aout};
-  const bool vec = cfg.vector_cols && (compact ? rc.n >= 2 : all_columns(m, rc, 2));
+  const bool vec = cfg.vector_cols && (compact ? layout_group(rc.n, false) == 2 : all_columns(m, rc, 2));
   if (aout)
     return vec ? launch_xfxq2_g<double, 2, true>(m, rc, x, q2, n, out, nerr, lds_grid_elems, invL01, cfg, ao, s)
                : launch_xfxq2_g<double, 1, true>(m, rc, x, q2, n, out, nerr, lds_grid_elems, invL01, cfg, ao, s);
@@ -680,8 +687,8 @@ hipError_t launch_xfxq2_f32(const MemberDev& m, const ReqCols& rc, const double*
                             float* out, unsigned long long* nerr, int lds_grid_elems, double invL01,
                             const LaunchCfg& cfg, const AlphasDev* A, double* aout, bool compact, hipStream_t s) {
   const AsOut ao{aout ? A : nullptr, aout};
-  const bool vec = cfg.vector_cols && (compact ? rc.n >= 4 : all_columns(m, rc, 4));
-  if (!vec && compact && rc.n >= 2)
+  const bool vec = cfg.vector_cols && (compact ? layout_group(rc.n, true) == 4 : all_columns(m, rc, 4));
+  if (!vec && compact && layout_group(rc.n, true) == 2)
     return aout ? launch_xfxq2_g<float, 2, true>(m, rc, x, q2, n, out, nerr, lds_grid_elems, invL01, cfg, ao, s)
                 : launch_xfxq2_g<float, 2, false>(m, rc, x, q2, n, out, nerr, lds_grid_elems, invL01, cfg, ao, s);
   if (aout)

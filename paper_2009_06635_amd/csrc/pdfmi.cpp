@@ -17,6 +17,7 @@
 #include <string>
 #include <vector>
 
+#include "layouts.h"
 #include "pdfmi_dev.h"
 
 namespace pdfmi {
@@ -724,19 +725,12 @@ static const MemberDev* use_layout(Member& M, bool f32, int64_t n, ReqCols& rc, 
     if (c.f32 == f32 && c.cols == cols) l = &c;
   if (!l) {
     if (M.layouts.size() >= kMaxLayouts) return &d;
-    const int g = f32 ? 4 : 2, es = f32 ? 4 : 8;
     M.layouts.push_back(Layout());
     l = &M.layouts.back();
     l->cols = cols;
     l->f32 = f32;
-    // rows of whole 16-byte groups where the copy fits LDS (aligned LDS
-    // reads); else 13 to 16 columns padded to full lines, fewer packed
-    const int whole = (rc.n + g - 1) / g * g;
-    if ((size_t)d.rows * whole * es + xfxq2_shared_bytes(d, f32) <= kLdsBytes - 1024)
-      l->stride = whole;
-    else
-      l->stride = rc.n > 12 ? (rc.n + 15) & ~15 : rc.n;
-    l->failed = (int64_t)d.rows * l->stride * es > kLayoutBytes;
+    l->stride = layout_stride(rc.n, f32, d.rows, (int64_t)kLdsBytes - 1024 - (int64_t)xfxq2_shared_bytes(d, f32));
+    l->failed = (int64_t)d.rows * l->stride * (f32 ? 4 : 8) > kLayoutBytes;
   }
   l->points += n;
   if (!l->mem && (l->failed || l->points < kLayoutPoints || !make_layout(*l, M, rc, stream))) return &d;
@@ -777,7 +771,9 @@ static int xfxq2_impl(int32_t member, const int32_t* pids, int32_t n_pids, const
   MemberDev alt;
   const MemberDev* dev = use_layout(*M, f32, n, req, alt, (hipStream_t)stream);
   const bool compact = dev == &alt;
-  const int lds = lds_grid_elems(*dev, f32, n, alphas_lds_bytes(fused ? &g_alphas : nullptr, true));
+  const bool stageable = !compact || layout_stageable(req.n, f32, f32 ? alt.P32 : alt.P64);
+  const int lds =
+      stageable ? lds_grid_elems(*dev, f32, n, alphas_lds_bytes(fused ? &g_alphas : nullptr, true)) : 0;
   hipError_t e;
   const LaunchCfg cfg{g_ncu, g_blocks_per_cu, g_vector_cols};
   const AlphasDev* A = fused ? &g_alphas : nullptr;
