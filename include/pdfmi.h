@@ -217,13 +217,20 @@ int pdf_batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, in
  * (1: columns in groups of up to 16 bytes where the grid in LDS or the
  * request allows it; 0: one lane per (point, flavour)),
  * use_graph (1: pdf_batch_run replays a hipGraph holding the persistent
- * kernel, after the counter reset if it takes tiles from the counter, built
- * on first use).  A change of tile_points
+ * kernel, built on first use; while a replay that takes tiles from a counter
+ * is in flight, further runs queue the kernel itself).  A change of tile_points
  * rebuilds the tile table and first waits for the device to be idle (a run
  * of the plan may still be reading the old table).
  */
 int pdf_batch_configure(int32_t plan, int32_t tile_points, int32_t vector_cols, int32_t use_graph);
-/* Queue one evaluation of every request of the plan on stream. */
+/*
+ * Queue one evaluation of every request of the plan on stream.  Runs of one
+ * plan may overlap: each evaluates everything itself, and its outputs are
+ * complete when its own stream has passed it (runs that overlap write the
+ * same values to the same outputs; the inputs must not change under any of
+ * them).  Capturable; a recorded run may overlap any other run of the plan,
+ * but not another replay of itself.
+ */
 int pdf_batch_run(int32_t plan, pdf_stream_t stream);
 /*
  * Time the plan on stream for each tile size in {1024, 2048, 4096, 8192,

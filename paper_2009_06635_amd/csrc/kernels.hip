@@ -1226,13 +1226,16 @@ namespace pdfmi {
 // staging and the next ones before the current are evaluated (with the first
 // tile from the counter too and points loaded where they are used, 100 members
 // x 2415 points in FP64, one tile each, took 37.8 us, now 31).  Every wave
-// reaches the exit once the counter passes the tile count.  A small kernel
-// zeroes the counter before each run (about 4 us), except for a plan that has
-// no more tiles than workgroups, which needs none.  Letting the last workgroup
-// zero it for the next run would save that, but two runs of one plan on
-// different streams may overlap, and then each must still evaluate every tile.
-// (Tiles dealt out in a fixed order instead: 514 us against 490 for the
-// 101-member plan.)
+// reaches the exit once the counter passes the tile count.
+//
+// Runs of one plan on different streams may overlap, and each has to have
+// evaluated every tile by its own end, so a run has its counter to itself (with
+// one per plan, the tiles taken by one run would be left out by the other).
+// The last workgroup to leave clears the counter and tells the host, which
+// then gives it to another run; a kernel before each run that clears it takes
+// about 4 us, an event recorded after it 6.  A run without a counter, because
+// all are in use, deals the tiles out in a fixed order (514 us against 490 for
+// the 101-member plan).
 //
 // In FP32 with the grid in LDS, a request of up to kCompactCols different
 // flavours (BatchReq::layout >= 0) is staged compacted: rows of kCompactCols
@@ -1250,15 +1253,12 @@ namespace pdfmi {
 constexpr int batch_threads(bool lds_grid) { return lds_grid ? 1024 : 512; }
 constexpr int kCompactRowB = kCompactCols * 4;
 
-__global__ void k_batch_reset(unsigned* counter) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *counter = 0u;
-}
-
 template <typename T, bool kLdsGrid, bool kLdsTables>
 __global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const BatchReq* __restrict__ reqs, const int* __restrict__ cols,
                                                       const BatchTile* __restrict__ tiles, int ntiles,
                                                       const MemberDev* __restrict__ members,
-                                                      const double* __restrict__ invL01s, unsigned* counter,
+                                                      const double* __restrict__ invL01s, RunSlot* slot,
+                                                      unsigned* done, unsigned run,
                                                       unsigned long long* __restrict__ nerr, int max_tbl,
                                                       int vector_cols) {
   static_assert(kLdsTables || !kLdsGrid, "a staged grid needs staged tables");
@@ -1361,8 +1361,15 @@ __global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const Batch
         finish_slow<T, !kLdsGrid>(q, nslow, rq.R, scol, g0, sizeof(T) == 8 ? m.P64 : m.P32, invL01, tb.logt, lane);
     }
     if (ntiles <= (int)gridDim.x) break;
-    if (threadIdx.x == 0) s_tile = (int)(gridDim.x + atomicAdd(counter, 1u));
+    if (threadIdx.x == 0) s_tile = slot ? (int)(gridDim.x + atomicAdd(&slot->taken, 1u)) : t + (int)gridDim.x;
     __syncthreads();  // the next tile is known, and every wave has left this one's LDS
+  }
+  if (slot && threadIdx.x == 0 &&
+      __hip_atomic_fetch_add(&slot->left, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) {
+    // no workgroup of this run takes another tile
+    __hip_atomic_store(&slot->taken, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&slot->left, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(done, run, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -1395,7 +1402,7 @@ BatchLaunch batch_launch_params(bool f32, bool lds, int max_tbl, int64_t max_ele
   L.block = (unsigned)batch_threads(lds);
   const int64_t g = min((int64_t)ntiles, (int64_t)batch_slots(lds, n_cu));
   L.grid = (unsigned)max((int64_t)1, g);
-  L.reset_fn = ntiles > (int)L.grid ? reinterpret_cast<const void*>(&k_batch_reset) : nullptr;
+  L.counted = ntiles > (int)L.grid;
   return L;
 }
 
@@ -1403,12 +1410,7 @@ hipError_t batch_prepare(const BatchLaunch& L) {
   return allow_dynamic_lds(L.main_fn, L.shm);
 }
 
-hipError_t batch_launch(const BatchLaunch& L, void** args, unsigned* counter, hipStream_t s) {
-  if (L.reset_fn) {
-    void* rargs[] = {&counter};
-    const hipError_t e = hipLaunchKernel(L.reset_fn, dim3(1), dim3(64), rargs, 0, s);
-    if (e != hipSuccess) return e;
-  }
+hipError_t batch_launch(const BatchLaunch& L, void** args, hipStream_t s) {
   return hipLaunchKernel(L.main_fn, dim3(L.grid), dim3(L.block), args, L.shm, s);
 }
 

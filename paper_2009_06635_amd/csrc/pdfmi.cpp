@@ -38,7 +38,7 @@ size_t batch_shared_bytes(int max_tbl, bool f32, bool lds);
 BatchLaunch batch_launch_params(bool f32, bool lds, int max_tbl, int64_t max_elems, int n_cu, int ntiles);
 int batch_slots(bool lds, int n_cu);
 hipError_t batch_prepare(const BatchLaunch& L);
-hipError_t batch_launch(const BatchLaunch& L, void** args, unsigned* counter, hipStream_t s);
+hipError_t batch_launch(const BatchLaunch& L, void** args, hipStream_t s);
 int sur_nparams();
 int sur_halves();
 constexpr int kSurMaxEnvKnots = 512;   // the inference kernel stages the envelope in LDS
@@ -887,6 +887,65 @@ extern "C" int pdf_get_tuning(int32_t knob, int32_t* value) {
 
 namespace {
 
+// The counters of the batched runs in flight (RunSlot).  A run that is queued
+// takes a free one; its kernel clears the counter and writes the run's number
+// to the slot's word in host memory when it has ended.  A recorded run's slot
+// is its plan's until the plan is destroyed.
+constexpr int kRunSlots = 4096;
+constexpr int kRecordedSlots = 1024;  // at most so many of them for recorded runs
+struct RunPool {
+  RunSlot* dev = nullptr;      // [kRunSlots]
+  unsigned* host = nullptr;    // [kRunSlots] last run that has ended in the slot (pinned)
+  unsigned* done = nullptr;    // device address of host
+  std::vector<unsigned> run;   // [kRunSlots] run that the slot was given to last
+  std::vector<bool> kept;      // [kRunSlots] kept by a plan
+  unsigned runs = 0;           // runs so far
+  int next = 0, recorded = 0;
+} g_runs;
+
+int runs_init() {
+  if (g_runs.dev) return PDF_OK;
+  RunPool p;
+  hipError_t e = hipMalloc(&p.dev, sizeof(RunSlot) * kRunSlots);
+  if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&p.host), sizeof(unsigned) * kRunSlots,
+                                          hipHostMallocMapped | hipHostMallocCoherent);
+  if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&p.done), p.host, 0);
+  if (e == hipSuccess) e = hipMemset(p.dev, 0, sizeof(RunSlot) * kRunSlots);
+  if (e == hipSuccess) e = hipDeviceSynchronize();
+  if (e != hipSuccess) {
+    if (p.dev) (void)hipFree(p.dev);
+    if (p.host) (void)hipHostFree(p.host);
+    return fail_hip(e, "counters of batched runs");
+  }
+  std::memset(p.host, 0, sizeof(unsigned) * kRunSlots);
+  p.run.assign(kRunSlots, 0);
+  p.kept.assign(kRunSlots, false);
+  g_runs = std::move(p);
+  return PDF_OK;
+}
+
+bool run_ended(int slot) { return __atomic_load_n(&g_runs.host[slot], __ATOMIC_ACQUIRE) == g_runs.run[slot]; }
+
+// Gives the slot to a new run, whose number it returns.
+unsigned run_begin(int slot) {
+  if (++g_runs.runs == 0) ++g_runs.runs;
+  return g_runs.run[slot] = g_runs.runs;
+}
+
+// The run was not queued after all.
+void run_cancel(int slot) { __atomic_store_n(&g_runs.host[slot], g_runs.run[slot], __ATOMIC_RELEASE); }
+
+// A free slot, or -1 if none of the next few is: they are given out in turn,
+// so only runs far behind, or very many, are in the way.
+int run_slot() {
+  for (int i = 0; i < 64; ++i) {
+    const int k = g_runs.next;
+    g_runs.next = (k + 1) % kRunSlots;
+    if (!g_runs.kept[k] && run_ended(k)) return k;
+  }
+  return -1;
+}
+
 struct Plan {
   bool used = false;
   int out_f64 = 0;
@@ -902,20 +961,24 @@ struct Plan {
   std::vector<std::pair<int32_t, uint64_t>> member_ids;  // (member id, load generation) behind members
   std::vector<double> invL01;
   int ntiles = 0;
-  void* dmem = nullptr;        // reqs, cols, members, invL01, counter
+  void* dmem = nullptr;        // reqs, cols, members, invL01
   BatchTile* d_tiles = nullptr;
   int tiles_cap = 0;
   BatchReq* d_reqs = nullptr;
   int* d_cols = nullptr;
   MemberDev* d_members = nullptr;
   double* d_invL01 = nullptr;
-  unsigned* d_counter = nullptr;   // tiles taken after each workgroup's first
+  std::vector<int> kept;           // slots of recorded runs
   void* compact = nullptr;         // compacted copies of members' values (FP64 plans)
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
+  int exec_slot = -1;
   // kernel argument storage (addresses handed to hipLaunchKernel / graph nodes)
+  RunSlot* a_slot = nullptr;
+  unsigned* a_done = nullptr;
+  unsigned a_run = 0;
   int a_ntiles = 0, a_max_tbl = 0, a_vec = 0;
-  void* args[10];
+  void* args[12];
 };
 
 std::vector<Plan> g_plans;
@@ -929,9 +992,14 @@ void plan_free_graph(Plan& P) {
 
 void plan_release(Plan& P) {
   plan_free_graph(P);
-  if (P.dmem) (void)hipFree(P.dmem);
+  if (P.dmem) (void)hipFree(P.dmem);  // waits for the device: no run of the plan is in flight after it
   if (P.d_tiles) (void)hipFree(P.d_tiles);
   if (P.compact) (void)hipFree(P.compact);
+  for (int k : P.kept) {
+    g_runs.kept[k] = false;
+    run_cancel(k);
+    --g_runs.recorded;
+  }
   P = Plan();
 }
 
@@ -986,7 +1054,11 @@ BatchLaunch plan_params(const Plan& P) {
   return batch_launch_params(!P.out_f64, P.lds, P.max_tbl, P.max_elems, g_ncu, P.ntiles);
 }
 
-void plan_args(Plan& P) {
+// Kernel arguments of a run with counter `slot` (-1: none).
+void plan_args(Plan& P, int slot) {
+  P.a_slot = slot < 0 ? nullptr : g_runs.dev + slot;
+  P.a_done = slot < 0 ? nullptr : g_runs.done + slot;
+  P.a_run = slot < 0 ? 0 : run_begin(slot);
   P.a_ntiles = P.ntiles;
   P.a_max_tbl = P.max_tbl;
   P.a_vec = P.vector_cols;
@@ -996,37 +1068,41 @@ void plan_args(Plan& P) {
   P.args[3] = &P.a_ntiles;
   P.args[4] = &P.d_members;
   P.args[5] = &P.d_invL01;
-  P.args[6] = &P.d_counter;
-  P.args[7] = &g_nerr;
-  P.args[8] = &P.a_max_tbl;
-  P.args[9] = &P.a_vec;
+  P.args[6] = &P.a_slot;
+  P.args[7] = &P.a_done;
+  P.args[8] = &P.a_run;
+  P.args[9] = &g_nerr;
+  P.args[10] = &P.a_max_tbl;
+  P.args[11] = &P.a_vec;
 }
 
-int plan_build_graph(Plan& P) {
+// A slot that the plan keeps for a recorded run, or -1.
+int plan_keep_slot(Plan& P) {
+  const int k = g_runs.recorded < kRecordedSlots ? run_slot() : -1;
+  if (k < 0) return -1;
+  P.kept.push_back(k);
+  g_runs.kept[k] = true;
+  ++g_runs.recorded;
+  return k;
+}
+
+int plan_build_graph(Plan& P, const BatchLaunch& L) {
   plan_free_graph(P);
-  const BatchLaunch L = plan_params(P);
   hipError_t e = batch_prepare(L);
   if (e != hipSuccess) return fail_hip(e, "hipFuncSetAttribute(batched)");
+  if (P.exec_slot >= 0 && !run_ended(P.exec_slot)) P.exec_slot = -1;  // a run of an earlier graph still has it
+  if (L.counted && P.exec_slot < 0) P.exec_slot = plan_keep_slot(P);
+  plan_args(P, L.counted ? P.exec_slot : -1);
+  if (L.counted && P.exec_slot >= 0) run_cancel(P.exec_slot);  // recorded, not in flight
   if ((e = hipGraphCreate(&P.graph, 0)) != hipSuccess) return fail_hip(e, "hipGraphCreate");
-  hipGraphNode_t reset, node;
-  if (L.reset_fn) {
-    hipKernelNodeParams r{};
-    void* rargs[] = {&P.d_counter};
-    r.func = const_cast<void*>(L.reset_fn);
-    r.gridDim = dim3(1);
-    r.blockDim = dim3(64);
-    r.sharedMemBytes = 0;
-    r.kernelParams = rargs;
-    if ((e = hipGraphAddKernelNode(&reset, P.graph, nullptr, 0, &r)) != hipSuccess) return fail_hip(e, "graph node");
-  }
   hipKernelNodeParams k{};
   k.func = const_cast<void*>(L.main_fn);
   k.gridDim = dim3(L.grid);
   k.blockDim = dim3(L.block);
   k.sharedMemBytes = (unsigned)L.shm;
   k.kernelParams = P.args;
-  if ((e = hipGraphAddKernelNode(&node, P.graph, L.reset_fn ? &reset : nullptr, L.reset_fn ? 1 : 0, &k)) != hipSuccess)
-    return fail_hip(e, "graph node");
+  hipGraphNode_t node;
+  if ((e = hipGraphAddKernelNode(&node, P.graph, nullptr, 0, &k)) != hipSuccess) return fail_hip(e, "graph node");
   if ((e = hipGraphInstantiate(&P.exec, P.graph, nullptr, nullptr, 0)) != hipSuccess)
     return fail_hip(e, "hipGraphInstantiate");
   return PDF_OK;
@@ -1034,22 +1110,30 @@ int plan_build_graph(Plan& P) {
 
 int plan_run(Plan& P, hipStream_t s) {
   if (P.ntiles == 0) return PDF_OK;
-  plan_args(P);
-  if (P.use_graph) {
+  const BatchLaunch L = plan_params(P);
+  const bool recording = L.counted && capturing(s);
+  // the plan's graph holds one counter: a run that finds it in flight is queued plainly
+  if (P.use_graph && !recording) {
     if (!P.exec) {
-      int rc = plan_build_graph(P);
+      const int rc = plan_build_graph(P, L);
       if (rc != PDF_OK) return rc;
     }
-    hipError_t e = hipGraphLaunch(P.exec, s);
-    if (e != hipSuccess) return fail_hip(e, "hipGraphLaunch");
-    return PDF_OK;
+    const int k = L.counted ? P.exec_slot : -1;
+    if (k < 0 || run_ended(k)) {
+      if (k >= 0) __atomic_store_n(&g_runs.host[k], 0u, __ATOMIC_RELEASE);
+      const hipError_t e = hipGraphLaunch(P.exec, s);
+      if (e == hipSuccess) return PDF_OK;
+      if (k >= 0) run_cancel(k);
+      return fail_hip(e, "hipGraphLaunch");
+    }
   }
-  const BatchLaunch L = plan_params(P);
+  const int k = !L.counted ? -1 : recording ? plan_keep_slot(P) : run_slot();
+  plan_args(P, k);
   hipError_t e = batch_prepare(L);
-  if (e != hipSuccess) return fail_hip(e, "hipFuncSetAttribute(batched)");
-  e = batch_launch(L, P.args, P.d_counter, s);
-  if (e != hipSuccess) return fail_hip(e, "launch batched");
-  return PDF_OK;
+  if (e == hipSuccess) e = batch_launch(L, P.args, s);
+  if (e == hipSuccess) return PDF_OK;
+  if (k >= 0) run_cancel(k);
+  return fail_hip(e, "launch batched");
 }
 
 Plan* get_plan(int32_t id) {
@@ -1176,6 +1260,7 @@ int batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, bool c
   if (!plan_out || (n_req > 0 && !reqs) || n_req < 0) return fail(PDF_ERR_ARG, "bad argument");
   std::lock_guard<std::mutex> lock(g_mu);
   int rc = ensure_init();
+  if (rc == PDF_OK) rc = runs_init();
   if (rc != PDF_OK) return rc;
   Plan P;
   P.used = true;
@@ -1251,7 +1336,7 @@ int batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, bool c
   const size_t bc = align_up(sizeof(int) * std::max<size_t>(1, P.cols.size()), 256);
   const size_t bm = align_up(sizeof(MemberDev) * std::max<size_t>(1, P.members.size()), 256);
   const size_t bi = align_up(sizeof(double) * std::max<size_t>(1, P.invL01.size()), 256);
-  hipError_t e = hipMalloc(&P.dmem, br + bc + bm + bi + 256);
+  hipError_t e = hipMalloc(&P.dmem, br + bc + bm + bi);
   if (e != hipSuccess) {
     plan_release(P);
     return fail_hip(e, "hipMalloc(plan)");
@@ -1261,7 +1346,6 @@ int batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, bool c
   P.d_cols = reinterpret_cast<int*>(b + br);
   P.d_members = reinterpret_cast<MemberDev*>(b + br + bc);
   P.d_invL01 = reinterpret_cast<double*>(b + br + bc + bm);
-  P.d_counter = reinterpret_cast<unsigned*>(b + br + bc + bm + bi);
   if (!P.reqs.empty() && (e = hipMemcpy(P.d_reqs, P.reqs.data(), sizeof(BatchReq) * P.reqs.size(),
                                         hipMemcpyHostToDevice)) != hipSuccess) {
     plan_release(P);
@@ -2082,6 +2166,9 @@ extern "C" int pdf_shutdown(void) {
   for (auto& S : g_surs)
     if (S.used) sur_release(S);
   g_surs.clear();
+  if (g_runs.dev) (void)hipFree(g_runs.dev);
+  if (g_runs.host) (void)hipHostFree(g_runs.host);
+  g_runs = RunPool();
   if (g_nerr) (void)hipFree(g_nerr);
   g_nerr = nullptr;
   if (g_fk_ws) (void)hipFree(g_fk_ws);

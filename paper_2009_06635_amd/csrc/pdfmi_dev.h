@@ -163,12 +163,19 @@ struct BatchTile {
   int64_t start;
 };
 
+// What a batched run in flight has to itself: how many tiles after each
+// workgroup's first have been taken, and how many workgroups have left.  Both
+// are 0 between runs (the last workgroup to leave clears them).
+struct alignas(64) RunSlot {
+  unsigned taken, left;
+};
+
 // Kernel node parameters of one batched run (the persistent kernel).
 struct BatchLaunch {
-  const void* reset_fn;  // zeroes the tile counter; null if the run needs none
   const void* main_fn;
   unsigned grid, block;
   size_t shm;
+  bool counted;  // more tiles than workgroups: the run takes tiles from a RunSlot
 };
 
 // Surrogate input normalisation and output envelope (device tables).  The
