@@ -106,14 +106,11 @@ namespace {
 
 // A copy of a member's values that holds the columns of one request, in request order.
 struct Layout {
-  std::vector<signed char> cols;
-  bool f32 = false;
+  LayoutKey key;
   int stride = 0;        // values per row
-  void* mem = nullptr;   // null until enough points have asked for it
+  void* mem = nullptr;
   hipEvent_t filled = nullptr;  // recorded after the copy on the stream that made it
   bool ready = false;    // the event has been seen complete
-  int64_t points = 0;    // points evaluated for this request so far
-  bool failed = false;
 };
 
 void layout_release(Layout& l) {
@@ -126,7 +123,8 @@ void layout_release(Layout& l) {
 
 struct Member {
   bool used = false;
-  std::vector<Layout> layouts;
+  std::vector<Layout> layouts;  // at most kMaxLayouts
+  LayoutsWanted wanted;
   MemberDev dev{};
   void* dmem = nullptr;
   std::vector<int> pids;   // stored column -> pid (0 normalised to 21)
@@ -672,9 +670,6 @@ extern "C" int pdf_load_alphas(int32_t n, const double* q2k, const double* a) {
 // making the copy takes about 50 us, which a call of two million points
 // gains back.  Returns the member to evaluate (m or a copy of it in `alt`
 // whose values are the layout's), with rc renumbered.
-constexpr int64_t kLayoutPoints = 1 << 21;
-constexpr size_t kMaxLayouts = 8;
-constexpr int64_t kLayoutBytes = (int64_t)16 << 20;
 
 static bool capturing(hipStream_t stream) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
@@ -683,21 +678,18 @@ static bool capturing(hipStream_t stream) {
   return true;
 }
 
-// Allocates and fills the layout on the caller's stream, without waiting for
-// it; nothing is made while that stream records a graph.
+// Allocates and fills the layout on the caller's stream, without waiting for it.
 static bool make_layout(Layout& l, const Member& M, const ReqCols& rc, hipStream_t stream) {
-  if (capturing(stream)) return false;
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // another thread's capture is not disturbed
   if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
-  hipError_t e = hipMalloc(&l.mem, (size_t)M.dev.rows * l.stride * (l.f32 ? 4 : 8));
+  hipError_t e = hipMalloc(&l.mem, (size_t)M.dev.rows * l.stride * (l.key.f32 ? 4 : 8));
   if (e == hipSuccess) e = hipEventCreateWithFlags(&l.filled, hipEventDisableTiming);
-  if (e == hipSuccess) e = launch_compact(M.dev, rc, l.f32, l.stride, l.mem, stream);
+  if (e == hipSuccess) e = launch_compact(M.dev, rc, l.key.f32, l.stride, l.mem, stream);
   if (e == hipSuccess) e = hipEventRecord(l.filled, stream);
   (void)hipThreadExchangeStreamCaptureMode(&mode);
   if (e == hipSuccess) return true;
   (void)hipGetLastError();
   layout_release(l);
-  l.failed = true;  // not tried again; the general path serves the request
   return false;
 }
 
@@ -719,21 +711,29 @@ static const MemberDev* use_layout(Member& M, bool f32, int64_t n, ReqCols& rc, 
   bool all = rc.n == d.P;
   for (int j = 0; j < rc.n && all; ++j) all = rc.col[j] == j;
   if (all || !g_vector_cols) return &d;
-  const std::vector<signed char> cols(rc.col, rc.col + rc.n);
+  static_assert(sizeof(LayoutKey::col) == kMaxReq, "a key holds any request");
+  LayoutKey key;
+  key.f32 = f32;
+  key.n = rc.n;
+  std::memcpy(key.col, rc.col, (size_t)rc.n);
   Layout* l = nullptr;
   for (Layout& c : M.layouts)
-    if (c.f32 == f32 && c.cols == cols) l = &c;
+    if (c.key == key) l = &c;
   if (!l) {
     if (M.layouts.size() >= kMaxLayouts) return &d;
-    M.layouts.push_back(Layout());
+    Layout made;
+    made.key = key;
+    made.stride = layout_stride(rc.n, f32, d.rows, (int64_t)kLdsBytes - 1024 - (int64_t)xfxq2_shared_bytes(d, f32));
+    // nothing is made while the stream records a graph
+    if (!layout_small(f32, d.rows, made.stride) || !M.wanted.add(key, n) || capturing(stream)) return &d;
+    if (!make_layout(made, M, rc, stream)) {
+      M.wanted.again(key);
+      return &d;
+    }
+    M.wanted.remove(key);
+    M.layouts.push_back(made);
     l = &M.layouts.back();
-    l->cols = cols;
-    l->f32 = f32;
-    l->stride = layout_stride(rc.n, f32, d.rows, (int64_t)kLdsBytes - 1024 - (int64_t)xfxq2_shared_bytes(d, f32));
-    l->failed = (int64_t)d.rows * l->stride * (f32 ? 4 : 8) > kLayoutBytes;
   }
-  l->points += n;
-  if (!l->mem && (l->failed || l->points < kLayoutPoints || !make_layout(*l, M, rc, stream))) return &d;
   if (!layout_ready(*l, stream)) return &d;
   alt = d;
   alt.P = rc.n;
