@@ -678,15 +678,24 @@ static bool capturing(hipStream_t stream) {
   return true;
 }
 
+// While it lives, this thread's calls that a capture forbids leave captures on
+// other streams (this thread's or another's) alone.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool ok = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  ~RelaxedCapture() {
+    if (ok) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+};
+
 // Allocates and fills the layout on the caller's stream, without waiting for it.
 static bool make_layout(Layout& l, const Member& M, const ReqCols& rc, hipStream_t stream) {
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // another thread's capture is not disturbed
-  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return false;
+  const RelaxedCapture relaxed;
+  if (!relaxed.ok) return false;
   hipError_t e = hipMalloc(&l.mem, (size_t)M.dev.rows * l.stride * (l.key.f32 ? 4 : 8));
   if (e == hipSuccess) e = hipEventCreateWithFlags(&l.filled, hipEventDisableTiming);
   if (e == hipSuccess) e = launch_compact(M.dev, rc, l.key.f32, l.stride, l.mem, stream);
   if (e == hipSuccess) e = hipEventRecord(l.filled, stream);
-  (void)hipThreadExchangeStreamCaptureMode(&mode);
   if (e == hipSuccess) return true;
   (void)hipGetLastError();
   layout_release(l);
@@ -698,6 +707,8 @@ static bool make_layout(Layout& l, const Member& M, const ReqCols& rc, hipStream
 static bool layout_ready(Layout& l, hipStream_t stream) {
   if (l.ready) return true;
   if (capturing(stream)) return false;
+  const RelaxedCapture relaxed;
+  if (!relaxed.ok) return false;
   const hipError_t e = hipEventQuery(l.filled);
   if (e == hipSuccess) return l.ready = true;
   (void)hipGetLastError();
