@@ -847,11 +847,16 @@ hipError_t launch_mc_sum(const T* xf1, const T* xf2, int P, const double* as, in
 // same device functions as k_xfxq2, forms sum_j xf1_j xf2_j in flavour order
 // and accumulates alpha_s times it -- the summation order of k_mc_partial, so
 // both paths give bit-identical sums.  The grid is staged in LDS when it
-// fits (kLdsGrid), else read from global memory.  In FP32 the LDS rows are
-// padded with zeros to a multiple of kGW = 4 columns when that fits too, and
-// the stencils are then read four columns at a time: one 16-byte LDS read
-// brings four columns of a stencil row (a random-row gather of 16-byte reads
-// delivers 2.3x the values per clock of 4-byte reads).  The flavour loop then
+// fits (kLdsGrid), if need be with the tables left in place (kStaged): they are
+// read a few times a point and mostly from the vector cache, the grid 32 times
+// a flavour (10^6 points, FP64, 11 columns of 50 x 33 knots: grid and tables in
+// global memory 1226 us, grid in LDS 95; at 50 x 32 all in LDS 101).  In FP32
+// the LDS rows are padded with zeros to a multiple of kGW = 4 columns when that
+// fits too, and the stencils are then read four columns at a time, as from
+// global memory: one 16-byte read
+// brings four columns of a stencil row (a random-row LDS gather of 16-byte reads
+// delivers 2.3x the values per clock of 4-byte reads; from global memory 10^6
+// points of 13 columns take 464 us, column by column 1185).  The flavour loop then
 // walks a list of column-group steps built once per workgroup from the
 // request: a step reads one group and applies the terms of the next 1..kGW
 // requested flavours whose columns fall in it, in request order, so the sum
@@ -942,7 +947,15 @@ __device__ __forceinline__ T mc_value(const T* g, const PointLoc& L, const McOri
                                    w[2], w[3], v[0], v[1], v[2], v[3], L.p0, L.p1, invL01, lt);
 }
 
-template <typename T, bool kLdsGrid, int kGW, bool kLdsTables = true>
+// What k_mc_fused stages of the tables: nothing, alpha_s (with the logarithm's
+// table), or the member's location tables too.
+enum McTables { kMcInPlace, kMcAlphas, kMcAll };
+
+__host__ __device__ static inline int mc_alphas_bytes(const AlphasDev& A, McTables staged) {
+  return staged == kMcInPlace ? 0 : alphas_staged_bytes(A, staged == kMcAll);
+}
+
+template <typename T, bool kLdsGrid, int kGW, McTables kStaged = kMcAll>
 __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc, AlphasDev A,
                                                          const double* __restrict__ X1,
                                                          const double* __restrict__ X2,
@@ -951,16 +964,17 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
                                                          unsigned long long* __restrict__ nerr, double invL01,
                                                          int split) {
   extern __shared__ __align__(16) unsigned char smem[];
+  constexpr bool kLdsTables = kStaged == kMcAll;
   unsigned char* stbl = smem;
   unsigned char* sas = smem + (kLdsTables ? m.tbl_bytes : 0);
-  const int as_bytes = alphas_staged_bytes(A, kLdsTables);
+  const int as_bytes = mc_alphas_bytes(A, kStaged);
   double* tree = reinterpret_cast<double*>(sas + as_bytes);  // [4][256], twice when split
   int* scol = reinterpret_cast<int*>(tree + (split ? 2 : 1) * kMcFusedBS);  // [kMaxReq]
   int* sstep = scol + kMaxReq;                            // [kMaxReq + 4] column-group steps (kGW > 1)
   T* sgrid = reinterpret_cast<T*>(sstep + kMaxReq + 4);   // 16-byte aligned: 2 kMaxReq + 4 ints
 
   if constexpr (kLdsTables) stage_copy<kMcFusedBS>(stbl, m.tables, m.tbl_bytes);
-  stage_copy<kMcFusedBS>(sas, A.tables, as_bytes);
+  if constexpr (kStaged != kMcInPlace) stage_copy<kMcFusedBS>(sas, A.tables, as_bytes);
   for (int i = threadIdx.x; i < rc.n; i += kMcFusedBS) scol[i] = rc.col[i];
   const int Pp = sizeof(T) == 8 ? m.P64 : m.P32;
   const T* __restrict__ gvals = member_values<T>(m);
@@ -971,8 +985,9 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
     if (threadIdx.x == 0) mc_build_steps<kGW>(rc, sstep);
   if constexpr (kLdsGrid) stage_rows<kMcFusedBS>(sgrid, gvals, m.rows, P, Pp);
   __syncthreads();
-  const Tables tb = tables_at(kLdsTables ? stbl : m.tables, m);
-  const AsView av{sas, kLdsTables ? tb.logt : reinterpret_cast<const LogEntry*>(sas + A.logt_off), nullptr};
+  Tables tb = tables_at(kLdsTables ? stbl : m.tables, m);
+  if constexpr (kStaged == kMcAlphas) tb.logt = reinterpret_cast<const LogEntry*>(sas + A.logt_off);
+  const AsView av{kStaged == kMcInPlace ? A.tables : sas, tb.logt, nullptr};
   const T* grid = kLdsGrid ? sgrid : gvals;
 
   const int q = threadIdx.x / kMcThreads, t = threadIdx.x % kMcThreads;
@@ -1007,8 +1022,8 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
       if (nb && (threadIdx.x & 63) == 0) atomicAdd(nerr, nb);
       const McOrigin o1 = mc_origin(L1, Qs.nqp, P), o2 = mc_origin(L2, Qs.nqp, P);
       double lum = 0.0;
-      if (kLdsGrid && kGW > 1 && !((L1.mode | L2.mode) & (kLowX | kLowQ | kHighQ))) {
-        // both lookups inside the LDS-staged grid, read a column group at a
+      if (kGW > 1 && !((L1.mode | L2.mode) & (kLowX | kLowQ | kHighQ))) {
+        // both lookups inside the grid, read a column group at a
         // time: per step, the kGW values of each lookup that mc_value gives
         // for the group's columns, then the step's terms in request order
         using V = typename VecOf<T, kGW>::type;
@@ -1147,9 +1162,8 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
 
 // LDS bytes of k_mc_fused (grid_elems > 0: the grid staged with row stride P).
 static size_t mc_fused_shared_bytes(const MemberDev& m, const AlphasDev& A, int64_t grid_elems, bool f32,
-                                    bool tables, bool split = false) {
-  return (tables ? (size_t)m.tbl_bytes : 0) + (size_t)alphas_staged_bytes(A, tables) +
-         (split ? 2 : 1) * kMcFusedBS * 8 +
+                                    McTables staged) {
+  return (staged == kMcAll ? (size_t)m.tbl_bytes : 0) + (size_t)mc_alphas_bytes(A, staged) + kMcFusedBS * 8 +
          (2 * kMaxReq + 4) * 4 + (size_t)grid_elems * (f32 ? 4 : 8);
 }
 
@@ -1164,31 +1178,51 @@ hipError_t launch_mc_fused(const MemberDev& m, const ReqCols& rc, const AlphasDe
     const int64_t rows = m.rows;
     const bool f32 = sizeof(T) == 4;
     // grid in LDS in column groups, else in LDS with stride P, else in global
-    // memory; location tables in LDS unless even they alone do not fit
-    const size_t lds_g = mc_fused_shared_bytes(m, A, rows * Pg, f32, true);
-    const size_t lds_1 = mc_fused_shared_bytes(m, A, rows * m.P, f32, true);
-    const size_t lds_0 = mc_fused_shared_bytes(m, A, 0, f32, true);
-    const int mode = kGW > 1 && lds_g <= 160 * 1024 ? 3
-                     : lds_1 <= 160 * 1024          ? 2
-                     : lds_0 <= 160 * 1024          ? 1
-                                                    : 0;
-    size_t shm = mode == 3 ? lds_g : mode == 2 ? lds_1 : mode == 1 ? lds_0 : mc_fused_shared_bytes(m, A, 0, f32, false);
+    // memory; with each, as many of the tables beside it as fit
+    struct Form {
+      decltype(&k_mc_fused<T, true, kGW>) kernel;
+      int64_t elems;
+      McTables staged;
+    };
+    const Form forms[] = {{&k_mc_fused<T, true, kGW, kMcAll>, rows * Pg, kMcAll},
+                          {&k_mc_fused<T, true, kGW, kMcAlphas>, rows * Pg, kMcAlphas},
+                          {&k_mc_fused<T, true, kGW, kMcInPlace>, rows * Pg, kMcInPlace},
+                          {&k_mc_fused<T, true, 1, kMcAll>, rows * m.P, kMcAll},
+                          {&k_mc_fused<T, true, 1, kMcAlphas>, rows * m.P, kMcAlphas},
+                          {&k_mc_fused<T, true, 1, kMcInPlace>, rows * m.P, kMcInPlace},
+                          {&k_mc_fused<T, false, kGW, kMcAll>, 0, kMcAll},
+                          {&k_mc_fused<T, false, kGW, kMcAlphas>, 0, kMcAlphas}};
     // One block of points per workgroup, its four points per thread over the
     // four quarters, when that takes fewer rounds than four blocks per
     // workgroup: rounds of 1024 points on the slots of the chip (300007 points,
     // 293 blocks: 2 rounds instead of 4, FP32 55 -> 38 us then, 32 now; 1e6 points:
     // 4 either way, and then the barrier per round costs 3 %, 91 against 94 us).
+    // It needs a second tree, and is then worth more than tables in LDS or
+    // column groups (FP32, 13 columns, 3e5 points: 58 us against 106).
     auto rounds = [&](size_t bytes, int per_wg) {
       const int64_t slots = (int64_t)n_cu * max(1, (int)(160 * 1024 / bytes));
       return ((np + per_wg - 1) / per_wg + slots - 1) / slots * per_wg;
     };
-    const size_t shm_split = shm + kMcFusedBS * 8;
-    const int split = shm_split <= 160 * 1024 && rounds(shm_split, 1) < rounds(shm, 4);
-    if (split) shm = shm_split;
-    auto kernel = mode == 3   ? &k_mc_fused<T, true, kGW>
-                  : mode == 2 ? &k_mc_fused<T, true, 1>
-                  : mode == 1 ? &k_mc_fused<T, false, 1>
-                              : &k_mc_fused<T, false, 1, false>;
+    constexpr size_t kTree = kMcFusedBS * 8;
+    const Form* form = nullptr;
+    size_t shm = 0;
+    int split = 0;
+    for (const Form& f : forms) {
+      const size_t b = mc_fused_shared_bytes(m, A, f.elems, f32, f.staged);
+      if (b > 160 * 1024) continue;  // the last always fits: at most 28 KB of alpha_s table
+      if (!form) {
+        form = &f;
+        shm = b;
+      }
+      if (form->elems && !f.elems) break;  // a grid in LDS comes first
+      if (b + kTree <= 160 * 1024 && rounds(b + kTree, 1) < rounds(b, 4)) {
+        form = &f;
+        shm = b + kTree;
+        split = 1;
+        break;
+      }
+    }
+    auto kernel = form->kernel;
     const void* fn = reinterpret_cast<const void*>(kernel);
     hipError_t e = allow_dynamic_lds(fn, shm);
     if (e != hipSuccess) return e;

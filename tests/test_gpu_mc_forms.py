@@ -1,0 +1,51 @@
+"""Fused Monte-Carlo sum on grids around the LDS limit: grid in LDS with all
+tables, with the alpha_s table alone, with none, in column groups and in single
+columns, and grid in global memory, each with and without a second summation
+tree -- bit-identical to the unfused calls."""
+import numpy as np
+import pytest
+
+from paper_2009_06635_amd import synth
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+from paper_2009_06635_amd import pdfmi  # noqa: E402
+
+DEV = "cuda:0"
+GRIDS = [(50, q, 11, False) for q in (30, 32, 33, 34, 35, 36)] + [(100, q, 2, False) for q in (80, 86, 89, 96)]
+GRIDS += [(50, q, 11, True) for q in (55, 58, 60, 62, 65, 68, 70, 72)] + [(50, q, 13, True) for q in (44, 46, 48, 55, 58, 61)]
+GRIDS += [(100, q, 4, True) for q in (84, 86, 89, 96, 99)]
+
+
+@pytest.mark.parametrize("n_alphas", [30, 256])
+@pytest.mark.parametrize("nx,nq,P,f32", GRIDS)
+def test_forms_equal_unfused(nx, nq, P, f32, n_alphas):
+    print("mc form", nx, nq, P, f32, n_alphas, flush=True)
+    rng = np.random.default_rng(nx * 1000 + nq)
+    xk = 10.0 ** (-6.0 + 6.0 * np.arange(nx) / (nx - 1))
+    xk[-1] = 1.0
+    g = synth.SynthGrid([xk], [synth.logspace_q2(1.65, 1e4, nq)], [rng.uniform(0.1, 1.0, (nx, nq, P))],
+                        synth.PIDS_13[:P])
+    qk = synth.logspace_q2(1.2, 2e4, n_alphas)
+    pdfmi.load_alphas(qk, synth.alphas_closed_form(qk))
+    m = pdfmi.load_synth(g)
+    ev = pdfmi.xfxq2_f32 if f32 else pdfmi.xfxq2
+    try:
+        for n in (3000, 200_000, 300_007):
+            x1, q2 = synth.config1_queries(n=n, seed=n)
+            x2 = x1[::-1].copy()
+            x1[::50] *= 1e-3
+            q2[::70] *= 1e5
+            x1, x2, q2 = (torch.from_numpy(a).to(DEV) for a in (x1, x2, q2))
+            for pids in (list(g.pids), [6, g.pids[-1], g.pids[0]]):
+                want = pdfmi.mc_chunk_sum(ev(m, pids, x1, q2), ev(m, pids, x2, q2), pdfmi.alphas_q2(q2))
+                got = pdfmi.mc_fused(m, pids, x1, x2, q2, f32=f32)
+                assert torch.equal(got.view(torch.int64), want.view(torch.int64)), (n, len(pids))
+            x1[7], q2[n // 2] = -1.0, float("nan")
+            pdfmi.error_count(reset=True)
+            assert torch.isnan(pdfmi.mc_fused(m, list(g.pids), x1, x2, q2, f32=f32)).all()
+            assert pdfmi.error_count(reset=True) == 4
+    finally:
+        pdfmi.unload(m)
