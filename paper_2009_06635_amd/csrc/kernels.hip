@@ -1287,7 +1287,8 @@ namespace pdfmi {
 constexpr int batch_threads(bool lds_grid) { return lds_grid ? 1024 : 512; }
 constexpr int kCompactRowB = kCompactCols * 4;
 
-template <typename T, bool kLdsGrid, bool kLdsTables>
+// kCounted: more tiles than workgroups (without it the arguments of the counter alone cost 0.3 us a run).
+template <typename T, bool kLdsGrid, bool kLdsTables, bool kCounted>
 __global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const BatchReq* __restrict__ reqs, const int* __restrict__ cols,
                                                       const BatchTile* __restrict__ tiles, int ntiles,
                                                       const MemberDev* __restrict__ members,
@@ -1394,16 +1395,20 @@ __global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const Batch
       else
         finish_slow<T, !kLdsGrid>(q, nslow, rq.R, scol, g0, sizeof(T) == 8 ? m.P64 : m.P32, invL01, tb.logt, lane);
     }
-    if (ntiles <= (int)gridDim.x) break;
+    if constexpr (!kCounted) break;  // no more tiles than workgroups
     if (threadIdx.x == 0) s_tile = slot ? (int)(gridDim.x + atomicAdd(&slot->taken, 1u)) : t + (int)gridDim.x;
     __syncthreads();  // the next tile is known, and every wave has left this one's LDS
   }
-  if (slot && threadIdx.x == 0 &&
-      __hip_atomic_fetch_add(&slot->left, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) {
+  // Relaxed atomics, in order because each waits for the one before: what this
+  // workgroup took of the count it has seen before it leaves.  (With acquire
+  // and release every workgroup writes its L2 back: 6 us a run.)
+  if (kCounted && slot && threadIdx.x == 0 &&
+      __hip_atomic_fetch_add(&slot->left, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1) {
     // no workgroup of this run takes another tile
     __hip_atomic_store(&slot->taken, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&slot->left, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(done, run, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __hip_atomic_store(done, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -1418,11 +1423,11 @@ size_t batch_shared_bytes(int max_tbl, bool f32, bool lds) {
 
 // Kernel node parameters of one batched run (used for direct launches and for building a hipGraph).
 
-template <typename T>
+template <typename T, bool kCounted>
 static const void* batch_fn(bool lds, bool tables) {
-  if (lds) return reinterpret_cast<const void*>(&k_batched<T, true, true>);
-  return tables ? reinterpret_cast<const void*>(&k_batched<T, false, true>)
-                : reinterpret_cast<const void*>(&k_batched<T, false, false>);
+  if (lds) return reinterpret_cast<const void*>(&k_batched<T, true, true, kCounted>);
+  return tables ? reinterpret_cast<const void*>(&k_batched<T, false, true, kCounted>)
+                : reinterpret_cast<const void*>(&k_batched<T, false, false, kCounted>);
 }
 
 // Workgroups of a batched run that are resident at once.
@@ -1432,11 +1437,12 @@ BatchLaunch batch_launch_params(bool f32, bool lds, int max_tbl, int64_t max_ele
   BatchLaunch L{};
   L.shm = batch_shared_bytes(max_tbl, f32, lds) + (lds ? (size_t)max_elems * (f32 ? 4 : 8) : 0);
   const bool tables = batch_tables(lds, max_tbl);
-  L.main_fn = f32 ? batch_fn<float>(lds, tables) : batch_fn<double>(lds, tables);
   L.block = (unsigned)batch_threads(lds);
   const int64_t g = min((int64_t)ntiles, (int64_t)batch_slots(lds, n_cu));
   L.grid = (unsigned)max((int64_t)1, g);
   L.counted = ntiles > (int)L.grid;
+  L.main_fn = L.counted ? (f32 ? batch_fn<float, true>(lds, tables) : batch_fn<double, true>(lds, tables))
+                        : (f32 ? batch_fn<float, false>(lds, tables) : batch_fn<double, false>(lds, tables));
   return L;
 }
 
