@@ -571,8 +571,9 @@ constexpr int kSmallWaves = 4;
 constexpr int kMinTilePts = 8;
 constexpr int kBlockTables = 512;   // tables staged in LDS, grid read from global memory
 constexpr int kBlockLds = 1024;     // tables and grid staged once per workgroup in LDS
-size_t xfxq2_shared_bytes(const MemberDev& m, bool f32) {
-  return shared_bytes(m, f32, kBlockLds, true);
+constexpr int kBlockLdsSmall = 768; // the same, where only fewer waves' records fit beside them
+size_t xfxq2_shared_bytes(const MemberDev& m, bool f32, bool small) {
+  return shared_bytes(m, f32, small ? kBlockLdsSmall : kBlockLds, true);
 }
 
 // Launch context: the alpha_s table and output of a fused evaluation (A and
@@ -603,10 +604,15 @@ static hipError_t launch_xfxq2_g(const MemberDev& m, const ReqCols& rc, const do
   const bool f32 = sizeof(T) == 4;
   const size_t as_bytes = alphas_lds_bytes(ao.A, true);
   if (lds_grid_elems > 0) {
-    const size_t shm = shared_bytes(m, f32, kBlockLds, true) + grid_lds_bytes<T>(lds_grid_elems) + as_bytes;
-    const int per_cu = (int)(160 * 1024 / shm) > 0 ? (int)(160 * 1024 / shm) : 1;
+    const size_t values = grid_lds_bytes<T>(lds_grid_elems) + as_bytes;
+    const bool large = shared_bytes(m, f32, kBlockLds, true) + values <= 160 * 1024;
+    const size_t shm = shared_bytes(m, f32, large ? kBlockLds : kBlockLdsSmall, true) + values;
+    const int per_cu = max(1, (int)(160 * 1024 / shm));
     const int64_t ntiles = (n + kBlockLds - 1) / kBlockLds;
     const int64_t nb = min(ntiles, (int64_t)n_cu * per_cu);
+    if (!large)
+      return launch_one<T, G, kBlockLdsSmall, true, true, kAlphas>(m, rc, x, q2, n, out, nerr, lds_grid_elems, invL01, nb,
+                                                                   shm, ao, s);
     return launch_one<T, G, kBlockLds, true, true, kAlphas>(m, rc, x, q2, n, out, nerr, lds_grid_elems, invL01, nb, shm, ao,
                                                    s);
   }

@@ -21,7 +21,7 @@
 #include "pdfmi_dev.h"
 
 namespace pdfmi {
-size_t xfxq2_shared_bytes(const MemberDev& m, bool f32);
+size_t xfxq2_shared_bytes(const MemberDev& m, bool f32, bool small);
 size_t alphas_lds_bytes(const AlphasDev* A, bool member_tables);
 hipError_t launch_xfxq2_f64(const MemberDev&, const ReqCols&, const double*, const double*, int64_t, double*,
                             unsigned long long*, int, double, const LaunchCfg&, const AlphasDev*, double*, bool,
@@ -332,13 +332,19 @@ Member* get_member(int32_t id) {
 int lds_grid_elems(const MemberDev& dev, bool f32, int64_t n, size_t extra = 0) {
   if (g_lds_policy == 1) return 0;
   const int64_t elems = f32 ? dev.elems32 : dev.elems64;
-  const size_t bytes = (size_t)elems * (f32 ? 4 : 8) + xfxq2_shared_bytes(dev, f32) + extra;
+  const size_t values = (size_t)elems * (f32 ? 4 : 8) + extra;
+  const bool small = values + xfxq2_shared_bytes(dev, f32, false) > kLdsBytes - 1024;
+  const size_t bytes = values + xfxq2_shared_bytes(dev, f32, small);
   if (bytes > kLdsBytes - 1024) return 0;
   if (g_lds_policy == 0) {
-    // each workgroup pays one grid copy; require enough tiles to amortise it
+    // each workgroup pays one grid copy; require enough tiles to amortise it,
+    // more of them for the smaller workgroup, which gains less (FP64 with
+    // alpha_s, 20 x 22 x 13 values, 3e5 and 2e6 points: 32 and 112 us, from
+    // global memory 31 and 135; 50 x 36 x 4, 1.1e6 points: 36.4 and 34.2)
     const int64_t tiles = (n + 255) / 256;
     const int per_cu = (int)(kLdsBytes / bytes);
-    if (tiles < (int64_t)4 * g_ncu * (per_cu > 0 ? per_cu : 1)) return 0;
+    const int least = !small ? 4 : (dev.P > 8 ? 10 : 24);
+    if (tiles < (int64_t)least * g_ncu * (per_cu > 0 ? per_cu : 1)) return 0;
   }
   return (int)elems;
 }
@@ -734,7 +740,7 @@ static const MemberDev* use_layout(Member& M, bool f32, int64_t n, ReqCols& rc, 
     if (M.layouts.size() >= kMaxLayouts) return &d;
     Layout made;
     made.key = key;
-    made.stride = layout_stride(rc.n, f32, d.rows, (int64_t)kLdsBytes - 1024 - (int64_t)xfxq2_shared_bytes(d, f32));
+    made.stride = layout_stride(rc.n, f32, d.rows, (int64_t)kLdsBytes - 1024 - (int64_t)xfxq2_shared_bytes(d, f32, true));
     // nothing is made while the stream records a graph
     if (!layout_small(f32, d.rows, made.stride) || !M.wanted.add(key, n) || capturing(stream)) return &d;
     if (!make_layout(made, M, rc, stream)) {
