@@ -21,7 +21,9 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
+#include <vector>
 
 #include "interp_dev.h"
 #include "layouts.h"
@@ -1259,13 +1261,15 @@ namespace pdfmi {
 // ---------------------------------------------------------------------------------------
 // Batched evaluation of many requests over many members (the paper's
 // multi-member evaluation of section 4.3): one persistent launch in which
-// each workgroup takes the tile of its own index, then repeatedly the next
-// one from a global counter, stages that tile's grid (and location tables) in
+// each workgroup takes a first tile of its own, then repeatedly the next
+// one from a counter, stages that tile's grid (and location tables) in
 // LDS when it differs from the one already staged, and runs the same per-wave
 // tile pipeline as k_xfxq2.  A wave's first points are loaded before the
-// staging and the next ones before the current are evaluated (with the first
-// tile from the counter too and points loaded where they are used, 100 members
-// x 2415 points in FP64, one tile each, took 37.8 us, now 31).  Every wave
+// staging and the next ones before the current are evaluated.  The first tiles
+// go to the 8 XCDs, which take workgroups in turn, in contiguous runs: a member's
+// rows are then read into one L2 and not into eight (100 members x 15000 points,
+// 13 columns of 1.3 MB a member, FP64: 347 us with the tile of the workgroup's
+// index, 259 with the first tile from the counter too, 236 so).  Every wave
 // reaches the exit once the counter passes the tile count.
 //
 // Runs of one plan on different streams may overlap, and each has to have
@@ -1286,16 +1290,20 @@ namespace pdfmi {
 // (flavour, knot) from random rows (101 members, 200 requests, 1.2e8 values:
 // 705 us, 541 with this layout).  Rows of 48 bytes start on every 16-byte bank slot, and
 // a compile-time stride lets the four Q^2 rows use immediate offsets.
-// Threads of a workgroup: one per compute unit with the grid in LDS, else two
-// of half the size, so that a plan of few points spreads over more of them
-// (100 members x 2415 points, FP64: tiles of 512 points on 500 of 512 slots
-// instead of 200 tiles of up to 2048 on 256).
-constexpr int batch_threads(bool lds_grid) { return lds_grid ? 1024 : 512; }
+// One workgroup of 1024 threads per compute unit; where the grids are read from
+// global memory and there are no more tiles of 512 points than two workgroups
+// of half the size per compute unit, those (kBatchHalf), so that a plan of few
+// points spreads over more of them (100 members x 2415 points, FP64: tiles of
+// 512 points on 500 of 512 slots instead of 200 tiles of up to 2048 on 256).
+// With more points they are the slower ones, as twice as many tiles, and so
+// members, share the caches (in the same example tiles of 4096 points: 575 us
+// where 1024 threads took 480).
+constexpr int kBatchThreads = 1024, kBatchHalf = 512;
 constexpr int kCompactRowB = kCompactCols * 4;
 
 // kCounted: more tiles than workgroups (without it the arguments of the counter alone cost 0.3 us a run).
-template <typename T, bool kLdsGrid, bool kLdsTables, bool kCounted>
-__global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const BatchReq* __restrict__ reqs, const int* __restrict__ cols,
+template <typename T, bool kLdsGrid, bool kLdsTables, bool kCounted, int kBS>
+__global__ __launch_bounds__(kBS) __attribute__((amdgpu_waves_per_eu(4))) void k_batched(const BatchReq* __restrict__ reqs, const int* __restrict__ cols,
                                                       const BatchTile* __restrict__ tiles, int ntiles,
                                                       const MemberDev* __restrict__ members,
                                                       const double* __restrict__ invL01s, RunSlot* slot,
@@ -1303,7 +1311,7 @@ __global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const Batch
                                                       unsigned long long* __restrict__ nerr, int max_tbl,
                                                       int vector_cols) {
   static_assert(kLdsTables || !kLdsGrid, "a staged grid needs staged tables");
-  constexpr int kBS = batch_threads(kLdsGrid), kWaves = kBS / kWave;
+  constexpr int kWaves = kBS / kWave;
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_tile;
   unsigned char* stbl = smem;                                              // [max_tbl] if staged
@@ -1315,7 +1323,9 @@ __global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const Batch
   unsigned char* rec = srec + wv * wave_record_bytes<T>();
   int staged_member = -1, staged_layout = -1;  // layouts are >= 0, or <= -2 for all columns of a member
   // the first tile is the workgroup's own, the others come from the counter
-  for (int t = (int)blockIdx.x; t < ntiles; t = __builtin_amdgcn_readfirstlane(s_tile)) {
+  const int per = (int)(gridDim.x >> 3), rest = (int)(gridDim.x & 7), xcd = (int)(blockIdx.x & 7);
+  const int t0 = xcd * per + min(xcd, rest) + (int)(blockIdx.x >> 3);
+  for (int t = t0; t < ntiles; t = __builtin_amdgcn_readfirstlane(s_tile)) {
     const BatchTile tl = tiles[t];
     const BatchReq rq = reqs[tl.req];
     const MemberDev& m = members[rq.member];
@@ -1422,33 +1432,85 @@ __global__ __launch_bounds__(batch_threads(kLdsGrid)) void k_batched(const Batch
 // grid is staged too).
 static bool batch_tables(bool lds, int max_tbl) { return lds || (size_t)max_tbl <= kMaxLdsTables; }
 
-size_t batch_shared_bytes(int max_tbl, bool f32, bool lds) {
+size_t batch_shared_bytes(int max_tbl, bool f32, bool lds, int block) {
   return (batch_tables(lds, max_tbl) ? (size_t)max_tbl : 0) + kMaxReq * 4 +
-         (batch_threads(lds) / kWave) * (f32 ? wave_record_bytes<float>() : wave_record_bytes<double>());
+         (block / kWave) * (f32 ? wave_record_bytes<float>() : wave_record_bytes<double>());
 }
 
 // Kernel node parameters of one batched run (used for direct launches and for building a hipGraph).
 
 template <typename T, bool kCounted>
-static const void* batch_fn(bool lds, bool tables) {
-  if (lds) return reinterpret_cast<const void*>(&k_batched<T, true, true, kCounted>);
-  return tables ? reinterpret_cast<const void*>(&k_batched<T, false, true, kCounted>)
-                : reinterpret_cast<const void*>(&k_batched<T, false, false, kCounted>);
+static const void* batch_fn(bool lds, bool tables, int block) {
+  if (lds) return reinterpret_cast<const void*>(&k_batched<T, true, true, kCounted, kBatchThreads>);
+  if (!kCounted && block == kBatchHalf)
+    return tables ? reinterpret_cast<const void*>(&k_batched<T, false, true, false, kBatchHalf>)
+                  : reinterpret_cast<const void*>(&k_batched<T, false, false, false, kBatchHalf>);
+  return tables ? reinterpret_cast<const void*>(&k_batched<T, false, true, kCounted, kBatchThreads>)
+                : reinterpret_cast<const void*>(&k_batched<T, false, false, kCounted, kBatchThreads>);
 }
 
-// Workgroups of a batched run that are resident at once.
-int batch_slots(bool lds, int n_cu) { return n_cu * (1024 / batch_threads(lds)); }
+// How the requests of a plan (n[i] points each) are cut into tiles of at most
+// `asked` points.  A plan of few tiles takes smaller ones, down to one pass of a
+// workgroup, where it then ends sooner.  The time is estimated in half passes:
+// a tile takes its passes and about one for the staging of the grid, or half
+// of one for the tables alone.  The compute units share the tiles, so the time
+// is at least their mean and, for every k, k + 1 of the tiles that the first k
+// rounds leave; the costliest come first where grids are in LDS, else the
+// compute units end half a tile apart on the average.
+BatchTiling batch_tiling(bool lds, int asked, const std::vector<int64_t>& n, int n_cu) {
+  int64_t half = 0;
+  for (int64_t ni : n) half += (ni + kBatchHalf - 1) / kBatchHalf;
+  if (!lds && asked >= kBatchHalf && half <= 2 * (int64_t)n_cu) return {kBatchHalf, kBatchHalf};
+  const int setup = lds ? 2 : 1;
+  int64_t tiles = 0;
+  std::vector<int64_t> count;  // tiles by passes
+  auto time_of = [&](int points) {
+    auto passes = [](int64_t p) { return (p + kBatchThreads - 1) / kBatchThreads; };
+    count.assign((size_t)passes(points) + 1, 0);
+    tiles = 0;
+    for (int64_t ni : n) {
+      const int64_t whole = ni / points, rest = ni - whole * points;
+      count[(size_t)passes(points)] += whole;
+      if (rest > 0) ++count[(size_t)passes(rest)];
+      tiles += whole + (rest > 0);
+    }
+    double work = 0.0, least = 0.0, longest = 0.0;
+    int64_t before = 0;  // tiles at least as costly
+    for (int64_t p = (int64_t)count.size() - 1; p >= 0; --p) {
+      if (count[p] == 0) continue;
+      const double c = 2.0 * p + setup;
+      longest = std::max(longest, c);
+      before += count[p];
+      work += c * count[p];
+      least = std::max(least, ((before - 1) / n_cu + 1) * c);
+    }
+    work /= n_cu;
+    return std::max(least, tiles <= n_cu || lds ? work : work + 0.5 * longest);
+  };
+  BatchTiling best{asked, kBatchThreads};
+  double least = time_of(asked);
+  if (tiles >= 2 * (int64_t)n_cu) return best;
+  for (int t = asked; t > kBatchThreads;) {
+    t = std::max(kBatchThreads, (t / 2 + 63) / 64 * 64);
+    const double c = time_of(t);
+    if (c < least) {
+      least = c;
+      best.points = t;
+    }
+  }
+  return best;
+}
 
-BatchLaunch batch_launch_params(bool f32, bool lds, int max_tbl, int64_t max_elems, int n_cu, int ntiles) {
+BatchLaunch batch_launch_params(bool f32, bool lds, int max_tbl, int64_t max_elems, int n_cu, int ntiles, int block) {
   BatchLaunch L{};
-  L.shm = batch_shared_bytes(max_tbl, f32, lds) + (lds ? (size_t)max_elems * (f32 ? 4 : 8) : 0);
+  L.shm = batch_shared_bytes(max_tbl, f32, lds, block) + (lds ? (size_t)max_elems * (f32 ? 4 : 8) : 0);
   const bool tables = batch_tables(lds, max_tbl);
-  L.block = (unsigned)batch_threads(lds);
-  const int64_t g = min((int64_t)ntiles, (int64_t)batch_slots(lds, n_cu));
+  L.block = (unsigned)block;
+  const int64_t g = min((int64_t)ntiles, (int64_t)n_cu * (block == kBatchHalf ? 2 : 1));
   L.grid = (unsigned)max((int64_t)1, g);
   L.counted = ntiles > (int)L.grid;
-  L.main_fn = L.counted ? (f32 ? batch_fn<float, true>(lds, tables) : batch_fn<double, true>(lds, tables))
-                        : (f32 ? batch_fn<float, false>(lds, tables) : batch_fn<double, false>(lds, tables));
+  L.main_fn = L.counted ? (f32 ? batch_fn<float, true>(lds, tables, block) : batch_fn<double, true>(lds, tables, block))
+                        : (f32 ? batch_fn<float, false>(lds, tables, block) : batch_fn<double, false>(lds, tables, block));
   return L;
 }
 

@@ -170,6 +170,11 @@ struct alignas(64) RunSlot {
   unsigned taken, left;
 };
 
+// How a batched plan is cut: points per tile, threads per workgroup.
+struct BatchTiling {
+  int points, block;
+};
+
 // Kernel node parameters of one batched run (the persistent kernel).
 struct BatchLaunch {
   const void* main_fn;
