@@ -7,7 +7,7 @@
 // [ndat][K], on the FP64 matrix cores (v_mfma_f64_16x16x4_f64).
 //
 // Two kernels: k_fk_contract for one tile of members (up to 112), k_fk_tiles
-// for more.  The summation order is fixed by the sizes and the number of
+// for more and for the largest tables (see fk_staged).  The summation order is fixed by the sizes and the number of
 // compute units (deterministic results).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -262,8 +262,25 @@ __global__ void k_fk_reduce(const double* __restrict__ P, int S, int64_t mn, dou
   }
 }
 
-// Up to this many members take k_fk_contract.
+// k_fk_contract takes up to this many members.
 constexpr int kFkOneTile = 16 * kFkMaxMT;
+
+// Is the contraction one for k_fk_tiles?  Above 112 members always.  Up to 80,
+// where its one tile of members pads little, also for tables beyond 256 MB (the
+// last cache): k_fk_contract then reads F from L2 four times as often as the
+// tiles of 128 table rows do, and rows that do not start on a 128-byte line
+// cost it more.  Times of k_fk_contract in those of k_fk_tiles, by members,
+// warm and with a new table each time: 1024 rows x 8001 0.64-0.76 and 0.72-0.94;
+// 1024 x 31395 24: 0.66, 32: 0.82 and 0.95, 64: 0.94 and 1.04; 3000 x 16001 24:
+// 1.01, 32: 1.07, 64: 1.29 and 1.21; 700 x 60001 33: 0.80, 64: 0.98; 10000 x 31395 24: 1.09, 32: 1.17, 64: 1.34,
+// 80: 1.25; with rows on lines (31392) 32: 0.92, 48: 1.05, 64: 1.11.  At 81 to
+// 112 members 0.6-1.03 everywhere (two tiles there).
+static bool fk_staged(int nrep, int ndat, int64_t K) {
+  if (nrep > kFkOneTile) return true;
+  const bool lines = K % 16 == 0;
+  const int64_t least = nrep > 48 ? 33000000 : 45000000;  // values of the table
+  return nrep <= 80 && nrep > (lines ? 48 : 24) && K >= least / std::max(ndat, 1);
+}
 
 // Rows per member tile of k_fk_tiles: 80 when that pads the member count no
 // more than 64 does (400 members: 5 tiles of 80 against 7 of 64), else 64.
@@ -302,12 +319,12 @@ int fk_limit_slices(int nrep, int ndat, int64_t K, int n_cu) {
                  std::max<int64_t>(1, std::min<int64_t>(64, K / (8 * kFkBK))));
 }
 
-// K slices of a contraction.  k_fk_contract: workgroups of four waves, one per
+// K slices of a contraction.  With k_fk_contract: workgroups of four waves, one per
 // compute unit for tiles of 64 members or more (its registers then hold one
 // wave per SIMD), else two; at least 64 k per wave, partial sums within the
 // scratch size.
 int fk_slices(int nrep, int ndat, int64_t K, int n_cu) {
-  if (nrep > kFkOneTile) return fk_limit_slices(nrep, ndat, K, n_cu);
+  if (fk_staged(nrep, ndat, K)) return fk_limit_slices(nrep, ndat, K, n_cu);
   const int64_t fit = (int64_t)(kFkScratchBytes / 8) / std::max<int64_t>(1, (int64_t)nrep * ndat);
   return fk_fill((ndat + kFkBN - 1) / kFkBN, (int64_t)(nrep > 48 ? 1 : 2) * std::max(n_cu, 1),
                  std::max<int64_t>(1, std::min({(int64_t)64, K / (64 * kFkWaves), fit})));
@@ -361,7 +378,7 @@ hipError_t launch_fk_contract(const double* F, const double* FK, int nrep, int n
                               double* ws, hipStream_t s) {
   double* dst = S > 1 ? ws : T;
   hipError_t e = hipSuccess;
-  if (nrep > kFkOneTile) {
+  if (fk_staged(nrep, ndat, K)) {
     int64_t kslice = (K + S - 1) / S;
     kslice = std::max<int64_t>((kslice + kFkBK - 1) / kFkBK * kFkBK, 1);
     const int bm = fk_tile_rows(nrep);
