@@ -27,6 +27,7 @@ hipError_t launch_xfxq2_f64(const MemberDev&, const ReqCols&, const double*, con
                             unsigned long long*, int, double, const LaunchCfg&, const AlphasDev*, double*, bool,
                             hipStream_t);
 hipError_t launch_compact(const MemberDev& m, const ReqCols& rc, bool f32, int Rp, void* dst, hipStream_t s);
+hipError_t launch_compact_jobs(const CompactJob* jobs, int n, int64_t max_elems, hipStream_t s);
 hipError_t launch_xfxq2_f32(const MemberDev&, const ReqCols&, const double*, const double*, int64_t, float*,
                             unsigned long long*, int, double, const LaunchCfg&, const AlphasDev*, double*, bool,
                             hipStream_t);
@@ -1233,13 +1234,8 @@ struct PlanBuilder {
     return (int)P.members.size() - 1;
   }
 
-  struct Copy {
-    const Member* from;
-    ReqCols rc;
-    int to;         // plan member index
-    size_t offset;  // bytes into the copies' memory
-  };
-  std::vector<Copy> todo;
+  std::vector<CompactJob> jobs;
+  std::vector<int> job_member;  // plan member index of each job's copy
 
   // Plan member index of the copy for this request, or -1 to read the member's
   // rows.  Rows of an even number of values (16-byte groups stay aligned where
@@ -1256,22 +1252,24 @@ struct PlanBuilder {
     d.P64 = stride;
     d.elems64 = (int64_t)M.dev.rows * stride;
     const int to = add_member(P, d, M);
-    todo.push_back({&M, rc, to, copied});
+    jobs.push_back({M.dev.v64, nullptr, d.elems64, M.dev.P64, stride, rc});
+    job_member.push_back(to);
     copied += bytes;
     return copies[key] = to;
   }
 
-  // Allocates and fills the copies.
-  hipError_t fill(Plan& P) {
-    if (todo.empty()) return hipSuccess;
-    hipError_t e = hipMalloc(&P.compact, copied);
-    for (size_t i = 0; i < todo.size() && e == hipSuccess; ++i) {
-      MemberDev& d = P.members[todo[i].to];
-      double* dst = reinterpret_cast<double*>(static_cast<unsigned char*>(P.compact) + todo[i].offset);
-      d.v64 = dst;
-      e = launch_compact(todo[i].from->dev, todo[i].rc, false, d.P64, dst, nullptr);
+  // Allocates the copies; the jobs fill them.
+  hipError_t allocate(Plan& P) {
+    if (jobs.empty()) return hipSuccess;
+    const hipError_t e = hipMalloc(&P.compact, copied);
+    if (e != hipSuccess) return e;
+    unsigned char* at = static_cast<unsigned char*>(P.compact);
+    for (size_t i = 0; i < jobs.size(); ++i) {
+      jobs[i].dst = reinterpret_cast<double*>(at);
+      P.members[job_member[i]].v64 = jobs[i].dst;
+      at += align_up((size_t)jobs[i].elems * sizeof(double), 256);
     }
-    return e == hipSuccess ? hipStreamSynchronize(nullptr) : e;
+    return hipSuccess;
   }
 };
 
@@ -1338,7 +1336,7 @@ int batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, bool c
     b.n = q.n;
     P.reqs.push_back(b);
   }
-  if (B.fill(P) != hipSuccess) {
+  if (B.allocate(P) != hipSuccess) {
     (void)hipGetLastError();
     plan_release(P);
     return kRetryPlain;
@@ -1353,37 +1351,42 @@ int batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, bool c
     else
       for (BatchReq& b : P.reqs) b.layout = -1;
   }
-  const size_t br = align_up(sizeof(BatchReq) * std::max<size_t>(1, P.reqs.size()), 256);
-  const size_t bc = align_up(sizeof(int) * std::max<size_t>(1, P.cols.size()), 256);
-  const size_t bm = align_up(sizeof(MemberDev) * std::max<size_t>(1, P.members.size()), 256);
-  const size_t bi = align_up(sizeof(double) * std::max<size_t>(1, P.invL01.size()), 256);
-  hipError_t e = hipMalloc(&P.dmem, br + bc + bm + bi);
+  // requests, columns, members, jobs of the copies: one block, one transfer
+  size_t bytes = 0;
+  auto part = [&](size_t n) {
+    const size_t at = bytes;
+    bytes += align_up(std::max<size_t>(1, n), 256);
+    return at;
+  };
+  const size_t br = part(sizeof(BatchReq) * P.reqs.size()), bc = part(sizeof(int) * P.cols.size());
+  const size_t bm = part(sizeof(MemberDev) * P.members.size()), bi = part(sizeof(double) * P.invL01.size());
+  const size_t bj = part(sizeof(CompactJob) * B.jobs.size());
+  std::vector<unsigned char> blob(bytes);
+  auto put = [&](size_t at, const auto& v) {
+    if (!v.empty()) std::memcpy(blob.data() + at, v.data(), sizeof(v[0]) * v.size());
+  };
+  put(br, P.reqs);
+  put(bc, P.cols);
+  put(bm, P.members);
+  put(bi, P.invL01);
+  put(bj, B.jobs);
+  hipError_t e = hipMalloc(&P.dmem, bytes);
+  if (e == hipSuccess) e = hipMemcpy(P.dmem, blob.data(), bytes, hipMemcpyHostToDevice);
+  unsigned char* b = static_cast<unsigned char*>(P.dmem);
+  if (e == hipSuccess && !B.jobs.empty()) {
+    int64_t most = 0;
+    for (const CompactJob& j : B.jobs) most = std::max(most, j.elems);
+    e = launch_compact_jobs(reinterpret_cast<const CompactJob*>(b + bj), (int)B.jobs.size(), most, nullptr);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  }
   if (e != hipSuccess) {
     plan_release(P);
-    return fail_hip(e, "hipMalloc(plan)");
+    return fail_hip(e, "plan tables");
   }
-  unsigned char* b = static_cast<unsigned char*>(P.dmem);
-  P.d_reqs = reinterpret_cast<BatchReq*>(b);
-  P.d_cols = reinterpret_cast<int*>(b + br);
-  P.d_members = reinterpret_cast<MemberDev*>(b + br + bc);
-  P.d_invL01 = reinterpret_cast<double*>(b + br + bc + bm);
-  if (!P.reqs.empty() && (e = hipMemcpy(P.d_reqs, P.reqs.data(), sizeof(BatchReq) * P.reqs.size(),
-                                        hipMemcpyHostToDevice)) != hipSuccess) {
-    plan_release(P);
-    return fail_hip(e, "hipMemcpy(plan)");
-  }
-  if (!P.cols.empty() &&
-      (e = hipMemcpy(P.d_cols, P.cols.data(), sizeof(int) * P.cols.size(), hipMemcpyHostToDevice)) != hipSuccess) {
-    plan_release(P);
-    return fail_hip(e, "hipMemcpy(plan)");
-  }
-  if (!P.members.empty() && ((e = hipMemcpy(P.d_members, P.members.data(), sizeof(MemberDev) * P.members.size(),
-                                            hipMemcpyHostToDevice)) != hipSuccess ||
-                             (e = hipMemcpy(P.d_invL01, P.invL01.data(), sizeof(double) * P.invL01.size(),
-                                            hipMemcpyHostToDevice)) != hipSuccess)) {
-    plan_release(P);
-    return fail_hip(e, "hipMemcpy(plan)");
-  }
+  P.d_reqs = reinterpret_cast<BatchReq*>(b + br);
+  P.d_cols = reinterpret_cast<int*>(b + bc);
+  P.d_members = reinterpret_cast<MemberDev*>(b + bm);
+  P.d_invL01 = reinterpret_cast<double*>(b + bi);
   if ((rc = plan_tiles(P)) != PDF_OK) {
     plan_release(P);
     return rc;

@@ -170,6 +170,15 @@ struct alignas(64) RunSlot {
   unsigned taken, left;
 };
 
+// A compacted copy of a member's FP64 values that a plan makes (device copy).
+struct CompactJob {
+  const double* src;
+  double* dst;
+  int64_t elems;  // values of the copy
+  int Ps, Rp;     // row strides of src and dst
+  ReqCols rc;
+};
+
 // How a batched plan is cut: points per tile, threads per workgroup.
 struct BatchTiling {
   int points, block;
