@@ -1203,7 +1203,11 @@ hipError_t launch_mc_fused(const MemberDev& m, const ReqCols& rc, const AlphasDe
     const int64_t rows = m.rows;
     const bool f32 = sizeof(T) == 4;
     // grid in LDS in column groups, else in LDS with stride P, else in global
-    // memory; with each, as many of the tables beside it as fit
+    // memory; with each, as many of the tables beside it as fit.  From global
+    // memory the groups' rows come one after another, which a few waves wait for
+    // longer than for single columns (13 columns, 64 points 45.2 against 43.2 us,
+    // 128 36.6 and 40.2; 5 columns, 256 points 32.5 and 29.2, 512 39.8 and 42.1)
+    const bool few = n * rc.n <= 1500;
     struct Form {
       decltype(&k_mc_fused<T, true, kGW>) kernel;
       int64_t elems;
@@ -1215,7 +1219,7 @@ hipError_t launch_mc_fused(const MemberDev& m, const ReqCols& rc, const AlphasDe
                           {&k_mc_fused<T, true, 1, kMcAll>, rows * m.P, kMcAll},
                           {&k_mc_fused<T, true, 1, kMcAlphas>, rows * m.P, kMcAlphas},
                           {&k_mc_fused<T, true, 1, kMcInPlace>, rows * m.P, kMcInPlace},
-                          {&k_mc_fused<T, false, kGW, kMcAll>, 0, kMcAll},
+                          {few ? &k_mc_fused<T, false, 1, kMcAll> : &k_mc_fused<T, false, kGW, kMcAll>, 0, kMcAll},
                           {&k_mc_fused<T, false, kGW, kMcAlphas>, 0, kMcAlphas}};
     // One block of points per workgroup, its four points per thread over the
     // four quarters, when that takes fewer rounds than four blocks per

@@ -33,7 +33,7 @@ def test_forms_equal_unfused(nx, nq, P, f32, n_alphas):
     m = pdfmi.load_synth(g)
     ev = pdfmi.xfxq2_f32 if f32 else pdfmi.xfxq2
     try:
-        for n in (3000, 200_000, 300_007):
+        for n in (100, 3000, 200_000, 300_007):
             x1, q2 = synth.config1_queries(n=n, seed=n)
             x2 = x1[::-1].copy()
             x1[::50] *= 1e-3
