@@ -233,33 +233,40 @@ uint64_t double_bits(double v) {
   return u;
 }
 
-HintAxis build_hints(const double* t, int n, std::vector<short>& hints) {
+// The buckets of a table's hint list (off stays -1); n == 0 if it has none.
+HintAxis hint_buckets(const double* t, int n) {
   HintAxis h{-1, 0, 0, 0};
   if (n < 4) return h;
-  const int last = n - 2;
+  std::vector<int> inside;
   for (int shift = 52; shift >= 32; --shift) {
     const uint64_t k0 = double_bits(t[0]) >> shift, k1 = double_bits(t[n - 1]) >> shift;
     const uint64_t nb = k1 - k0 + 1;
     if (nb > (uint64_t)kMaxHintsPerAxis) break;  // finer buckets only make the list longer
-    std::vector<int> inside(nb, 0);
+    inside.assign(nb, 0);
     const uint64_t low_mask = (1ull << shift) - 1;
     for (int i = 0; i < n; ++i) {
       const uint64_t u = double_bits(t[i]);
       if (u & low_mask) ++inside[(u >> shift) - k0];  // above the bucket's smallest value
     }
     if (*std::max_element(inside.begin(), inside.end()) > 2) continue;
-    h.off = (int)hints.size();
     h.n = (int)nb;
     h.shift = shift - 32;
     h.key0 = (int)k0;
-    for (uint64_t b = 0; b < nb; ++b) {
-      const uint64_t lo_bits = (k0 + b) << shift;
-      double lo;
-      std::memcpy(&lo, &lo_bits, 8);
-      const int i = (int)(std::upper_bound(t, t + n, lo) - t) - 1;  // largest i with t[i] <= lo
-      hints.push_back((short)std::min(std::max(i, 0), last));
-    }
-    return h;
+    break;
+  }
+  return h;
+}
+
+HintAxis build_hints(const double* t, int n, std::vector<short>& hints) {
+  HintAxis h = hint_buckets(t, n);
+  if (h.n == 0) return h;
+  h.off = (int)hints.size();
+  for (int b = 0; b < h.n; ++b) {
+    const uint64_t lo_bits = (uint64_t)(h.key0 + b) << (h.shift + 32);
+    double lo;
+    std::memcpy(&lo, &lo_bits, 8);
+    const int i = (int)(std::upper_bound(t, t + n, lo) - t) - 1;  // largest i with t[i] <= lo
+    hints.push_back((short)std::min(std::max(i, 0), n - 2));
   }
   return h;
 }
@@ -446,7 +453,7 @@ extern "C" int pdf_load_grid(int32_t K, const int32_t* shape, int32_t P, const i
   std::vector<double> hk, hq;
   std::vector<CellCoef> hc;
   std::vector<QCell> hqc;
-  std::vector<short> hh, one;
+  std::vector<short> hh;
   std::vector<SubDesc> subs(K);
   std::vector<double> hv((size_t)n64, 0.0);
   std::vector<float> hf((size_t)n32, 0.0f);
@@ -483,11 +490,7 @@ extern "C" int pdf_load_grid(int32_t K, const int32_t* shape, int32_t P, const i
       hqc.push_back(QCell{qc[i], row_off[k] + sq, nqp[k], k << 16 | i, i - sq, {}});
     }
     if (k == K - 1) hq.push_back(qk[nq - 1]);
-    if (K > 1) {
-      one.clear();
-      build_hints(qk, nq, one);
-      ref_hints += one.size();
-    }
+    if (K > 1) ref_hints += hint_buckets(qk, nq).n;
     for (int ix = 0; ix < nx; ++ix)
       for (int iq = 0; iq < nq; ++iq)
         for (int c = 0; c < P; ++c) {
@@ -606,7 +609,8 @@ extern "C" int pdf_load_alphas(int32_t n, const double* q2k, const double* a) {
   // the cells of every segment with their stencil values, the knots once each
   std::vector<double> hk;
   std::vector<AsCell> hc;
-  std::vector<short> hh, ref_hints;
+  std::vector<short> hh;
+  int ref_hints = 0;
   for (int lo = 0, i = 1; i <= n; ++i) {
     if (i < n && q2k[i] != q2k[i - 1]) continue;
     const int m = i - lo;  // knots lo .. i - 1 form a segment
@@ -622,9 +626,8 @@ extern "C" int pdf_load_alphas(int32_t n, const double* q2k, const double* a) {
       hc.push_back(ac);
     }
     // hints counted as per-segment lists for the size that pdf_mc_fused accepts
-    const size_t before = ref_hints.size();
-    build_hints(q2k + lo, m, ref_hints);
-    if ((int)ref_hints.size() > kAlphasMaxHints) ref_hints.resize(before);
+    const int buckets = hint_buckets(q2k + lo, m).n;
+    if (ref_hints + buckets <= kAlphasMaxHints) ref_hints += buckets;
     lo = i;
   }
   hk.push_back(q2k[n - 1]);
@@ -657,7 +660,7 @@ extern "C" int pdf_load_alphas(int32_t n, const double* q2k, const double* a) {
     return fail_hip(e, "hipMemcpy(alpha_s)");
   }
   A.tables = static_cast<const unsigned char*>(mem);
-  g_alphas_mc_bytes = align_up(n, 2) * (8 + 8 + 48) + align_up(ref_hints.size(), 8) * 2;
+  g_alphas_mc_bytes = align_up(n, 2) * (8 + 8 + 48) + align_up((size_t)ref_hints, 8) * 2;
   if (g_alphas_mem) (void)hipFree(g_alphas_mem);
   g_alphas_mem = mem;
   g_alphas = A;
