@@ -107,6 +107,15 @@ int pdf_load_alphas(int32_t n_knots, const double* q2_knots, const double* alpha
  *                 requested flavours
  * n == 0 is a no-op.  Errors: PDF_ERR_MEMBER, PDF_ERR_PID, PDF_ERR_ARG,
  * PDF_ERR_DEVICE.
+ *
+ * Memory: once a list of flavours other than every stored one in load order
+ * has been asked for at 2^21 points of a member, the call that gets there
+ * allocates a copy of the member's values in that order (here and in
+ * pdf_xfxq2_f32 and the pdf_xfxq2_alphas calls, a copy per precision; at most
+ * 16 MiB each and eight per member, freed by pdf_unload) and fills it on its
+ * stream; later calls read the copy, with identical results.  Nothing is
+ * allocated while the stream records a graph, a failed allocation is no
+ * error, and PDF_TUNE_VECTOR_COLUMNS = 0 declines the copies.
  */
 int pdf_xfxq2(int32_t member, const int32_t* pids, int32_t n_pids,
               const double* x, const double* q2, int64_t n,
@@ -173,12 +182,16 @@ int pdf_set_lds_policy(int32_t policy);
  * change speed).  Process-wide; set them before queueing work.
  *   PDF_TUNE_LDS_POLICY      as pdf_set_lds_policy (0, 1, 2)
  *   PDF_TUNE_VECTOR_COLUMNS  1: a request for every stored flavour in load
- *                            order is served by lanes that each own a
- *                            16-byte group of columns (2 FP64 / 4 FP32);
- *                            0: one lane per (point, flavour)
+ *                            order, or one whose columns the library has
+ *                            copied (see pdf_xfxq2 and pdf_batch_create), is
+ *                            served by lanes that each own a 16-byte group of
+ *                            columns (2 FP64 / 4 FP32); 0: one lane per
+ *                            (point, flavour), no copy is made or read, and
+ *                            plans are created without copies
  *   PDF_TUNE_BLOCKS_PER_CU   workgroups launched per compute unit when the
- *                            grid is read from global memory (1..4096;
- *                            capped at one 64-point tile per wave)
+ *                            grid is read from global memory (1..4096; fewer
+ *                            where a wave would have less than about three
+ *                            64-point tiles, but at least two if allowed)
  * PDF_ERR_ARG for an unknown knob or value out of range.
  */
 enum { PDF_TUNE_LDS_POLICY = 0, PDF_TUNE_VECTOR_COLUMNS = 1, PDF_TUNE_BLOCKS_PER_CU = 2 };
@@ -209,6 +222,11 @@ typedef struct {
  * members and the x / q2 / out buffers named by the requests must stay valid
  * for the plan's lifetime; running the plan again evaluates whatever the x
  * and q2 buffers then hold.  *plan_out receives the plan id.
+ * Memory: a plan with FP64 outputs keeps copies of the members' values in the
+ * order of its requests (those of two or more flavours that are not every
+ * stored one in load order; at most 256 MiB per plan, freed by
+ * pdf_batch_destroy; without them if they cannot be allocated or
+ * PDF_TUNE_VECTOR_COLUMNS is 0).  The one-shot calls make none.
  */
 int pdf_batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, int32_t* plan_out);
 /*

@@ -1324,7 +1324,7 @@ int batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, bool c
       b.layout = B.layouts.insert({{b.member, list}, (int)B.layouts.size()}).first->second;
       B.compact_elems = std::max(B.compact_elems, (int64_t)M->dev.rows * kCompactCols);
     }
-    if (copies && P.out_f64 && !b.all_cols && b.R >= 2 && q.n > 0) {
+    if (copies && g_vector_cols && P.out_f64 && !b.all_cols && b.R >= 2 && q.n > 0) {
       const int c = B.copy_of(P, b.member, *M, rcols, list);
       if (c >= 0) {
         b.member = c;
@@ -1408,7 +1408,7 @@ int batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, bool c
 }  // namespace
 
 extern "C" int pdf_batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, int32_t* plan_out) {
-  const int rc = batch_create(reqs, n_req, out_f64, true, plan_out);
+  const int rc = batch_create(reqs, n_req, out_f64, true, plan_out);  // with copies unless declined
   return rc == kRetryPlain ? batch_create(reqs, n_req, out_f64, false, plan_out) : rc;
 }
 
