@@ -44,7 +44,7 @@ __device__ __forceinline__ f64x2 load2(const double* p) {
 // takes k0 + 8 j + 2 q and + 1, so a load is 16 bytes per lane and 64
 // contiguous bytes per row.  The four waves of a workgroup take four ranges of
 // k of one tile and add their sums through LDS at the end, which leaves few
-// slices to add in global memory.  K = 31395, 1024 table rows: 10 members 59 us
+// slices to add in global memory.  K = 31395, 1024 table rows: 10 members 59-63 us
 // (staged tiles of 64 or 80 x 128: 101), 30: 79 (104), 50: 99 (108), 80: 122
 // (130), 100: 144 (164); 100 rows x 100 members 42 (65).  400 members took 496
 // us here and 456 with the staged tiles, whose operands eight waves share.

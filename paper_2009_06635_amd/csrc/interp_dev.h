@@ -33,12 +33,15 @@ __device__ __forceinline__ Tables tables_at(const unsigned char* base, const Mem
 
 __device__ __forceinline__ int high_word(double v) { return __double2hiint(v); }
 
-// ln v by table (Tang's method): v = 2^k z with z in [0.6875, 1.375), z in
-// interval i of 128 with c_i near its middle, r = z / c_i - 1, |r| <= 2^-7:
+// ln v by table, by the method of the log function of Arm's Optimized Routines
+// (MIT, or Apache-2.0 with LLVM exception): reduction by the high word to
+// v = 2^k z, z in [0.6875, 1.375); z in interval i of 128 with c_i near its
+// middle; r = z / c_i - 1 by one fma, |r| <= 2^-7;
 // ln v = k ln 2 + ln c_i + log1p(r).  The two intervals next to 1 have c = 1,
 // so small logarithms keep their relative precision; ln 2 is split so that
 // k ln 2's high part is exact, the error of its sum with ln c_i is carried,
-// and the c_i are chosen so that ln c_i is a double to about 1/64 ulp.  Error
+// and the c_i are chosen so that ln c_i is a double to about 1/64 ulp.  The
+// table is made by make_log_table, log1p is its plain series.  Error
 // against long double: rms 0.28-0.31 ulp, as the correctly rounded result's,
 // at most 1 ulp.  About 25 instructions and one 16-byte table read; with the
 // library function (about 100) alpha_s of 1e7 points took 86 us, now 37.

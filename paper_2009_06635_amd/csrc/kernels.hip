@@ -10,13 +10,17 @@
 // Extrapolation (figure 1 EXTRAPOLATE) uses anchor values on the edge rows or
 // columns of the same stencil, combined in FP64.
 //
-// Work split per tile of 256 points:
-//   phase 1, one lane per point: validate, region, sub-grid, FP64 knot search
-//     (raw FP64 comparisons), FP64 log transform, Hermite weights -> LDS;
-//   phase 2, one lane per (point, flavour), consecutive lanes on consecutive
-//     output elements (coalesced point-major stores): 16 grid reads from LDS
-//     (grid staged once per workgroup when it fits) or from L2-resident
-//     global memory, 20 FMAs.
+// Work split: each wave takes its own tiles of 64 points (8 to 32 in small
+// calls), with no workgroup barrier after the tables are staged.
+//   phase 1, one lane per point: validate, region, one FP64 knot search per
+//     axis (raw FP64 comparisons, all Q^2 sub-grids in one table), logarithms
+//     by table, Hermite weights -> the wave's records in LDS;
+//   phase 2, one lane per (point, flavour), or per (point, group of columns of
+//     up to 16 bytes) where the request is every stored column in order or has
+//     a compacted copy; consecutive lanes on consecutive output elements
+//     (coalesced point-major stores): 16 grid reads from LDS (grid staged once
+//     per workgroup when it fits) or from L2-resident global memory, 20 FMAs
+//     per value.  Points outside the grid wait in a list until they fill a pass.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -541,8 +545,9 @@ __global__ __launch_bounds__(256) void k_alphas(AlphasDev A, const double* __res
 // Launchers (host side, called by pdfmi.cpp)
 
 // Location tables up to this size are staged in LDS (typical sets need
-// 10-40 KB: a few hundred knots of 8 bytes plus 48 bytes of coefficients per
-// cell); larger ones are read from global memory.
+// 10-40 KB: a few hundred knots of 8 bytes, 48 bytes per x cell, 80 per Q^2
+// cell, the hints and 2 KB for the logarithm); larger ones are read from
+// global memory.
 constexpr size_t kMaxLdsTables = 64 * 1024;
 static bool tables_fit(const MemberDev& m) { return (size_t)m.tbl_bytes <= kMaxLdsTables; }
 
