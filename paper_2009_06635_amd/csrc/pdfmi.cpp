@@ -924,8 +924,9 @@ struct RunPool {
   int next = 0, recorded = 0;
 } g_runs;
 
-int runs_init() {
-  if (g_runs.dev) return PDF_OK;
+// Without the pool (no memory) every run goes without a counter.
+void runs_init() {
+  if (g_runs.dev) return;
   RunPool p;
   hipError_t e = hipMalloc(&p.dev, sizeof(RunSlot) * kRunSlots);
   if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&p.host), sizeof(unsigned) * kRunSlots,
@@ -936,13 +937,13 @@ int runs_init() {
   if (e != hipSuccess) {
     if (p.dev) (void)hipFree(p.dev);
     if (p.host) (void)hipHostFree(p.host);
-    return fail_hip(e, "counters of batched runs");
+    (void)hipGetLastError();
+    return;
   }
   std::memset(p.host, 0, sizeof(unsigned) * kRunSlots);
   p.run.assign(kRunSlots, 0);
   p.kept.assign(kRunSlots, false);
   g_runs = std::move(p);
-  return PDF_OK;
 }
 
 bool run_ended(int slot) { return __atomic_load_n(&g_runs.host[slot], __ATOMIC_ACQUIRE) == g_runs.run[slot]; }
@@ -959,7 +960,7 @@ void run_cancel(int slot) { __atomic_store_n(&g_runs.host[slot], g_runs.run[slot
 // A free slot, or -1 if none of the next few is: they are given out in turn,
 // so only runs far behind, or very many, are in the way.
 int run_slot() {
-  for (int i = 0; i < 64; ++i) {
+  for (int i = 0; g_runs.dev && i < 64; ++i) {
     const int k = g_runs.next;
     g_runs.next = (k + 1) % kRunSlots;
     if (!g_runs.kept[k] && run_ended(k)) return k;
@@ -1282,8 +1283,8 @@ int batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, bool c
   if (!plan_out || (n_req > 0 && !reqs) || n_req < 0) return fail(PDF_ERR_ARG, "bad argument");
   std::lock_guard<std::mutex> lock(g_mu);
   int rc = ensure_init();
-  if (rc == PDF_OK) rc = runs_init();
   if (rc != PDF_OK) return rc;
+  runs_init();
   Plan P;
   P.used = true;
   P.out_f64 = out_f64 ? 1 : 0;
