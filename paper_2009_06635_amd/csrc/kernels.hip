@@ -977,12 +977,13 @@ __device__ __forceinline__ T mc_value(const T* g, const PointLoc& L, const McOri
                                    w[2], w[3], v[0], v[1], v[2], v[3], L.p0, L.p1, invL01, lt);
 }
 
-// What k_mc_fused stages of the tables: nothing, alpha_s (with the logarithm's
-// table), or the member's location tables too.
+// What k_mc_fused stages of the tables: the logarithm's alone (an extrapolated
+// value waits for up to four logarithms, one after another), alpha_s with it,
+// or the member's location tables too.
 enum McTables { kMcInPlace, kMcAlphas, kMcAll };
 
 __host__ __device__ static inline int mc_alphas_bytes(const AlphasDev& A, McTables staged) {
-  return staged == kMcInPlace ? 0 : alphas_staged_bytes(A, staged == kMcAll);
+  return staged == kMcInPlace ? A.bytes - A.logt_off : alphas_staged_bytes(A, staged == kMcAll);
 }
 
 template <typename T, bool kLdsGrid, int kGW, McTables kStaged = kMcAll>
@@ -1004,7 +1005,7 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
   T* sgrid = reinterpret_cast<T*>(sstep + kMaxReq + 4);   // 16-byte aligned: 2 kMaxReq + 4 ints
 
   if constexpr (kLdsTables) stage_copy<kMcFusedBS>(stbl, m.tables, m.tbl_bytes);
-  if constexpr (kStaged != kMcInPlace) stage_copy<kMcFusedBS>(sas, A.tables, as_bytes);
+  stage_copy<kMcFusedBS>(sas, A.tables + (kStaged == kMcInPlace ? A.logt_off : 0), as_bytes);
   for (int i = threadIdx.x; i < rc.n; i += kMcFusedBS) scol[i] = rc.col[i];
   const int Pp = sizeof(T) == 8 ? m.P64 : m.P32;
   const T* __restrict__ gvals = member_values<T>(m);
@@ -1016,7 +1017,7 @@ __global__ __launch_bounds__(kMcFusedBS) void k_mc_fused(MemberDev m, ReqCols rc
   if constexpr (kLdsGrid) stage_rows<kMcFusedBS>(sgrid, gvals, m.rows, P, Pp);
   __syncthreads();
   Tables tb = tables_at(kLdsTables ? stbl : m.tables, m);
-  if constexpr (kStaged == kMcAlphas) tb.logt = reinterpret_cast<const LogEntry*>(sas + A.logt_off);
+  if constexpr (!kLdsTables) tb.logt = reinterpret_cast<const LogEntry*>(sas + (kStaged == kMcAlphas ? A.logt_off : 0));
   const AsView av{kStaged == kMcInPlace ? A.tables : sas, tb.logt, nullptr};
   const T* grid = kLdsGrid ? sgrid : gvals;
 
@@ -1248,7 +1249,11 @@ hipError_t launch_mc_fused(const MemberDev& m, const ReqCols& rc, const AlphasDe
         form = &f;
         shm = b;
       }
-      if (form->elems && !f.elems) break;  // a grid in LDS comes first
+      // a grid in LDS comes first; in FP32 and with few blocks not before four
+      // quarters on one (50 x 56 x 13, 10^5 points: 101 us, from global memory
+      // 79, and with 5 % of the points outside 207 and 96; 2 10^5 points: 103 and
+      // 108; FP64, 50 x 33 x 11, 10^5 points: 86 and 198)
+      if (form->elems && !f.elems && !(kGW > 1 && 2 * np <= n_cu)) break;
       if (b + kTree <= 160 * 1024 && rounds(b + kTree, 1) < rounds(b, 4)) {
         form = &f;
         shm = b + kTree;

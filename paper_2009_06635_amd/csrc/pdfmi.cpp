@@ -744,7 +744,7 @@ static const MemberDev* use_layout(Member& M, bool f32, int64_t n, ReqCols& rc, 
     if (M.layouts.size() >= kMaxLayouts) return &d;
     Layout made;
     made.key = key;
-    made.stride = layout_stride(rc.n, f32, d.rows, (int64_t)kLdsBytes - 1024 - (int64_t)xfxq2_shared_bytes(d, f32, true));
+    made.stride = layout_stride(rc.n, f32, d.rows, (int64_t)kLdsBytes - 1024 - (int64_t)xfxq2_shared_bytes(d, f32, false));
     // nothing is made while the stream records a graph
     if (!layout_small(f32, d.rows, made.stride) || !M.wanted.add(key, n) || capturing(stream)) return &d;
     if (!make_layout(made, M, rc, stream)) {
