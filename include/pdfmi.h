@@ -172,7 +172,8 @@ int pdf_validate_alphas(int32_t n_knots, const double* q2_knots, const double* a
  *   0 = automatic (stage when it fits and the call has enough points to pay
  *       for one grid copy per workgroup), 1 = never, 2 = whenever it fits.
  * A batch plan takes the policy in force when it is created: 1 reads the
- * grids from global memory, 0 and 2 stage them whenever the largest fits.
+ * grids from global memory, 2 stages them whenever the largest fits, and 0
+ * too, unless it barely fits and the plan is small.
  * Results are identical under every policy.
  */
 int pdf_set_lds_policy(int32_t policy);

@@ -1329,7 +1329,9 @@ namespace pdfmi {
 // With more points they are the slower ones, as twice as many tiles, and so
 // members, share the caches (100 requests of 30000 points, 100 members of 1.3
 // MB, FP64, one column: 576 us where 1024 threads took 475).
-constexpr int kBatchThreads = 1024, kBatchHalf = 512;
+// Grids that fit LDS only without four of the 16 waves' records get workgroups
+// of 12 (kBatchSmall).
+constexpr int kBatchThreads = 1024, kBatchSmall = 768, kBatchHalf = 512;
 constexpr int kCompactRowB = kCompactCols * 4;
 
 // kCounted: more tiles than workgroups (without it the arguments of the counter alone cost 0.3 us a run).
@@ -1472,7 +1474,9 @@ size_t batch_shared_bytes(int max_tbl, bool f32, bool lds, int block) {
 
 template <typename T, bool kCounted>
 static const void* batch_fn(bool lds, bool tables, int block) {
-  if (lds) return reinterpret_cast<const void*>(&k_batched<T, true, true, kCounted, kBatchThreads>);
+  if (lds)
+    return block == kBatchThreads ? reinterpret_cast<const void*>(&k_batched<T, true, true, kCounted, kBatchThreads>)
+                                  : reinterpret_cast<const void*>(&k_batched<T, true, true, kCounted, kBatchSmall>);
   if (!kCounted && block == kBatchHalf)
     return tables ? reinterpret_cast<const void*>(&k_batched<T, false, true, false, kBatchHalf>)
                   : reinterpret_cast<const void*>(&k_batched<T, false, false, false, kBatchHalf>);

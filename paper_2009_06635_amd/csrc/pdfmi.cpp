@@ -973,6 +973,7 @@ struct Plan {
   int out_f64 = 0;
   int tile_points = 4096;
   int block = 1024;  // threads of a workgroup
+  int lds_block = 1024;  // the same with grids in LDS
   int vector_cols = 1;
   int use_graph = 0;
   bool lds = false;
@@ -1042,13 +1043,13 @@ int plan_tiles(Plan& P) {
   std::vector<int64_t> counts;
   for (const BatchReq& r : P.reqs) counts.push_back(r.n);
   const BatchTiling cut = batch_tiling(P.lds, P.tile_points, counts, g_ncu);
-  P.block = cut.block;
+  P.block = P.lds ? P.lds_block : cut.block;
   for (int r : order) {
     const int64_t n = P.reqs[r].n;
     // workgroups of one tile each: a request's tiles alike (700 points as 384
     // and 316, not 512 and 188); else the remainders fill the end of the run
     const int64_t k = (n + cut.points - 1) / cut.points;
-    const int64_t tp = cut.block == 1024 || k == 0 ? cut.points : ((n + k - 1) / k + 63) / 64 * 64;
+    const int64_t tp = P.block != 512 || k == 0 ? cut.points : ((n + k - 1) / k + 63) / 64 * 64;
     for (int64_t s0 = 0; s0 < n; s0 += tp) t.push_back(BatchTile{r, (int)std::min<int64_t>(tp, n - s0), s0});
   }
   if ((int64_t)t.size() > (1LL << 30)) return fail(PDF_ERR_ARG, "too many tiles");
@@ -1345,12 +1346,21 @@ int batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, bool c
     plan_release(P);
     return kRetryPlain;
   }
-  P.lds = g_lds_policy != 1 &&
-          batch_shared_bytes(P.max_tbl, !P.out_f64, true, 1024) + (size_t)P.max_elems * (P.out_f64 ? 8 : 4) <=
-              kLdsBytes - 1024;
+  // the grids in LDS where the largest fits beside the records of 16 waves, or
+  // of 12 if there is more than a round of half-size workgroups to do (30
+  // requests of 3000 points on 100 x 51 x 2 values in FP32, all outside the grid:
+  // 21 us, from global memory 15; of 100000 points inside it: 70 and 156)
+  int64_t half = 0;
+  for (const BatchReq& r : P.reqs) half += (r.n + 511) / 512;
+  auto fits = [&](int64_t elems, int block) {
+    return batch_shared_bytes(P.max_tbl, !P.out_f64, true, block) + (size_t)elems * (P.out_f64 ? 8 : 4) <= kLdsBytes - 1024;
+  };
+  P.lds_block = fits(P.max_elems, 1024) ? 1024 : 768;
+  P.lds = g_lds_policy != 1 && fits(P.max_elems, P.lds_block) &&
+          (P.lds_block == 1024 || g_lds_policy == 2 || half > 2 * (int64_t)g_ncu);
   // compacted layouts when their rows fit LDS too
   if (P.lds && B.compact_elems > P.max_elems) {
-    if (batch_shared_bytes(P.max_tbl, true, true, 1024) + (size_t)B.compact_elems * 4 <= kLdsBytes - 1024)
+    if (fits(B.compact_elems, P.lds_block))
       P.max_elems = B.compact_elems;
     else
       for (BatchReq& b : P.reqs) b.layout = -1;
