@@ -19,6 +19,7 @@
 
 #include "layouts.h"
 #include "pdfmi_dev.h"
+#include "tiles.h"
 
 namespace pdfmi {
 size_t xfxq2_shared_bytes(const MemberDev& m, bool f32, bool small);
@@ -1053,6 +1054,17 @@ int plan_tiles(Plan& P) {
     for (int64_t s0 = 0; s0 < n; s0 += tp) t.push_back(BatchTile{r, (int)std::min<int64_t>(tp, n - s0), s0});
   }
   if ((int64_t)t.size() > (1LL << 30)) return fail(PDF_ERR_ARG, "too many tiles");
+  // one tile per workgroup: dealt out by cost, points times columns (46 requests
+  // of 1000 to 15900 points and 1 to 11 columns, FP64: 22.8 us in request order,
+  // 20.4 so, 20.8 one by one; 50 requests of 5000 points and 13 columns, 50
+  // members: 34, 34 and 69 us)
+  if (P.block == 512) {
+    std::vector<int64_t> cost;
+    for (const BatchTile& b : t) cost.push_back((int64_t)b.count * P.reqs[b.req].R);
+    std::vector<BatchTile> dealt;
+    for (size_t i : deal_tiles(cost)) dealt.push_back(t[i]);
+    t.swap(dealt);
+  }
   // the costliest tiles first (points times groups of four columns), so that
   // the workgroups end together on small ones; equal tiles stay grouped.  Not
   // where the grids are read from global memory: there a request's tiles belong
