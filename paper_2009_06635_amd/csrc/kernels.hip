@@ -31,6 +31,7 @@
 
 #include "interp_dev.h"
 #include "layouts.h"
+#include "tiles.h"
 #include "pdfmi_dev.h"
 
 namespace pdfmi {
@@ -1331,7 +1332,6 @@ namespace pdfmi {
 // MB, FP64, one column: 576 us where 1024 threads took 475).
 // Grids that fit LDS only without four of the 16 waves' records get workgroups
 // of 12 (kBatchSmall).
-constexpr int kBatchThreads = 1024, kBatchSmall = 768, kBatchHalf = 512;
 constexpr int kCompactRowB = kCompactCols * 4;
 
 // kCounted: more tiles than workgroups (without it the arguments of the counter alone cost 0.3 us a run).
@@ -1482,58 +1482,6 @@ static const void* batch_fn(bool lds, bool tables, int block) {
                   : reinterpret_cast<const void*>(&k_batched<T, false, false, false, kBatchHalf>);
   return tables ? reinterpret_cast<const void*>(&k_batched<T, false, true, kCounted, kBatchThreads>)
                 : reinterpret_cast<const void*>(&k_batched<T, false, false, kCounted, kBatchThreads>);
-}
-
-// How the requests of a plan (n[i] points each) are cut into tiles of at most
-// `asked` points.  A plan of few tiles takes smaller ones, down to one pass of a
-// workgroup, where it then ends sooner.  The time is estimated in half passes:
-// a tile takes its passes and about one for the staging of the grid, or half
-// of one for the tables alone.  The compute units share the tiles, so the time
-// is at least their mean and, for every k, k + 1 of the tiles that the first k
-// rounds leave; the costliest come first where grids are in LDS, else the
-// compute units end half a tile apart on the average.
-BatchTiling batch_tiling(bool lds, int asked, const std::vector<int64_t>& n, int n_cu) {
-  int64_t half = 0;
-  for (int64_t ni : n) half += (ni + kBatchHalf - 1) / kBatchHalf;
-  if (!lds && asked >= kBatchHalf && half <= 2 * (int64_t)n_cu) return {kBatchHalf, kBatchHalf};
-  const int setup = lds ? 2 : 1;
-  int64_t tiles = 0;
-  std::vector<int64_t> count;  // tiles by passes
-  auto time_of = [&](int points) {
-    auto passes = [](int64_t p) { return (p + kBatchThreads - 1) / kBatchThreads; };
-    count.assign((size_t)passes(points) + 1, 0);
-    tiles = 0;
-    for (int64_t ni : n) {
-      const int64_t whole = ni / points, rest = ni - whole * points;
-      count[(size_t)passes(points)] += whole;
-      if (rest > 0) ++count[(size_t)passes(rest)];
-      tiles += whole + (rest > 0);
-    }
-    double work = 0.0, least = 0.0, longest = 0.0;
-    int64_t before = 0;  // tiles at least as costly
-    for (int64_t p = (int64_t)count.size() - 1; p >= 0; --p) {
-      if (count[p] == 0) continue;
-      const double c = 2.0 * p + setup;
-      longest = std::max(longest, c);
-      before += count[p];
-      work += c * count[p];
-      least = std::max(least, ((before - 1) / n_cu + 1) * c);
-    }
-    work /= n_cu;
-    return std::max(least, tiles <= n_cu || lds ? work : work + 0.5 * longest);
-  };
-  BatchTiling best{asked, kBatchThreads};
-  double least = time_of(asked);
-  if (tiles >= 2 * (int64_t)n_cu) return best;
-  for (int t = asked; t > kBatchThreads;) {
-    t = std::max(kBatchThreads, (t / 2 + 63) / 64 * 64);
-    const double c = time_of(t);
-    if (c < least) {
-      least = c;
-      best.points = t;
-    }
-  }
-  return best;
 }
 
 BatchLaunch batch_launch_params(bool f32, bool lds, int max_tbl, int64_t max_elems, int n_cu, int ntiles, int block) {

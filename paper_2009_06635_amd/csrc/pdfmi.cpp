@@ -38,7 +38,6 @@ hipError_t launch_alphas(const AlphasDev&, const double*, int64_t, double*, unsi
 int64_t mc_partials(int64_t n);
 size_t batch_shared_bytes(int max_tbl, bool f32, bool lds, int block);
 BatchLaunch batch_launch_params(bool f32, bool lds, int max_tbl, int64_t max_elems, int n_cu, int ntiles, int block);
-BatchTiling batch_tiling(bool lds, int asked, const std::vector<int64_t>& n, int n_cu);
 hipError_t batch_prepare(const BatchLaunch& L);
 hipError_t batch_launch(const BatchLaunch& L, void** args, hipStream_t s);
 int sur_nparams();
@@ -1041,16 +1040,16 @@ int plan_tiles(Plan& P) {
   std::vector<int> order(P.reqs.size());
   for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return P.reqs[a].member < P.reqs[b].member; });
-  std::vector<int64_t> counts;
-  for (const BatchReq& r : P.reqs) counts.push_back(r.n);
-  const BatchTiling cut = batch_tiling(P.lds, P.tile_points, counts, g_ncu);
+  std::vector<TileReq> sizes;
+  for (const BatchReq& r : P.reqs) sizes.push_back(TileReq{r.n, r.R});
+  const BatchTiling cut = batch_tiling(P.lds, P.tile_points, sizes, g_ncu);
   P.block = P.lds ? P.lds_block : cut.block;
   for (int r : order) {
     const int64_t n = P.reqs[r].n;
     // workgroups of one tile each: a request's tiles alike (700 points as 384
     // and 316, not 512 and 188); else the remainders fill the end of the run
     const int64_t k = (n + cut.points - 1) / cut.points;
-    const int64_t tp = P.block != 512 || k == 0 ? cut.points : ((n + k - 1) / k + 63) / 64 * 64;
+    const int64_t tp = P.block != kBatchHalf || k == 0 ? cut.points : ((n + k - 1) / k + 63) / 64 * 64;
     for (int64_t s0 = 0; s0 < n; s0 += tp) t.push_back(BatchTile{r, (int)std::min<int64_t>(tp, n - s0), s0});
   }
   if ((int64_t)t.size() > (1LL << 30)) return fail(PDF_ERR_ARG, "too many tiles");
@@ -1058,7 +1057,7 @@ int plan_tiles(Plan& P) {
   // of 1000 to 15900 points and 1 to 11 columns, FP64: 22.8 us in request order,
   // 20.4 so, 20.8 one by one; 50 requests of 5000 points and 13 columns, 50
   // members: 34, 34 and 69 us)
-  if (P.block == 512) {
+  if (P.block == kBatchHalf) {
     std::vector<int64_t> cost;
     for (const BatchTile& b : t) cost.push_back((int64_t)b.count * P.reqs[b.req].R);
     std::vector<BatchTile> dealt;
@@ -1367,9 +1366,9 @@ int batch_create(const pdf_request* reqs, int32_t n_req, int32_t out_f64, bool c
   auto fits = [&](int64_t elems, int block) {
     return batch_shared_bytes(P.max_tbl, !P.out_f64, true, block) + (size_t)elems * (P.out_f64 ? 8 : 4) <= kLdsBytes - 1024;
   };
-  P.lds_block = fits(P.max_elems, 1024) ? 1024 : 768;
+  P.lds_block = fits(P.max_elems, kBatchThreads) ? kBatchThreads : kBatchSmall;
   P.lds = g_lds_policy != 1 && fits(P.max_elems, P.lds_block) &&
-          (P.lds_block == 1024 || g_lds_policy == 2 || half > 2 * (int64_t)g_ncu);
+          (P.lds_block == kBatchThreads || g_lds_policy == 2 || half > 2 * (int64_t)g_ncu);
   // compacted layouts when their rows fit LDS too
   if (P.lds && B.compact_elems > P.max_elems) {
     if (fits(B.compact_elems, P.lds_block))

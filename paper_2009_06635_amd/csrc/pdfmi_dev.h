@@ -179,11 +179,6 @@ struct CompactJob {
   ReqCols rc;
 };
 
-// How a batched plan is cut: points per tile, threads per workgroup.
-struct BatchTiling {
-  int points, block;
-};
-
 // Kernel node parameters of one batched run (the persistent kernel).
 struct BatchLaunch {
   const void* main_fn;
